@@ -33,6 +33,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -509,6 +510,7 @@ struct GParams {
   const uint32_t* meta;
   const float* lamf;
   const int32_t* active;         // per-instance flag (NULL: all)
+  double* part;                  // cut sequences: the groups' FP64 terms go here (NULL: carried)
   double scale;
   int32_t nchunk;
 };
@@ -967,8 +969,10 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
         for (int o = 0; o < kGrpComps; ++o) {
           if (CARRY) {
             acc[o][k] = ((G.acc & (1 << o)) ? 0.0 : acc[o][k]) + val[o];
-            if (G.out[o] >= 0 && (G.acc & (1 << (4 + o))) && h < G.stride)
-              out[G.out[o] + h] = h < n_own ? (float)(sl * acc[o][k]) : 0.f;
+            if (G.out[o] >= 0 && (G.acc & (1 << (4 + o))) && h < G.stride) {
+              if (P.part) P.part[G.out[o] + h] = acc[o][k];
+              else out[G.out[o] + h] = h < n_own ? (float)(sl * acc[o][k]) : 0.f;
+            }
           } else if (G.out[o] >= 0 && h < G.stride) {
             out[G.out[o] + h] = h < n_own ? (float)(sl * val[o]) : 0.f;
           }
@@ -980,6 +984,36 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       __syncthreads();   // the next group's staging overwrites the prefix slots
     }
   }
+}
+
+// Rows of cut sequences: the FP64 terms of a row's groups, added in group
+// order (the carrying kernel's own order and type, so the sums are the same
+// bits), weighted and rounded once.  blockIdx.x: row of either direction,
+// blockIdx.y: 256 of its hands.  Latency-bound: a turn all-in row over 48
+// river cards is 48 independent coalesced loads per hand.
+struct GRed {
+  int32_t out;                   // element offset of the output row
+  int32_t part;                  // element offset of its first term (terms `stride` apart)
+  int32_t n, stride, n_own;      // terms; row length incl. padding; own hands
+  int32_t inst;
+  int64_t lam_off;               // own hands' lambda
+};
+__global__ __launch_bounds__(256) void k_grp_reduce(const GRed* __restrict__ r0, int n0,
+                                                    const double* __restrict__ part0, float* __restrict__ out0,
+                                                    double scale0, const GRed* __restrict__ r1,
+                                                    const double* __restrict__ part1, float* __restrict__ out1,
+                                                    double scale1, const float* __restrict__ lamf,
+                                                    const int32_t* __restrict__ active) {
+  const bool second = (int)blockIdx.x >= n0;
+  const GRed r = second ? r1[blockIdx.x - n0] : r0[blockIdx.x];
+  const int h = (int)(blockIdx.y * 256 + threadIdx.x);
+  if (h >= r.stride || (active && !active[r.inst])) return;
+  const double* __restrict__ p = (second ? part1 : part0) + r.part + h;
+  double v = 0.0;
+#pragma unroll 16
+  for (int j = 0; j < r.n; ++j) v += p[(int64_t)j * r.stride];
+  const double sl = (second ? scale1 : scale0) * (double)(h < r.n_own ? lamf[r.lam_off + h] : 0.f);
+  (second ? out1 : out0)[r.out + h] = h < r.n_own ? (float)(sl * v) : 0.f;
 }
 
 // ---------------------------------------------------------------------------
@@ -1930,6 +1964,15 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
   int count[GrpDir::kKinds][kGrpClasses] = {};
   DBuf<int32_t> chunks_act[GrpDir::kKinds][kGrpClasses];   // the solver's lists: active instances only
   int count_act[GrpDir::kKinds][kGrpClasses] = {};
+  // sequences carrying sums over many groups, cut into their groups
+  // (cut_sequences): chunks per class, the rows their terms add up to, and
+  // the terms, one buffer for the solver's products and one for the others
+  std::vector<int32_t> cut_h[kGrpClasses];
+  DBuf<int32_t> cut[kGrpClasses], cut_act[kGrpClasses];
+  int n_cut[kGrpClasses] = {}, n_cut_act[kGrpClasses] = {};
+  DBuf<GRed> red;
+  int n_red = 0, red_blocks = 0;
+  DBuf<double> part[2];
   bool built = false;
 };
 
@@ -2034,6 +2077,7 @@ struct Game {
   hipStream_t side[kSide] = {};
   hipEvent_t fork_ev = nullptr, join_ev[kSide] = {};
   bool fork_ok = false;
+  std::mutex fork_mu;               // the side streams and their events, one product at a time
   ~Game() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -2156,7 +2200,103 @@ static int upload_grp_active(Game* g, int d) {
       if (rc) return rc;
       E.count_act[kind][c] = (int)L.size() / 4;
     }
+  for (int c = 0; c < kGrpClasses; ++c) {
+    std::vector<int32_t> L;
+    const std::vector<int32_t>& F = E.cut_h[c];
+    for (size_t i = 0; i + 3 < F.size(); i += 4)
+      if (all || g->listed[F[i + 2]]) L.insert(L.end(), F.begin() + i, F.begin() + i + 4);
+    int rc = E.cut_act[c].upload(L);
+    if (rc) return rc;
+    E.n_cut_act[c] = (int)L.size() / 4;
+  }
   return PMX_OK;
+}
+
+// Groups a sequence must have before its product cuts it.  A sequence's
+// groups otherwise run one after another in one workgroup, about 9 us each
+// at 1,128 hands: the turn + river game's 8 sequences of 49 groups took
+// 431 us of a 450 us product whose other 7,000 groups took 160 us.  Cut, they
+// are 392 workgroups beside the others and a sum of 7 us: 145 us per product.
+// Below some eight groups the fork, the join and the sum cost what they save.
+static constexpr int kCutMinGroups = 8;
+
+// Cuts the carrying sequences (kind 1) of a direction into their groups when
+// one of them is long: every group becomes a chunk of its own that writes its
+// outputs' FP64 terms to rows of the term buffer, and k_grp_reduce adds a
+// row's terms in group order.  The uncut chunks stay: a product that a caller
+// captures takes them, since replays of its graph may overlap other calls
+// and the term buffer is the game's.
+static int cut_sequences(Game* g, int d, std::vector<GGroup>& groups) {
+  DevGrp& E = g->dg[d];
+  const GrpDir& M = g->hg.grp[d];
+  std::vector<GRed> red;
+  std::vector<std::array<std::array<int, 2>, kGrpComps>> term;   // (row in red, term of the row) per output of a cut group
+  int longest = 0, max_stride = 0;
+  const size_t n_uncut = groups.size();
+  for (int c = 0; c < kGrpClasses; ++c) {
+    E.cut_h[c].clear();
+    const std::vector<int32_t>& F = M.chunks[1][c];
+    for (size_t i = 0; i + 3 < F.size(); i += 4) {
+      int at[kGrpComps] = {-1, -1, -1, -1};   // each slot's row in red
+      int len = 0;
+      for (int gi = F[i]; gi < F[i + 1]; ++gi, ++len) {
+        GGroup G = M.groups[gi];
+        std::array<std::array<int, 2>, kGrpComps> tm{};
+        bool any = false;
+        for (int o = 0; o < kGrpComps; ++o) {
+          if (G.out[o] < 0) continue;
+          if (G.acc & (1 << o)) {
+            len = 0;
+            at[o] = (int)red.size();
+            GRed r{};
+            r.out = G.out[o];
+            r.stride = G.stride;
+            r.n_own = G.n_own;
+            r.inst = F[i + 2];
+            r.lam_off = M.ctx[G.ctx].lam_own_off;
+            red.push_back(r);
+            max_stride = std::max(max_stride, G.stride);
+          }
+          if (G.ks[o] == 0.0 && G.kf[o] == 0.0) {   // the row has no term in this group
+            G.out[o] = -1;
+            continue;
+          }
+          G.acc |= (1 << o) | (1 << (4 + o));       // starts and ends here
+          tm[o] = {at[o], red[at[o]].n++};
+          any = true;
+        }
+        longest = std::max(longest, len + 1);
+        if (!any) continue;
+        E.cut_h[c].insert(E.cut_h[c].end(), {(int32_t)groups.size(), (int32_t)groups.size() + 1, F[i + 2], G.ctx});
+        groups.push_back(G);
+        term.push_back(tm);
+      }
+    }
+  }
+  int64_t elems = 0;
+  for (const GRed& r : red) elems += (int64_t)r.n * r.stride;
+  E.n_red = 0;
+  if (longest < kCutMinGroups || elems >= ((int64_t)1 << 31)) {
+    for (auto& v : E.cut_h) v.clear();
+    groups.resize(n_uncut);
+    return PMX_OK;
+  }
+  elems = 0;
+  for (GRed& r : red) {
+    r.part = (int32_t)elems;
+    elems += (int64_t)r.n * r.stride;
+  }
+  for (size_t k = 0; k < term.size(); ++k)
+    for (int o = 0; o < kGrpComps; ++o)
+      if (groups[n_uncut + k].out[o] >= 0) {
+        const GRed& r = red[term[k][o][0]];
+        groups[n_uncut + k].out[o] = r.part + term[k][o][1] * r.stride;
+      }
+  E.n_red = (int)red.size();
+  E.red_blocks = (max_stride + 255) / 256;
+  int rc = E.red.upload(red);
+  for (int k = 0; k < 2 && !rc; ++k) rc = E.part[k].alloc((size_t)elems);
+  return rc;
 }
 
 static int upload_grp(Game* g, int d) {
@@ -2174,9 +2314,15 @@ static int upload_grp(Game* g, int d) {
       M.ctx[ci].lam_own_off = g->lam_off[p][ii];
       M.ctx[ci].lam_opp_off = g->lam_off[q][ii];
     }
-  if ((rc = E.ctx.upload(M.ctx)) || (rc = E.groups.upload(M.groups)) || (rc = E.q.upload(M.q)) ||
+  std::vector<GGroup> groups = M.groups;
+  if ((rc = cut_sequences(g, d, groups))) return rc;
+  if ((rc = E.ctx.upload(M.ctx)) || (rc = E.groups.upload(groups)) || (rc = E.q.upload(M.q)) ||
       (rc = E.src.upload(M.src)) || (rc = E.meta.upload(M.meta)) || (rc = E.rk.upload(M.rk)))
     return rc;
+  for (int c = 0; c < kGrpClasses; ++c) {
+    if ((rc = E.cut[c].upload(E.cut_h[c]))) return rc;
+    E.n_cut[c] = (int)E.cut_h[c].size() / 4;
+  }
   for (int kind = 0; kind < GrpDir::kKinds; ++kind)
     for (int c = 0; c < kGrpClasses; ++c) {
       if ((rc = E.chunks[kind][c].upload(M.chunks[kind][c]))) return rc;
@@ -2441,9 +2587,14 @@ static void launch_mc_class(const McParams& A, const IO* in0, IO* out0, const Mc
 // Under stream capture the fork and join become graph edges.  A class's
 // tail then overlaps the others' work, and workgroups of different classes
 // share a CU's LDS.  `launch(i, stream, first)` enqueues launch i; `first`
-// marks the one launch that carries the iteration tick.
+// marks the one launch that carries the iteration tick.  `pinned` launches
+// (the first n_pinned) go to side stream 0 whatever the load, in order: work
+// on buffers of the game's own that successive products share is so ordered,
+// whatever streams those products are called on.
 template <typename F>
-static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, int64_t workgroups, F&& launch) {
+static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, int64_t workgroups, F&& launch,
+                         int n_pinned = 0) {
+  std::lock_guard<std::mutex> lock(g->fork_mu);
   int order[32];
   int64_t work[32];
   if (n > 32) return fail(PMX_EINVAL, "too many concurrent launches");
@@ -2451,20 +2602,23 @@ static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, 
     order[i] = i;
     work[i] = work_in[i];
   }
-  for (int i = 1; i < n; ++i)
-    for (int j = i; j > 0 && work[j] > work[j - 1]; --j) {
+  for (int i = n_pinned + 1; i < n; ++i)
+    for (int j = i; j > n_pinned && work[j] > work[j - 1]; --j) {
       std::swap(work[j], work[j - 1]);
       std::swap(order[j], order[j - 1]);
     }
   // a fork and join cost about ten microseconds: small products (a single
   // river endgame's) stay on the caller's stream
-  const int ns = (g->fork_ok && workgroups >= kForkMinWorkgroups) ? std::min(n, kForkStreams) : 1;
+  if (n_pinned && !g->fork_ok) return fail(PMX_ESTATE, "no side streams");
+  const int ns = (g->fork_ok && workgroups >= kForkMinWorkgroups) ? std::max(std::min(n, kForkStreams), n_pinned ? 2 : 1)
+               : n_pinned ? 2 : 1;
   int on[32];
   int64_t load[kForkStreams] = {};
   for (int i = 0; i < n; ++i) {
     int best = 0;
     for (int k = 1; k < ns; ++k)
       if (load[k] < load[best]) best = k;
+    if (i < n_pinned) best = 1;
     on[i] = best;
     load[best] += work[i];
   }
@@ -2532,12 +2686,16 @@ static int launch_mc(Game* g, const MvParams& P0, const IO* in0, IO* out0, const
   return PMX_OK;
 }
 
-static GParams grp_params(Game* g, int d, const MvParams& like, int kind, int c) {
+// cut: the carrying sequences (kind 1) by their groups, terms to the term
+// buffer; otherwise carried.
+static GParams grp_params(Game* g, int d, const MvParams& like, int kind, int c, bool cut) {
   DevGrp& E = g->dg[d];
   GParams P;
   const bool solver = like.active != nullptr;
+  cut = cut && kind == 1 && E.n_red > 0;
   P.groups = E.groups.p;
-  P.chunks = (const int4*)(solver ? E.chunks_act[kind][c].p : E.chunks[kind][c].p);
+  P.chunks = (const int4*)(cut ? (solver ? E.cut_act[c].p : E.cut[c].p)
+                               : (solver ? E.chunks_act[kind][c].p : E.chunks[kind][c].p));
   P.ctx = E.ctx.p;
   P.q = (const uint4*)E.q.p;
   P.rk = E.rk.p;
@@ -2545,8 +2703,11 @@ static GParams grp_params(Game* g, int d, const MvParams& like, int kind, int c)
   P.meta = E.meta.p;
   P.lamf = g->lamf.p;
   P.active = like.active;
+  P.part = cut ? E.part[solver ? 1 : 0].p : nullptr;
   P.scale = like.scale;
-  P.nchunk = like.nblk > 0 ? (solver ? E.count_act[kind][c] : E.count[kind][c]) : 0;
+  P.nchunk = like.nblk <= 0 ? 0
+             : cut ? (solver ? E.n_cut_act[c] : E.n_cut[c])
+                   : (solver ? E.count_act[kind][c] : E.count[kind][c]);
   return P;
 }
 
@@ -2580,19 +2741,44 @@ static int64_t grp_launch_weight(int kind, int c, int nchunk, bool pair) {
 static int launch_grp(Game* g, const MvParams& P0, const float* in0, float* out0, const MvParams& P1,
                       const float* in1, float* out1, hipStream_t s, double* tick) {
   if (!g->dg[0].built || !g->dg[1].built) return fail(PMX_ESTATE, "grouped matvec layout not built");
-  int cls[GrpDir::kKinds * kGrpClasses], n = 0;
-  int64_t work[GrpDir::kKinds * kGrpClasses], wgs = 0;
-  for (int kind = 0; kind < GrpDir::kKinds; ++kind)
+  // long carrying sequences are cut, except in a product the caller captures
+  const int nr0 = P0.nblk > 0 ? g->dg[P0.dir].n_red : 0, nr1 = P1.nblk > 0 ? g->dg[P1.dir].n_red : 0;
+  bool cut = nr0 + nr1 > 0;
+  if (cut && !P0.active) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    HIP_TRY(hipStreamIsCapturing(s, &st));
+    cut = st == hipStreamCaptureStatusNone;
+  }
+  // launches in list order: the cut sequences first (on side stream 0, with
+  // the sum of their terms behind them), then the other kinds
+  int cls[GrpDir::kKinds * kGrpClasses + 1], n = 0, n_pinned = 0;
+  int64_t work[GrpDir::kKinds * kGrpClasses + 1], wgs = 0;
+  const int kinds[GrpDir::kKinds] = {1, 0, 2, 3};
+  for (int kind : kinds) {
     for (int c = 0; c < kGrpClasses; ++c) {
-      const GParams A = grp_params(g, P0.dir, P0, kind, c), B = grp_params(g, P1.dir, P1, kind, c);
+      const GParams A = grp_params(g, P0.dir, P0, kind, c, cut), B = grp_params(g, P1.dir, P1, kind, c, cut);
       if (A.nchunk + B.nchunk == 0) continue;
       work[n] = grp_launch_weight(kind, c, A.nchunk + B.nchunk, A.nchunk > 0 && B.nchunk > 0);
       wgs += A.nchunk + B.nchunk;
       cls[n++] = kind * kGrpClasses + c;
     }
+    if (kind == 1 && cut && n > 0) {
+      work[n] = 10000;
+      cls[n++] = -1;
+      n_pinned = n;
+    }
+  }
   int rc = fork_launches(g, s, n, work, wgs, [&](int i, hipStream_t st, bool first) {
+    if (cls[i] < 0) {
+      const int blocks = std::max(nr0 ? g->dg[P0.dir].red_blocks : 0, nr1 ? g->dg[P1.dir].red_blocks : 0);
+      const int b = P0.active ? 1 : 0;
+      hipLaunchKernelGGL(k_grp_reduce, dim3(nr0 + nr1, blocks), dim3(256), 0, st, g->dg[P0.dir].red.p, nr0,
+                         g->dg[P0.dir].part[b].p, out0, P0.scale, g->dg[P1.dir].red.p, g->dg[P1.dir].part[b].p, out1,
+                         P1.scale, g->lamf.p, P0.active);
+      return PMX_OK;
+    }
     const int kind = cls[i] / kGrpClasses, c = cls[i] % kGrpClasses;
-    const GParams A = grp_params(g, P0.dir, P0, kind, c), B = grp_params(g, P1.dir, P1, kind, c);
+    const GParams A = grp_params(g, P0.dir, P0, kind, c, cut), B = grp_params(g, P1.dir, P1, kind, c, cut);
     double* tk = first ? tick : nullptr;
     if (kind == 0) {
       switch (c) {
@@ -2628,7 +2814,7 @@ static int launch_grp(Game* g, const MvParams& P0, const float* in0, float* out0
       }
     }
     return PMX_OK;
-  });
+  }, n_pinned);
   if (rc) return rc;
   // every instance retired from the lists: the iteration still counts
   if (n == 0 && tick) hipLaunchKernelGGL(k_add1, dim3(1), dim3(1), 0, s, tick);
@@ -2751,7 +2937,9 @@ static int rm_update(Game* g, int p, hipStream_t s) {
   // pieces of one pass are independent; only the chain is ordered)
   const bool side = g->fork_ok && D > 1 && E.blk_pull0 > E.blk_off[0] && E.blk_off[1] > E.blk_pull0 &&
                     E.blk_off[D] - E.blk_off[0] >= kForkMinWorkgroups;
+  std::unique_lock<std::mutex> lock(g->fork_mu, std::defer_lock);
   if (side) {
+    lock.lock();
     HIP_TRY(hipEventRecord(g->fork_ev, s));
     HIP_TRY(hipStreamWaitEvent(g->side[0], g->fork_ev, 0));
     launch_range(0, 0, E.blk_off[0], E.blk_pull0, g->side[0]);
