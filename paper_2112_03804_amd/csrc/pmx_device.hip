@@ -29,7 +29,8 @@
 //                 paper's GPU solver updates all hands in parallel), the
 //                 piece's rows resident in LDS during the walk; four
 //                 wavefronts walk subtree groups of the piece concurrently.
-//   k_br          FP64 best responses (bottom-up max / min) for the gap.
+//   k_brq         FP64 best responses (bottom-up max / min) for the gap, on
+//                 the same pieces.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1025,13 +1026,7 @@ struct TpParams {
   const int32_t* inf_nact;
   const int32_t* order;
   const TpTask* tasks;
-  const TpPull* pulls;
   const int2* blocks;
-  int32_t stage_stride;
-  const int32_t* active;     // per-instance flag (NULL: all); inactive tasks are skipped
-  int32_t dcfr;              // 0: regret matching+, 1: discounted CFR
-  int32_t gamma;             // averaging weight t^gamma (1 for RM+)
-  float alpha, beta;         // DCFR regret discounts
 };
 
 // Per-iteration constants of the regret update and the averaging weight.
@@ -1053,9 +1048,6 @@ __device__ inline RmStep rm_step(int dcfr, int gamma, float alpha, float beta, d
     r.dn = tb / (tb + 1.f);
   }
   return r;
-}
-__device__ inline RmStep rm_step(const TpParams& P, double t) {
-  return rm_step(P.dcfr, P.gamma, P.alpha, P.beta, t);
 }
 // New regret from the old one and the instantaneous regret: RM+ clips at 0;
 // discounted CFR scales positive and other regrets by their factors.
@@ -1093,7 +1085,9 @@ __global__ void k_add1(double* tdev) { tdev[0] += 1.0; }
 // One workgroup of a regret-update launch: its piece and first hand.
 struct RmBlock {
   RmTask t;
-  int32_t h0, pad[3];
+  int32_t h0;
+  int32_t has_root;             // the piece holds infosets at the treeplex's root
+  int32_t pad[2];
 };
 
 struct RmParams {
@@ -1653,57 +1647,170 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   }
 }
 
-// Best response: per hand, bottom-up max (Player 1) or min (Player 2) of g
-// plus the values below; sums of root values go to hv[hand_base + h].
-template <int MODE, bool MAXIMIZE>
-__global__ __launch_bounds__(TPB) void k_br(TpParams P, double* __restrict__ g,
-                                            double* __restrict__ stage, double* __restrict__ hv) {
-  const int2 bt = P.blocks[blockIdx.x];
-  const TpTask T = P.tasks[bt.x];
-  if (P.active && !P.active[T.inst]) return;   // instance not asked for
-  const int h = bt.y + threadIdx.x;
-  if (h >= T.n_hands) return;
-  const int64_t base = T.vec_base + h, stride = T.stride;
-  if (MODE == 2) {
-    for (int i = T.pull_begin; i < T.pull_end; ++i) {
-      const TpPull pl = P.pulls[i];
-      g[base + (int64_t)pl.seq * stride] += stage[(int64_t)pl.stage * P.stage_stride + h];
-    }
-  }
-  double vroot = 0.0;
-  for (int i = T.inf_end - 1; i >= T.inf_begin; --i) {
-    const int I = P.order[i];
-    const int par = P.inf_parent[I], f = P.inf_first[I], n = P.inf_nact[I];
-    double V = g[base + (int64_t)f * stride];
-    for (int a = 1; a < n; ++a) {
-      const double q = g[base + (int64_t)(f + a) * stride];
-      // a NaN propagates (fmax / fmin would drop it): a non-finite gradient
-      // must reach the host check
-      if (isnan(q) || (MAXIMIZE ? q > V : q < V)) V = q;
-    }
-    if (par == T.ext_parent) vroot += V;
-    else g[base + (int64_t)par * stride] += V;
-  }
-  if (MODE == 1) stage[(int64_t)T.stage * P.stage_stride + h] = vroot;
-  else hv[T.hand_base + h] = vroot;
+// ---------------------------------------------------------------------------
+// FP64 best responses on the regret update's pieces: per hand, bottom-up max
+// (Player 1) or min (Player 2) of the gradient plus the values below.  As in
+// k_rmq a workgroup holds 16 hands of a piece in LDS, four lanes per hand,
+// and walks the subtree groups on four wavefronts.  A deep piece leaves its
+// root values in g itself, over its own first rows (read before): row k
+// takes external parent k's, where the piece above pulls it, and the row
+// after those the sum of the piece's treeplex roots, where k_br_sum reads it.
+// Both players run in one launch per depth.
+// One lane per hand over rows in HBM, a dependent access per action, took
+// 187 us on a batch of 128 rivers and 1,080 us on the turn + river game (its
+// root piece 470 us per player: 1,392 pulls one after another).  This form
+// takes 49 and 189 us (98 + 70 + 21 by depth, the deep passes at 3.6 TB/s of
+// gradient rows); the latency of its loads, walk and pulls bounds it.
+// ---------------------------------------------------------------------------
+struct BrSide {
+  const RmBlock* blocks;
+  const int32_t* rows;
+  const int32_t* infs;
+  const int32_t* pulls;         // as RmParams, with the pulled sequence in place of the stage row
+  const int32_t* grp;
+  double* g;                    // the gradient; overwritten
+};
+
+// The larger (smaller) of two values; a NaN on either side is kept, so that a
+// non-finite gradient reaches the host check.
+__device__ inline double br_pick(double a, double b, bool maximize) {
+  return (isnan(b) || (maximize ? b > a : b < a)) ? b : a;
 }
 
-// Per-instance sum of per-hand values, fixed order (deterministic).
-__global__ __launch_bounds__(256) void k_sum_instances(const double* __restrict__ hv,
-                                                       const int64_t* __restrict__ off,
-                                                       double* __restrict__ out) {
+template <int ROWS>
+__global__ __launch_bounds__(64 * RMW) void k_brq(BrSide P0, BrSide P1, int n0,
+                                                  const int32_t* __restrict__ active) {
+  extern __shared__ double brs[];
+  const bool second = (int)blockIdx.x >= n0;
+  const BrSide P = second ? P1 : P0;
+  const int bi = (int)blockIdx.x - (second ? n0 : 0);
+  const RmBlock* __restrict__ bk = P.blocks + (bi >> 2);
+  const RmTask T = bk->t;
+  const int h0 = bk->h0 + RQH * (bi & 3);
+  if (h0 >= T.n_hands) return;                 // whole block
+  if (active && !active[T.inst]) return;       // whole block: instance not asked for
+  const bool has_root = bk->has_root != 0;
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int q = lane & 3, hl = lane >> 2;
+  const int h = h0 + hl;
+  const bool act = h < T.n_hands;
+  const int SL = T.n_rows;
+  double* Al = brs + kRmRowLocal * RQH;
+  double* __restrict__ gb = P.g + T.vec_base + (act ? h : T.n_hands - 1);   // in-bounds hand
+  const int64_t stride = T.stride;
+  auto row_id = [&](int r) { return T.row0 >= 0 ? T.row0 + r : P.rows[T.rows_off + r]; };
+  const int infv = lane < T.n_inf ? P.infs[T.inf_off + lane] : 0;
+  const bool grouped = T.grp_off >= 0;
+  const int grpv = grouped ? P.grp[T.grp_off + lane] : 0;
+  constexpr int RQK = ROWS / (4 * RMW);
+  {
+    double a[RQK];
+#pragma unroll
+    for (int k = 0; k < RQK; ++k) a[k] = gb[(int64_t)row_id(min(4 * (wv + RMW * k) + q, SL - 1)) * stride];
+#pragma unroll
+    for (int k = 0; k < RQK; ++k) {
+      const int r = 4 * (wv + RMW * k) + q;
+      if (r < SL) Al[r * RQH + hl] = a[k];
+    }
+  }
+  // the root sink, the group-root slots and the external parents start at 0
+  for (int i = threadIdx.x; i < kRmRowLocal * RQH; i += 64 * RMW) brs[i] = 0.0;
+  __syncthreads();
+  if (T.n_pull > 0) {
+    const int32_t* pl = P.pulls + T.pull_off;
+    const int hdr = lane < RMW ? pl[lane] : 0;
+    int beg = RMW;
+    for (int w = 0; w < wv; ++w) beg += rl(hdr, w);
+    const int cnt = rl(hdr, wv);
+    double acc = 0.0;
+    int row = -1;
+    for (int c0 = 0; c0 < cnt; c0 += 64) {
+      const int pv = c0 + lane < cnt ? pl[beg + c0 + lane] : 0;
+      const int nn = min(64, cnt - c0);
+      for (int j0 = 0; j0 < nn; j0 += 16) {
+        double sv[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) sv[u] = gb[(int64_t)((uint32_t)rl(pv, min(j0 + u, nn - 1)) >> 8) * stride];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          if (j0 + u < nn) {
+            const int lr = rl(pv, j0 + u) & 255;
+            if (lr != row) {
+              if (row >= 0 && q == 0) Al[row * RQH + hl] += acc;
+              acc = 0.0;
+              row = lr;
+            }
+            acc += sv[u];
+          }
+        }
+      }
+    }
+    if (row >= 0 && q == 0) Al[row * RQH + hl] += acc;
+    __syncthreads();
+  }
+  const int gbeg = grouped ? rl(grpv, kRmGBeg + wv) : 0, gend = grouped ? rl(grpv, kRmGEnd + wv) : 0;
+  const int tb = grouped ? rl(grpv, kRmGTop) : 0, te = grouped ? rl(grpv, kRmGTop + 1) : T.n_inf;
+#pragma unroll 1
+  for (int ps = grouped ? 0 : 1; ps < 2; ++ps) {
+    if (ps == 1 && grouped) {
+      __syncthreads();
+      // group-root values into their targets, in list order; the padding
+      // entries add the sink, still 0, to itself
+      if (wv == 0 && q == 0)
+        for (int e = 0; e < kRmMergeMax; ++e) {
+          const int c = (rl(grpv, kRmGMrg + e / 2) >> (16 * (e & 1))) & 0xffff;
+          const int src = c & 255, dst = c >> 8;
+          if (src != dst) brs[dst * RQH + hl] += brs[src * RQH + hl];
+        }
+    }
+    if (ps == 1 && wv != 0) break;
+    const int i0 = ps ? tb : gbeg, i1 = ps ? te : gend;
+    for (int i = i1 - 1; i >= i0; --i) {
+      const int v = rl(infv, i);
+      const int f = v & 255, n = (v >> 8) & 255, up = (v >> 16) & 255;
+      double best = Al[(f + min(q, n - 1)) * RQH + hl];
+      for (int a = q + 4; a < n; a += 4) best = br_pick(best, Al[(f + a) * RQH + hl], !second);
+      best = br_pick(best, dpp_d<0xB1, 0xf>(best), !second);   // quad_perm [1,0,3,2]
+      best = br_pick(best, dpp_d<0x4E, 0xf>(best), !second);   // quad_perm [2,3,0,1]
+      if (q == 0) brs[up * RQH + hl] += best;
+    }
+  }
+  if (wv == 0 && act && q == 0) {
+    for (int k = 0; k < T.n_ext; ++k) gb[(int64_t)row_id(k) * stride] = brs[(kRmRowExt + k) * RQH + hl];
+    if (has_root) gb[(int64_t)row_id(T.n_ext) * stride] = brs[kRmRowOne * RQH + hl];
+  }
+}
+
+// Per-instance sums of the pieces' root values over the hands, in a fixed
+// order; blockIdx.y: player.
+struct BrSeg {
+  int64_t off;                  // element offset of the row of root values in g
+  int32_t n, pad;               // hands
+};
+__global__ __launch_bounds__(256) void k_br_sum(const BrSeg* __restrict__ s0, const int32_t* __restrict__ off0,
+                                                const double* __restrict__ g0, const BrSeg* __restrict__ s1,
+                                                const int32_t* __restrict__ off1, const double* __restrict__ g1,
+                                                double* __restrict__ out, const int32_t* __restrict__ active) {
   __shared__ double red[256];
   const int i = blockIdx.x;
-  const int64_t a = off[i], b = off[i + 1];
+  if (active && !active[i]) return;
+  const bool second = blockIdx.y != 0;
+  const BrSeg* __restrict__ sg = second ? s1 : s0;
+  const int32_t* __restrict__ off = second ? off1 : off0;
+  const double* __restrict__ g = second ? g1 : g0;
   double s = 0.0;
-  for (int64_t j = a + threadIdx.x; j < b; j += 256) s += hv[j];
+  for (int k = off[i]; k < off[i + 1]; ++k) {
+    const BrSeg S = sg[k];
+    for (int j = threadIdx.x; j < S.n; j += 256) s += g[S.off + j];
+  }
   red[threadIdx.x] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
     if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) out[i] = red[0];
+  if (threadIdx.x == 0) out[blockIdx.y * gridDim.x + i] = red[0];
 }
 
 // Uniform realization plan (top-down with zero regrets), thread per hand.
@@ -1979,13 +2086,8 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
 struct DevTp {
   DBuf<int32_t> inf_parent, inf_first, inf_nact, order;
   DBuf<TpTask> tasks;
-  DBuf<TpPull> pulls;
   DBuf<int2> b_single, b_deep, b_top, b_all;
   int n_single = 0, n_deep = 0, n_top = 0, n_all = 0;
-  DBuf<float> stage;
-  DBuf<double> stage_d;
-  DBuf<double> hv;
-  int stage_stride = 0;
 };
 
 struct DevRm {                  // regret-update pieces of one player
@@ -1996,6 +2098,12 @@ struct DevRm {                  // regret-update pieces of one player
   std::vector<int> max_rows, max_ext;   // per depth
   DBuf<float> stage;
   int stage_stride = 1;
+  // FP64 best responses: blocks of every instance, pulls by sequence, and the
+  // rows of root values of each instance
+  DBuf<RmBlock> br_blocks;
+  std::vector<int> br_off;
+  DBuf<int32_t> br_pulls, br_seg_off;
+  DBuf<BrSeg> br_seg;
 };
 
 struct Game {
@@ -2011,7 +2119,6 @@ struct Game {
   DBuf<float> lamf;
   int64_t lam_base[2] = {0, 0};
   std::vector<int64_t> lam_off[2];   // per player: offset of each instance's lambdas
-  DBuf<int64_t> inst_hand_off[2];
   // solver state
   DBuf<float> R[2], x[2], grad[2];
   DBuf<double> xs[2], gd[2], sd[2], br_inst;
@@ -2380,6 +2487,58 @@ static int upload_rm_blocks(Game* g, int p, const std::vector<char>& act) {
   return E.blocks.upload(blocks);
 }
 
+// The best responses' view of the pieces: blocks of every instance by depth,
+// the pulls naming the sequence whose row of g holds the pulled value (a deep
+// piece's value of external parent k lies in its own row k), and the rows
+// that hold root values.
+static int upload_br(Game* g, int p) {
+  const RmPlan& T = g->hg.rm[p];
+  DevRm& E = g->drm[p];
+  const int D = (int)T.by_depth.size(), nt = (int)T.tasks.size();
+  std::vector<char> root(nt, 0);
+  std::vector<int32_t> slot_seq(std::max(T.n_slot, 1), 0);
+  std::vector<BrSeg> segs;
+  std::vector<int32_t> seg_off(g->hg.inst.size() + 1, 0);
+  for (int id = 0; id < nt; ++id) {   // tasks are listed instance by instance
+    const RmTask& t = T.tasks[id];
+    for (int i = 0; i < t.n_inf; ++i) root[id] |= ((uint32_t)T.infs[t.inf_off + i] >> 24) == kRmRowOne;
+    for (int k = 0; k < t.n_ext; ++k) slot_seq[T.ext_slot[t.ext_off + k]] = T.rows[t.rows_off + k];
+    if (root[id]) {
+      BrSeg s{};
+      s.off = t.vec_base + (int64_t)T.rows[t.rows_off + t.n_ext] * t.stride;
+      s.n = t.n_hands;
+      segs.push_back(s);
+    }
+    seg_off[t.inst + 1] = (int32_t)segs.size();
+  }
+  for (size_t i = 0; i < g->hg.inst.size(); ++i) seg_off[i + 1] = std::max(seg_off[i + 1], seg_off[i]);
+  std::vector<int32_t> pulls = T.pulls;
+  for (const RmTask& t : T.tasks)
+    for (int i = kRmGroups; i < t.n_pull; ++i) {
+      int32_t& v = pulls[t.pull_off + i];
+      v = (int32_t)((uint32_t)(v & 255) | ((uint32_t)slot_seq[(uint32_t)v >> 8] << 8));
+    }
+  std::vector<RmBlock> blocks;
+  E.br_off.assign(D + 1, 0);
+  for (int d = 0; d < D; ++d) {
+    E.br_off[d] = (int)blocks.size();
+    for (int id : T.by_depth[d])
+      for (int h0 = 0; h0 < T.tasks[id].n_hands; h0 += 64) {
+        RmBlock bk{};
+        bk.t = T.tasks[id];
+        bk.h0 = h0;
+        bk.has_root = root[id];
+        blocks.push_back(bk);
+      }
+  }
+  E.br_off[D] = (int)blocks.size();
+  int rc;
+  if ((rc = E.br_blocks.upload(blocks)) || (rc = E.br_pulls.upload(pulls)) || (rc = E.br_seg.upload(segs)) ||
+      (rc = E.br_seg_off.upload(seg_off)))
+    return rc;
+  return PMX_OK;
+}
+
 static int upload_rm(Game* g, int p) {
   const RmPlan& T = g->hg.rm[p];
   DevRm& E = g->drm[p];
@@ -2398,6 +2557,7 @@ static int upload_rm(Game* g, int p) {
     }
   if ((rc = upload_rm_blocks(g, p, g->listed.size() == g->hg.inst.size() ? g->listed : std::vector<char>())))
     return rc;
+  if ((rc = upload_br(g, p))) return rc;
   E.stage_stride = std::max(T.stage_stride, 1);
   return E.stage.alloc((size_t)std::max(T.n_slot, 1) * E.stage_stride);
 }
@@ -2427,7 +2587,7 @@ static int upload_game(Game* g) {
     DevTp& E = g->dt[p];
     if ((rc = E.inf_parent.upload(T.inf_parent)) || (rc = E.inf_first.upload(T.inf_first)) ||
         (rc = E.inf_nact.upload(T.inf_nact)) || (rc = E.order.upload(T.order)) ||
-        (rc = E.tasks.upload(T.tasks)) || (rc = E.pulls.upload(T.pulls)))
+        (rc = E.tasks.upload(T.tasks)))
       return rc;
     auto bs = tp_blocks(T, T.single), bd = tp_blocks(T, T.deep), bt = tp_blocks(T, T.top);
     std::vector<int32_t> all_ids = T.single;
@@ -2440,14 +2600,6 @@ static int upload_game(Game* g) {
     E.n_deep = (int)bd.size();
     E.n_top = (int)bt.size();
     E.n_all = (int)ba.size();
-    E.stage_stride = std::max(T.stage_stride, 1);
-    if ((rc = E.stage.alloc((size_t)std::max(T.n_stage, 1) * E.stage_stride)) ||
-        (rc = E.stage_d.alloc((size_t)std::max(T.n_stage, 1) * E.stage_stride)) ||
-        (rc = E.hv.alloc((size_t)std::max<int64_t>(T.hands_total, 1))))
-      return rc;
-    std::vector<int64_t> ho(1, 0);
-    for (auto& b : hg.inst) ho.push_back(ho.back() + b.inst.n[p]);
-    if ((rc = g->inst_hand_off[p].upload(ho))) return rc;
   }
   for (int p = 0; p < 2; ++p) {
     size_t n = (size_t)hg.elems[p];
@@ -2850,14 +3002,7 @@ static TpParams tp_params(Game* g, int p, const int2* blocks) {
   P.inf_nact = E.inf_nact.p;
   P.order = E.order.p;
   P.tasks = E.tasks.p;
-  P.pulls = E.pulls.p;
   P.blocks = blocks;
-  P.stage_stride = E.stage_stride;
-  P.active = nullptr;
-  P.dcfr = 0;
-  P.gamma = 1;
-  P.alpha = 1.f;
-  P.beta = 1.f;
   return P;
 }
 
@@ -2956,43 +3101,41 @@ static int rm_update(Game* g, int p, hipStream_t s) {
   return PMX_OK;
 }
 
-static TpParams tp_params_for(Game* g, int p, const int2* blocks, const int32_t* need) {
-  TpParams P = tp_params(g, p, blocks);
-  P.active = need;
-  return P;
-}
-
-// Best-response values per hand and their per-instance sums; need (device,
-// NULL: all) limits the work to the instances flagged.
-// Best-response values of player p from the FP64 gradient gvec; stage_d
-// (the deep pieces' root values) and hv (per-hand values) are scratch, and
-// the per-instance sums go to br_out[0 .. instances).
-static int br_values(Game* g, int p, double* gvec, double* stage_d, double* hv, double* br_out, hipStream_t s,
-                     const int32_t* need) {
-  DevTp& E = g->dt[p];
-  if (p == 0) {
-    if (E.n_single)
-      hipLaunchKernelGGL((k_br<0, true>), dim3(E.n_single), dim3(TPB), 0, s,
-                         tp_params_for(g, p, E.b_single.p, need), gvec, stage_d, hv);
-    if (E.n_deep)
-      hipLaunchKernelGGL((k_br<1, true>), dim3(E.n_deep), dim3(TPB), 0, s,
-                         tp_params_for(g, p, E.b_deep.p, need), gvec, stage_d, hv);
-    if (E.n_top)
-      hipLaunchKernelGGL((k_br<2, true>), dim3(E.n_top), dim3(TPB), 0, s,
-                         tp_params_for(g, p, E.b_top.p, need), gvec, stage_d, hv);
-  } else {
-    if (E.n_single)
-      hipLaunchKernelGGL((k_br<0, false>), dim3(E.n_single), dim3(TPB), 0, s,
-                         tp_params_for(g, p, E.b_single.p, need), gvec, stage_d, hv);
-    if (E.n_deep)
-      hipLaunchKernelGGL((k_br<1, false>), dim3(E.n_deep), dim3(TPB), 0, s,
-                         tp_params_for(g, p, E.b_deep.p, need), gvec, stage_d, hv);
-    if (E.n_top)
-      hipLaunchKernelGGL((k_br<2, false>), dim3(E.n_top), dim3(TPB), 0, s,
-                         tp_params_for(g, p, E.b_top.p, need), gvec, stage_d, hv);
+// Best-response values of both players from the FP64 gradients gd (which
+// they overwrite): the pieces of each depth, deepest first, both players in
+// one launch; the per-instance sums go to br_out[0 .. 2 x instances).  need
+// (device, NULL: all) limits the work to the instances flagged.
+static int br_values(Game* g, double* const gd[2], double* br_out, hipStream_t s, const int32_t* need) {
+  BrSide S[2];
+  for (int p = 0; p < 2; ++p) {
+    DevRm& E = g->drm[p];
+    S[p].rows = E.rows.p;
+    S[p].infs = E.infs.p;
+    S[p].pulls = E.br_pulls.p;
+    S[p].grp = E.grp.p;
+    S[p].g = gd[p];
+  }
+  const int D = (int)std::max(g->drm[0].max_rows.size(), g->drm[1].max_rows.size());
+  for (int d = D - 1; d >= 0; --d) {
+    int nb[2], rows = 0;
+    for (int p = 0; p < 2; ++p) {
+      DevRm& E = g->drm[p];
+      const bool on = d < (int)E.max_rows.size();
+      nb[p] = on ? E.br_off[d + 1] - E.br_off[d] : 0;
+      S[p].blocks = E.br_blocks.p + (on ? E.br_off[d] : 0);
+      if (nb[p]) rows = std::max(rows, E.max_rows[d]);
+    }
+    if (nb[0] + nb[1] == 0) continue;
+    const size_t lds = sizeof(double) * RQH * (size_t)(kRmRowLocal + rows);
+    const dim3 grid(4 * (nb[0] + nb[1]));
+    if (rows > kTaskRowsMax)
+      hipLaunchKernelGGL(k_brq<kTaskRowsWhole>, grid, dim3(64 * RMW), lds, s, S[0], S[1], 4 * nb[0], need);
+    else
+      hipLaunchKernelGGL(k_brq<kTaskRowsMax>, grid, dim3(64 * RMW), lds, s, S[0], S[1], 4 * nb[0], need);
   }
   const int ni = (int)g->hg.inst.size();
-  hipLaunchKernelGGL(k_sum_instances, dim3(ni), dim3(256), 0, s, hv, g->inst_hand_off[p].p, br_out);
+  hipLaunchKernelGGL(k_br_sum, dim3(ni, 2), dim3(256), 0, s, g->drm[0].br_seg.p, g->drm[0].br_seg_off.p, gd[0],
+                     g->drm[1].br_seg.p, g->drm[1].br_seg_off.p, gd[1], br_out, need);
   HIP_TRY(hipGetLastError());
   return PMX_OK;
 }
@@ -3616,36 +3759,34 @@ static void inst_range(const Game* g, int p, size_t i, int64_t* b, int64_t* e) {
 // instances flagged, whose row chunks must all be in the solver's launch
 // lists (the matvec then takes those lists); need_host is the same set on
 // the host, and only its instances are written.
-// Device scratch of an FP64 gap: both players' gradients, deep-piece stage
-// rows and per-hand values, and the per-instance sums (2 x instances).
+// Device scratch of an FP64 gap: both players' gradients and the
+// per-instance sums (2 x instances).
 struct GapBufs {
   double* gd[2];
-  double* stage[2];
-  double* hv[2];
   double* br;
 };
 static GapBufs game_gap_bufs(Game* g) {
   GapBufs B;
-  for (int p = 0; p < 2; ++p) {
-    B.gd[p] = g->gd[p].p;
-    B.stage[p] = g->dt[p].stage_d.p;
-    B.hv[p] = g->dt[p].hv.p;
-  }
+  for (int p = 0; p < 2; ++p) B.gd[p] = g->gd[p].p;
   B.br = g->br_inst.p;
   return B;
+}
+
+// Both products in one launch per class, then both best responses.
+static int gap_launches(Game* g, const double* xsum, const double* ysum, const int32_t* need_dev, hipStream_t s,
+                        const GapBufs& B) {
+  MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, 1.0);
+  PA.active = PT.active = need_dev;
+  const int rc = launch_mv<double>(g, PA, ysum, B.gd[0], PT, xsum, B.gd[1], s);
+  return rc ? rc : br_values(g, B.gd, B.br, s, need_dev);
 }
 
 static int gap_from_sums(Game* g, const double* xsum, const double* ysum, const double* scale,
                          const int32_t* need_dev, const int32_t* need_host, double* gap, double* br1,
                          double* br2, hipStream_t s, const GapBufs& B) {
   int rc;
-  MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, 1.0);
-  PA.active = PT.active = need_dev;
   const int ni = (int)g->hg.inst.size();
-  if ((rc = launch_mv<double>(g, PA, ysum, B.gd[0], empty_params(PA), nullptr, nullptr, s))) return rc;
-  if ((rc = launch_mv<double>(g, PT, xsum, B.gd[1], empty_params(PT), nullptr, nullptr, s))) return rc;
-  if ((rc = br_values(g, 0, B.gd[0], B.stage[0], B.hv[0], B.br, s, need_dev))) return rc;
-  if ((rc = br_values(g, 1, B.gd[1], B.stage[1], B.hv[1], B.br + ni, s, need_dev))) return rc;
+  if ((rc = gap_launches(g, xsum, ysum, need_dev, s, B))) return rc;
   std::vector<double> h(2 * (size_t)ni);
   HIP_TRY(hipMemcpyAsync(h.data(), B.br, h.size() * sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipStreamSynchronize(s));
@@ -3787,11 +3928,15 @@ int saddle_gap_of_static(Game* g, const double* x, const double* y, double* gap,
   if (!br1 || !br2) return fail(PMX_EINVAL, "br1 and br2 are required (they receive the per-instance sums)");
   double* base = nullptr;
   if ((rc = static_scratch(g->device_id, &base))) return rc;
-  // carve the FP64 gradients, stage rows, per-hand values and the
-  // per-instance sums out of the static array, each on 256-byte boundaries
+  // carve the FP64 gradients and the per-instance sums out of the static
+  // array, each on 256-byte boundaries; the limit counts stage rows and
+  // per-hand values too, as its description in pmx.h does
   const int ni = (int)g->hg.inst.size();
-  size_t need[7] = {(size_t)g->hg.elems[0], (size_t)g->hg.elems[1], g->dt[0].stage_d.n, g->dt[1].stage_d.n,
-                    g->dt[0].hv.n, g->dt[1].hv.n, 2 * (size_t)ni};
+  const TpPlan* tp = g->hg.tp;
+  auto stage_elems = [](const TpPlan& T) { return (size_t)std::max(T.n_stage, 1) * std::max(T.stage_stride, 1); };
+  size_t need[7] = {(size_t)g->hg.elems[0], (size_t)g->hg.elems[1], stage_elems(tp[0]), stage_elems(tp[1]),
+                    (size_t)std::max<int64_t>(tp[0].hands_total, 1), (size_t)std::max<int64_t>(tp[1].hands_total, 1),
+                    2 * (size_t)ni};
   double* part[7];
   size_t off = 0;
   for (int k = 0; k < 7; ++k) {
@@ -3805,17 +3950,9 @@ int saddle_gap_of_static(Game* g, const double* x, const double* y, double* gap,
   GapBufs B;
   B.gd[0] = part[0];
   B.gd[1] = part[1];
-  B.stage[0] = part[2];
-  B.stage[1] = part[3];
-  B.hv[0] = part[4];
-  B.hv[1] = part[5];
   B.br = part[6];
   hipStream_t s = (hipStream_t)stream;
-  MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, 1.0);
-  if ((rc = launch_mv<double>(g, PA, y, B.gd[0], empty_params(PA), nullptr, nullptr, s))) return rc;
-  if ((rc = launch_mv<double>(g, PT, x, B.gd[1], empty_params(PT), nullptr, nullptr, s))) return rc;
-  if ((rc = br_values(g, 0, B.gd[0], B.stage[0], B.hv[0], B.br, s, nullptr))) return rc;
-  if ((rc = br_values(g, 1, B.gd[1], B.stage[1], B.hv[1], B.br + ni, s, nullptr))) return rc;
+  if ((rc = gap_launches(g, x, y, nullptr, s, B))) return rc;
   // the sums straight into the caller's arrays (no host buffer either)
   HIP_TRY(hipMemcpyAsync(br1, B.br, (size_t)ni * sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_TRY(hipMemcpyAsync(br2, B.br + ni, (size_t)ni * sizeof(double), hipMemcpyDeviceToHost, s));

@@ -72,3 +72,44 @@ def test_cut_rows_equal_carried_rows(name, fn):
         lim_AT = 1e-6 * payoff.abs_matvec_AT(o, xi) + 1e-7 * o.abs_col_sums().max() * xi.max()
         assert (np.abs(got_A[i] - o.matvec_A(yi)) <= lim_A).all()
         assert (np.abs(got_AT[i] - o.matvec_AT(xi)) <= lim_AT).all()
+
+
+# FP64 best responses on pieces of the treeplex: one piece, pieces under
+# pieces, treeplex roots beside pieces that hang from a parent, whole
+# treeplexes beyond 64 rows, one hand, more than eight actions
+GAP_CASES = [
+    ("tiny", lambda: I.tiny_config(), (64, 8)),
+    ("river_roots", lambda: I.river_config(seed=3, n_keep=(17, 65), bet_fracs=(0.33, 0.75, 1.5), max_raises=4,
+                                           stack=900.0), (64, 8, 13)),
+    ("whole_menu", lambda: I.libratus_river(seed=2, n_keep=(33, 16), stack=900.0), (None, 64, 9)),
+    ("many_actions", lambda: I.river_config(seed=5, n_keep=(40, 1), stack=20000.0, max_raises=1,
+                                            bet_fracs=tuple(0.1 * k for k in range(1, 13))), (None, 64, 16)),
+    ("turn_2card", lambda: I.small_turn_river(3, deck_size=13, n_board=3, cards_per_hand=2, bet_fracs=(0.5, 1.0),
+                                              max_raises=1, stack=30.0, zero_frac=0.2), (64, 8)),
+]
+
+
+@pytest.mark.parametrize("name,fn,cuts", GAP_CASES, ids=[c[0] for c in GAP_CASES])
+def test_best_responses_on_pieces(name, fn, cuts):
+    d = fn()
+    g = _game([d, I.small_river(0)])
+    rng = np.random.default_rng(9)
+    plans = [[], []]
+    for i in range(2):
+        for p in range(2):
+            L = g.layouts[i][p]
+            v = rng.random((L["n_seq"], L["n_hands"])) + 0.01
+            for parent, first, n in zip(L["infoset_parent"], L["infoset_first"], L["infoset_nact"]):
+                v[first:first + n] /= v[first:first + n].sum(axis=0)
+                if parent >= 0:
+                    v[first:first + n] *= v[parent]
+            plans[p].append(v)
+    x, y = (torch.from_numpy(g.pack(p, plans[p], dtype=np.float64)).cuda() for p in range(2))
+    refs = [solver.saddle_gap(payoff.Game(di), plans[0][i], plans[1][i]) for i, di in enumerate((d, I.small_river(0)))]
+    for cut in cuts:
+        if cut is not None:
+            g.solver_set_task_rows(cut)
+        got = g.saddle_gap_of(x, y)
+        for i, di in enumerate((d, I.small_river(0))):
+            for k in range(3):
+                assert abs(got[k][i] - refs[i][k]) <= 1e-9 * 2 * di.contrib, (cut, i, k, got[k][i], refs[i][k])
