@@ -467,6 +467,14 @@ int mlp_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, int32_t ld
                   const uint16_t* B, int32_t ldb, int32_t transB, const float* bias, int32_t relu,
                   const float* mask, int32_t ldm, float* C, int32_t ldc, uint16_t* Cb, int32_t ldcb,
                   float* work, int64_t work_elems, void* stream);
+/* Logits Z [M][8] (FP32) of the whole network (64 -> 512 -> 512 -> 8, ReLU) for
+ * BF16 rows X [M][64]: BF16 weights W1 [512][64], W2 [512][512], W3 [8][512],
+ * FP32 biases, hidden activations rounded to BF16 as by mlp_gemm_bf16, FP32
+ * accumulation.  work: device scratch of 512 * 512 BF16 values.  Inputs and
+ * scratch 16-byte aligned. */
+int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* W2,
+                     const float* b2, const uint16_t* W3, const float* b3, float* Z, uint16_t* work,
+                     void* stream);
 /* Masked softmax cross-entropy over K <= 64 slots (target < 0 = invalid):
  * dlogits[r][a] = weight[r] (softmax - target) (FP32 and / or BF16, stride K);
  * loss_partial[b] = sum of weight[r] * cross-entropy over block b's 256 rows. */

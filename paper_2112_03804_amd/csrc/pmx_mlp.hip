@@ -215,6 +215,165 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs P, int splits) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Inference of the whole network (64 -> 512 -> 512 -> 8, ReLU) in one kernel:
+// the activations of a tile of rows never leave the CU.  Everything runs
+// transposed, features x rows, so that a lane of an MFMA result holds four
+// consecutive features of one row: the hidden layer goes to LDS as [row][k]
+// by 8-byte writes and comes back as 16-byte B fragments (rows padded by 16
+// bytes: the 16 rows of a fragment fall on different banks), and the second
+// hidden layer feeds the output layer's 16x16x16 MFMA straight from
+// registers.
+//
+// Eight wavefronts, each 64 features of a hidden layer for every row of the
+// tile; the second layer's weights stream from L2, the next k step in
+// flight during the current one's MFMAs.  A tile of 128 rows (133 KB of LDS)
+// asks 31 bytes per cycle and CU of L2 at the MFMA rate, a quarter of what 32
+// rows would.  PACKED: those weights in fragment order, 1 KB contiguous per
+// load; as stored, a k step would use half of each 128-byte line and find
+// the other half evicted.  Workgroups take tiles in turn, the next tile's
+// inputs in flight during the second layer.
+//
+// 1.5 M rows: 6.12 ms layer by layer with the activations through HBM in FP32
+// and BF16 (148 TFLOP/s), 0.78 ms here (1,157 TFLOP/s; an 8192^3 library
+// product reaches 1,190).  Up to 8,192 rows: 20 us, the latency of one tile.
+// ---------------------------------------------------------------------------
+constexpr int NetIn = 64, NetW = 512, NetOut = 8;
+constexpr int NetPitch = NetW + 8;
+constexpr int NetWaves = 8;                      // 64 features of a hidden layer each
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+struct NetArgs {
+  int64_t M;
+  const uint16_t *X, *W1, *W2, *W3;
+  const float *b1, *b2, *b3;
+  float* Z;
+};
+
+// W2 in fragment order: [feature tile of 16][k step of 32][lane][8]
+__global__ __launch_bounds__(256) void k_net_pack(const uint16_t* __restrict__ W, uint16_t* __restrict__ Wp) {
+  const int i = blockIdx.x * 256 + threadIdx.x;   // one 16-byte piece
+  const int lane = i & 63, ks = (i >> 6) % (NetW / 32), ft = (i >> 6) / (NetW / 32);
+  ((uint4*)Wp)[i] = *(const uint4*)(W + (int64_t)(16 * ft + (lane & 15)) * NetW + 32 * ks + 8 * (lane >> 4));
+}
+
+__device__ inline s16x4 net_hidden(f32x4 v, const float* __restrict__ bias) {
+  const float4 b = *(const float4*)bias;
+  const float t[4] = {v[0] + b.x, v[1] + b.y, v[2] + b.z, v[3] + b.w};
+  s16x4 o;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) o[i] = (short)f2bf(t[i] > 0.f ? t[i] : 0.f);
+  return o;
+}
+
+template <int RT, bool PACKED>
+__global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(RT == 8 ? 2 : 4)))
+void k_net(NetArgs P, const uint16_t* __restrict__ W2p) {
+  extern __shared__ __attribute__((aligned(16))) char net_smem[];
+  constexpr int ROWS = 16 * RT;
+  constexpr int XP = NetIn + 8;
+  uint16_t* H = (uint16_t*)net_smem;             // [ROWS][NetPitch], then the waves' partial outputs
+  uint16_t* Xs = H + ROWS * NetPitch;            // [ROWS][XP] inputs of the tile
+  float* part = (float*)net_smem;                // [NetWaves][ROWS][NetOut]
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4, f0 = 64 * w;
+  // a tile's inputs as 16-byte pieces, at most two per thread (one for half
+  // of the threads in a 32-row tile)
+  constexpr int PIECES = ROWS * NetIn / 8, NT = 64 * NetWaves;
+  static_assert(PIECES <= 2 * NT && (PIECES <= NT || PIECES == 2 * NT), "one or two input pieces per thread");
+  const int xc0 = min(tid, PIECES - 1), xr0 = xc0 / (NetIn / 8), xk = 8 * (xc0 % (NetIn / 8));
+  constexpr int xrd = NT / (NetIn / 8);          // rows between a thread's two pieces
+  const int64_t tiles = (P.M + ROWS - 1) / ROWS;
+  int64_t tile = blockIdx.x;
+  uint4 xa = *(const uint4*)(P.X + min(tile * ROWS + xr0, P.M - 1) * NetIn + xk), xb = xa;
+  if (PIECES > NT) xb = *(const uint4*)(P.X + min(tile * ROWS + xr0 + xrd, P.M - 1) * NetIn + xk);
+  // this lane's second-layer fragments: feature tile i, k step ks at w2 + i * w2t + ks * w2k
+  const uint16_t* w2 = PACKED ? W2p + (int64_t)(4 * w) * (NetW / 32) * 512 + 8 * lane
+                              : P.W2 + (int64_t)(f0 + l16) * NetW + 8 * lq;
+  constexpr int w2t = 16 * NetW, w2k = PACKED ? 512 : 32;
+  for (; tile < tiles; tile += gridDim.x) {
+    if (PIECES >= NT || tid < PIECES) *(uint4*)&Xs[xr0 * XP + xk] = xa;
+    if (PIECES > NT) *(uint4*)&Xs[(xr0 + xrd) * XP + xk] = xb;
+    f32x4 acc[4][RT];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < RT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    __syncthreads();   // the inputs are in place; the last tile's partial outputs are read
+    // layer 1
+#pragma unroll
+    for (int ks = 0; ks < NetIn / 32; ++ks) {
+      bf16x8 a[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        a[i] = *(const bf16x8*)(P.W1 + (int64_t)(f0 + 16 * i + l16) * NetIn + 32 * ks + 8 * lq);
+#pragma unroll
+      for (int j = 0; j < RT; ++j) {
+        const bf16x8 b = *(const bf16x8*)&Xs[(16 * j + l16) * XP + 32 * ks + 8 * lq];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0);
+      }
+    }
+    bf16x8 an[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) an[i] = *(const bf16x8*)(w2 + i * w2t);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < RT; ++j) {
+        *(s16x4*)&H[(16 * j + l16) * NetPitch + f0 + 16 * i + 4 * lq] = net_hidden(acc[i][j], P.b1 + f0 + 16 * i + 4 * lq);
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    __syncthreads();
+    // layer 2, the next tile's inputs on their way
+    if (tile + gridDim.x < tiles) {
+      const int64_t r = (tile + gridDim.x) * ROWS + xr0;
+      xa = *(const uint4*)(P.X + min(r, P.M - 1) * NetIn + xk);
+      if (PIECES > NT) xb = *(const uint4*)(P.X + min(r + xrd, P.M - 1) * NetIn + xk);
+    }
+#pragma unroll 2
+    for (int ks = 0; ks < NetW / 32; ++ks) {
+      const int kn = min(ks + 1, NetW / 32 - 1);
+      bf16x8 a[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = an[i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) an[i] = *(const bf16x8*)(w2 + i * w2t + kn * w2k);
+#pragma unroll
+      for (int j = 0; j < RT; ++j) {
+        const bf16x8 b = *(const bf16x8*)&H[(16 * j + l16) * NetPitch + 32 * ks + 8 * lq];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[i][j], 0, 0, 0);
+      }
+    }
+    // layer 3: this wavefront's 64 features, outputs 8 to 15 of the MFMA unused
+    f32x4 z[RT];
+#pragma unroll
+    for (int j = 0; j < RT; ++j) z[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s16x4 a3 = {0, 0, 0, 0};
+      if (l16 < NetOut) a3 = *(const s16x4*)(P.W3 + (int64_t)l16 * NetW + f0 + 16 * i + 4 * lq);
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+        z[j] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a3, net_hidden(acc[i][j], P.b2 + f0 + 16 * i + 4 * lq), z[j], 0, 0, 0);
+    }
+    __syncthreads();   // the hidden layer is read
+    if (lq < NetOut / 4)
+#pragma unroll
+      for (int j = 0; j < RT; ++j)
+        *(f32x4*)&part[((w * ROWS) + 16 * j + l16) * NetOut + 4 * lq] = z[j];
+    __syncthreads();
+    for (int i = tid; i < ROWS * NetOut; i += 64 * NetWaves) {
+      float v = 0.f;
+#pragma unroll
+      for (int k = 0; k < NetWaves; ++k) v += part[k * ROWS * NetOut + i];
+      const int64_t r = tile * ROWS + i / NetOut;
+      if (r < P.M) P.Z[r * NetOut + i % NetOut] = v + P.b3[i % NetOut];
+    }
+  }
+}
+
 // Masked softmax cross-entropy per row: targets < 0 mark invalid actions.
 // loss_r = w_r * sum_a -t_a log p_a ; dlogits = w_r * (p - t) on valid actions.
 __global__ __launch_bounds__(256) void k_softmax_xent(int rows, int K, const float* __restrict__ z, int ldz,
@@ -379,6 +538,35 @@ int mlp_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, int32_t ld
     const int64_t mn = (int64_t)M * N;
     hipLaunchKernelGGL(k_gemm_reduce, dim3((unsigned)std::min<int64_t>((mn + 255) / 256, 4096)), dim3(256), 0, s,
                        P, splits);
+  }
+  MLP_TRY(hipGetLastError());
+  return PMX_OK;
+}
+
+// Rows from which the 128-row tiles are used: 32-row tiles read the second
+// layer's weights four times as often but give a small call four times the
+// workgroups and need no packed weights (8,191 rows: 20.0 us, 8,192: 22.5 us;
+// beyond 256 workgroups they would run in rounds).
+static constexpr int64_t kNetLargeRows = 8192;
+
+int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* W2,
+                     const float* b2, const uint16_t* W3, const float* b3, float* Z, uint16_t* work, void* stream) {
+  if (M < 0 || !X || !W1 || !b1 || !W2 || !b2 || !W3 || !b3 || !Z || !work)
+    return mfail(PMX_EINVAL, "bad network arguments");
+  const uintptr_t all = (uintptr_t)X | (uintptr_t)W1 | (uintptr_t)b1 | (uintptr_t)W2 | (uintptr_t)b2 | (uintptr_t)W3 |
+                        (uintptr_t)work;
+  if (all % 16) return mfail(PMX_EINVAL, "network buffers must be 16-byte aligned");
+  if (M == 0) return PMX_OK;
+  hipStream_t s = (hipStream_t)stream;
+  const NetArgs P{M, X, W1, W2, W3, b1, b2, b3, Z};
+  auto lds = [](int rows) { return sizeof(uint16_t) * (size_t)rows * (NetPitch + NetIn + 8); };
+  if (M >= kNetLargeRows) {
+    hipLaunchKernelGGL(k_net_pack, dim3(NetW * NetW / 8 / 256), dim3(256), 0, s, W2, work);
+    const int64_t tiles = (M + 127) / 128;
+    hipLaunchKernelGGL((k_net<8, true>), dim3((unsigned)std::min<int64_t>(tiles, 256)), dim3(64 * NetWaves), lds(128),
+                       s, P, work);
+  } else {
+    hipLaunchKernelGGL((k_net<2, false>), dim3((unsigned)((M + 31) / 32)), dim3(64 * NetWaves), lds(32), s, P, work);
   }
   MLP_TRY(hipGetLastError());
   return PMX_OK;

@@ -56,6 +56,7 @@ class WarmMLP:
                                                   pmx.dptr(self.pb[name]), pmx.stream_ptr()))
         self.step = 0
         self._ws = {}
+        self._ws_net = {}   # scratch of logits()
 
     # -- buffers ------------------------------------------------------------
     def _work(self, M: int):
@@ -138,9 +139,18 @@ class WarmMLP:
                                  lr, b1, b2, eps, wd, self.step, pmx.stream_ptr()))
 
     def logits(self, Xb, M: int, chunk: int = 1 << 20):
-        """Logits for M rows in chunks (inference)."""
+        """Logits for M rows (inference): one kernel for the whole network,
+        or, for rows not aligned to 16 bytes, layer by layer in chunks."""
         torch = _torch()
         out = torch.empty((M, K), dtype=torch.float32, device="cuda")
+        if Xb.data_ptr() % 16 == 0:
+            if "pack" not in self._ws_net:
+                self._ws_net["pack"] = torch.empty((WIDTH * WIDTH,), dtype=torch.bfloat16, device="cuda")
+            p, pb, d = self.p, self.pb, pmx.dptr
+            pmx.check(pmx.lib().mlp_forward_bf16(M, d(Xb), d(pb["W1"]), d(p["b1"]), d(pb["W2"]), d(p["b2"]),
+                                                 d(pb["W3"]), d(p["b3"]), d(out), d(self._ws_net["pack"]),
+                                                 pmx.stream_ptr()))
+            return out
         for a in range(0, M, chunk):
             b = min(M, a + chunk)
             z = self.forward(Xb[a:b], b - a)

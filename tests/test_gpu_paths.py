@@ -113,3 +113,31 @@ def test_best_responses_on_pieces(name, fn, cuts):
         for i, di in enumerate((d, I.small_river(0))):
             for k in range(3):
                 assert abs(got[k][i] - refs[i][k]) <= 1e-9 * 2 * di.contrib, (cut, i, k, got[k][i], refs[i][k])
+
+
+# the network's inference kernel: single rows, remainders of 32- and 128-row
+# tiles, both sides of the row count where the tile changes, more tiles than
+# workgroups
+@pytest.mark.parametrize("rows", [1, 31, 32, 33, 1000, 8191, 8192, 8193, 32769, 66001])
+def test_network_inference(rows):
+    _game(I.tiny_config()).close()
+    from paper_2112_03804_amd import warmstart
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    net = warmstart.WarmMLP(seed=rows)
+    for k in ("b1", "b2", "b3"):
+        net.p[k].copy_(0.2 * torch.randn(net.p[k].shape, generator=gen, device="cuda"))
+    X = torch.randn((rows + 3, warmstart.D_IN), generator=gen, device="cuda").to(torch.bfloat16)
+    got = net.logits(X[1:], rows)
+    # the layer-by-layer path rounds the same activations to BF16, so the two
+    # differ by FP32 summation order (512 terms: 512 * 2^-24 of the summed
+    # magnitudes) and by the rare activation that it rounds the other way
+    # (2^-8 of one term)
+    ref = net.forward(X[1:], rows).clone()
+    w3 = net.pb["W3"].float().abs()
+    h2 = net._ws["H2b"][:rows].float().abs()
+    mag = h2 @ w3.t().contiguous() + net.p["b3"].abs()
+    top = (h2.max(dim=1, keepdim=True).values * w3.max(dim=1).values[None, :])
+    assert got.shape == (rows, warmstart.K)
+    assert ((got - ref).abs() <= 512 * 2.0 ** -24 * mag + 2 * 2.0 ** -8 * top).all()
+    # and nearly all of them by the summation order alone
+    assert ((got - ref).abs() <= 512 * 2.0 ** -24 * mag).float().mean() > 0.98
