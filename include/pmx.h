@@ -224,8 +224,8 @@ int game_hand_meta(const Game* g, int32_t instance, int32_t ctx, int32_t player,
  * groups, a group scanning up to four input rows of one board context at
  * once (Technique B's solve and the inclusion-exclusion of eq. cf applied to
  * all of them).  rows_per_chunk in [1, 64]: output rows per chunk (2, 3) or
- * groups per chunk (4).  The FP64 products always run the chunk-aligned
- * layout.  Synchronizes the device; drops the captured solver graph.  The
+ * groups per chunk (4).  The FP64 products always run on the
+ * grouped layout's scans, a row at a time.  Synchronizes the device; drops the captured solver graph.  The
  * defaults depend on the game's size; an autotuner may override them.
  * PMX_EINVAL for a kernel outside [2, 4]. */
 int game_tune(Game* g, int32_t kernel, int32_t rows_per_chunk);

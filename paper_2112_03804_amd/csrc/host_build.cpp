@@ -550,11 +550,11 @@ int default_rows_per_block(int64_t rows, int kernel) {
   return kernel == 3 ? 8 : 2;
 }
 
-// The FP64 products (the gap) run the chunk-aligned layout: 512-thread
-// workgroups (fewer entries per thread, shorter serial passes) when instances
-// hold many hands on average, 256-thread workgroups for batches of smaller
-// instances.  The FP32 products default to the grouped kernel (4), one group
-// per workgroup.
+// Chunk-aligned layout: 512-thread workgroups (fewer entries per thread,
+// shorter serial passes) when instances hold many hands on average, 256-thread
+// workgroups for batches of smaller instances.  The FP32 products default to
+// the grouped kernel (4), one group per workgroup; the FP64 products take the
+// row chunks chosen here.
 int default_mv_kernel(int64_t mean_hands) { return mean_hands > 800 ? 3 : 2; }
 
 namespace {
@@ -826,7 +826,7 @@ int build_mc_layout(HostGame& hg, int d, int block, std::string& msg) {
         msg = "instance " + std::to_string(ii) + ": scan entries exceed the workgroup";
         return PMX_EINVAL;
       }
-      // byte offset of a slot for 4-byte values (the FP64 kernels double it)
+      // byte offset of a slot for 4-byte values
       auto slot = [&](int sg, int i) { return 4 * ((cstart[sg] + i / ke) * sk + i % ke); };
       McCtx m{};
       m.n_own = in.n[p];
@@ -1033,6 +1033,7 @@ int build_grp_layout(HostGame& hg, int d, int gpc, std::string& msg) {
       msg = "instance " + std::to_string(ii) + " has too many hands for matvec kernel 4";
       return PMX_EINVAL;
     }
+    M.inst_cls.push_back(cls);
     const int KE = kGrpKE[cls];
     const int ctx_base = (int)M.ctx.size();
     for (int c = 0; c < b.n_ctx; ++c) {

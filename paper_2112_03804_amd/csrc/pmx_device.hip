@@ -1,7 +1,7 @@
 // libpmx device code for gfx950 (CDNA4) and the C ABI.
 //
 // Kernels
-//   k_mvc         rows of A y (or A^T x), schedules 2 and 3 and every FP64 product: one
+//   k_mvc         rows of A y (or A^T x), FP32 schedules 2 and 3: one
 //                 workgroup of 256 or 512 threads per chunk of output rows,
 //                 one launch per hands-per-thread class, on the
 //                 chunk-aligned layout (every segment starts at a thread's
@@ -19,6 +19,8 @@
 //                 FP32 sums inside a thread's chunk, FP64 carries across
 //                 chunks (FP64 adds issue at the unpacked FP32 rate on
 //                 CDNA4, so this costs less than compensated FP32).
+//   k_mvd         rows of A y (or A^T x) in FP64 (the gap), on the grouped
+//                 layout's contexts.
 //   k_mvg         rows of A y (or A^T x), the default FP32 schedule (4):
 //                 groups of up to four input rows of one board context
 //                 share one staged gather, one segmented scan and one set of
@@ -174,24 +176,16 @@ struct McParams {
   const uint4* q;
   const uint2* pos;
   const uint32_t* meta;
-  const double* lam;
   const float* lamf;
   const int32_t* active;         // per-instance flag (NULL: all)
   void* part;                    // partial rows of rows cut into parts (IO elements)
   double scale;
   int32_t nchunk;
 };
-template <typename IO>
-__device__ inline const IO* mc_lam(const McParams& P);
-template <>
-__device__ inline const float* mc_lam<float>(const McParams& P) { return P.lamf; }
-template <>
-__device__ inline const double* mc_lam<double>(const McParams& P) { return P.lam; }
-
 // LDS value at a slot given as the byte offset of a 4-byte value.
 template <typename IO>
 __device__ inline IO& at_slot(IO* base, int off4) {
-  return *(IO*)((char*)base + (sizeof(IO) == 4 ? off4 : 2 * off4));
+  return *(IO*)((char*)base + off4);
 }
 
 template <typename IO>
@@ -205,16 +199,6 @@ struct Vec4<float> {
   }
   __device__ static void st(float* p, const float* v) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
 };
-template <>
-struct Vec4<double> {
-  static constexpr int N = 2;
-  __device__ static void ld(const double* p, double* v) {
-    const double2 t = *(const double2*)p;
-    v[0] = t.x; v[1] = t.y;
-  }
-  __device__ static void st(double* p, const double* v) { *(double2*)p = make_double2(v[0], v[1]); }
-};
-
 // One workgroup per row chunk.  Per item: the weighted opponent inputs are
 // written to their three slots (global, card 0, card 1), each thread sums its
 // chunk of KE slots in FP64, a segmented block scan carries the sums across
@@ -224,11 +208,10 @@ struct Vec4<double> {
 // the per-card fold totals (eq. cf).
 // Wavefronts per SIMD each FP32 class is built for: the register budget of
 // the workgroups per CU its LDS allows (4 of 256 threads for the small
-// classes, 3 and 2 for the larger ones, 2 of 512).  The FP64 forms, used for
-// the gap only, are left unconstrained.
+// classes, 3 and 2 for the larger ones, 2 of 512).
 template <int BLOCK, int KH, typename IO>
 constexpr int mc_waves_per_simd() {
-  return sizeof(IO) != 4 ? 1 : (BLOCK == 512 ? 4 : (KH <= 2 ? 4 : (KH <= 4 ? 3 : 2)));
+  return BLOCK == 512 ? 4 : (KH <= 2 ? 4 : (KH <= 4 ? 3 : 2));
 }
 
 template <int BLOCK, int KH, typename IO>
@@ -247,7 +230,7 @@ void k_mvc(McParams P0, const IO* __restrict__ in0, IO* __restrict__ out0,
   const McParams& P = second ? P1 : P0;
   const IO* __restrict__ in = second ? in1 : in0;
   IO* __restrict__ out = second ? out1 : out0;
-  const IO* __restrict__ lam = mc_lam<IO>(P);
+  const IO* __restrict__ lam = P.lamf;
   const int4 cr = P.chunks[second ? (int)blockIdx.x - P0.nchunk : (int)blockIdx.x];
   if (P.active && !P.active[cr.z]) return;   // retired instance
   const int tid = threadIdx.x;
@@ -420,7 +403,7 @@ void k_mvc(McParams P0, const IO* __restrict__ in0, IO* __restrict__ out0,
       // after a segment's last entry receives the segment's total; the
       // zeroed slots after it add nothing, and no query reads past it.
       const IO eh = (IO)es;
-      IO run = sizeof(IO) == 4 ? (IO)(es - (double)eh) : (IO)0;
+      IO run = (IO)(es - (double)eh);
 #pragma unroll
       for (int j = 0; j < KE; j += VN) {
         IO v[VN], pc[VN];
@@ -983,6 +966,214 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
         __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();   // the next group's staging overwrites the prefix slots
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// FP64 products on the grouped layout's contexts
+// ---------------------------------------------------------------------------
+struct DParams {
+  const MvItem* items;
+  const int4* chunks;            // (first item, end item, instance, first context) per workgroup
+  const GCtx* ctx;
+  const uint4* q;
+  const uint16_t* rk;
+  const uint32_t* src;
+  const uint32_t* meta;
+  const double* lam;
+  const int32_t* active;         // per-instance flag (NULL: all)
+  double* part;                  // partial rows of rows cut into parts
+  double scale;
+  int32_t nchunk;
+};
+
+template <int KH>
+constexpr size_t mvd_lds() {
+  return sizeof(double) * (2 * kMcSegMax + 3 * 8 + (size_t)kGrpBlock * kGrpKE[KH - 1]) + grp_stage_bytes<KH>();
+}
+
+// One workgroup of 512 threads per row chunk.  Per item (an output row's
+// showdown input and fold input of one board context) every opponent hand
+// stages the pair of weighted values as one 16-byte row at its strength
+// position; two threads per chunk of the grouped layout's entry list gather
+// its halves from those rows and sum both values, a segmented block scan
+// carries the sums, the showdown value's exclusive prefix sums go to 8-byte
+// slots, and every own hand combines six prefix sums, the segment totals and
+// the identical hand's staging row.  All in FP64.
+// Only the showdown value has slots (a fold term needs its segment totals and
+// the identical hand), so the 1,025-to-1,280-hand class takes 60 KB of LDS:
+// two workgroups, 16 wavefronts, per CU.  LDS accesses bound it, about 6,000
+// cycles per row and CU at 1,128 hands with the bank conflicts of the random
+// rows and slots.  Both directions of the turn + river game: 726 us on the
+// chunk-aligned layout (values scattered to three zeroed slots each in two
+// channels, 98 KB, one workgroup per CU), 386 us here.
+template <int KH>
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4)))
+void k_mvd(DParams P0, const double* __restrict__ in0, double* __restrict__ out0, DParams P1,
+           const double* __restrict__ in1, double* __restrict__ out1) {
+  constexpr int BT = 512, CB = kGrpBlock, KE = kGrpKE[KH - 1], KQ = (KH + 1) / 2;
+  constexpr int NP = (KE / 2 + 1) / 2;           // entry pairs of a chunk's first half (the second has no more)
+  const bool second = (int)blockIdx.x >= P0.nchunk;
+  const DParams& P = second ? P1 : P0;
+  const double* __restrict__ in = second ? in1 : in0;
+  double* __restrict__ out = second ? out1 : out0;
+  const auto crp = cst((const int32_t*)(P.chunks + (second ? (int)blockIdx.x - P0.nchunk : (int)blockIdx.x)));
+  const int it0 = crp[0], it1 = crp[1];
+  if (P.active && !*cst(P.active + crp[2])) return;   // instance not asked for
+  const int tid = threadIdx.x, half = tid & 1, chunk = tid >> 1;
+  extern __shared__ double smem[];
+  double2* segT = (double2*)smem;                // [kMcSegMax] (showdown, fold) totals per segment
+  double* scr = smem + 2 * kMcSegMax;            // [3 * 8] scan scratch
+  double* R = scr + 3 * 8;                       // [KE * CB] showdown prefix slots
+  char* St = (char*)(R + CB * KE);               // staging rows, 16 bytes each
+
+  if (crp[3] < 0) {
+    // a chunk of rows without terms: zeros
+    for (int it = it0; it < it1; ++it) {
+      const auto ip = cst(P.items + it);
+#pragma unroll
+      for (int k = 0; k < KQ; ++k)
+        if (tid + k * BT < ip->stride) (out + ip->out)[tid + k * BT] = 0.0;
+    }
+    return;
+  }
+
+  double acc[KQ], vs[KQ], vf[KQ];                // the row's sum; the inputs of the item in flight
+#pragma unroll
+  for (int k = 0; k < KQ; ++k) acc[k] = 0.0;
+  {
+    const auto ip = cst(P.items + it0);
+    const double* ps = in + max(ip->in_s, (int64_t)0);   // an absent row's loads are masked below
+    const double* pf = in + max(ip->in_f, (int64_t)0);
+#pragma unroll
+    for (int k = 0; k < KQ; ++k) {
+      const uint32_t h = (uint32_t)min(tid + k * BT, ip->n_opp - 1);
+      vs[k] = ps[h];
+      vf[k] = pf[h];
+    }
+  }
+  int it = it0;
+  while (it < it1) {
+    // a run of items on one board context: its records stay in registers
+    const int ctx = cst(P.items + it)->ctx;
+    const auto cp = cst(P.ctx + ctx);
+    const int n_own = cp->n_own, n_opp = cp->n_opp, cph = cp->cph;
+    const uint32_t zrow = (uint32_t)cp->zrow;
+    const bool wlive = ((tid & ~63) >> 1) < cp->n_chunk;
+    uint4 qr[KQ];
+    uint32_t rko[KQ], srcp[NP];
+    double lo[KQ], lp[KQ];
+    {
+      const uint16_t* rk = P.rk + cp->rk_off;
+      const double* lopp = P.lam + cp->lam_opp_off;
+      const double* lown = P.lam + cp->lam_own_off;
+      const uint4* qp = P.q + cp->q_off;
+      const uint32_t* sp = P.src + cp->src_off;
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) {
+        const uint32_t ho = (uint32_t)min(tid + k * BT, n_opp - 1), hw = (uint32_t)min(tid + k * BT, n_own - 1);
+        rko[k] = rk[ho];
+        lp[k] = lopp[ho];
+        qr[k] = qp[hw];
+        lo[k] = lown[hw];
+      }
+#pragma unroll
+      for (int j = 0; j < NP; ++j) srcp[j] = sp[(uint32_t)(min(half * NP + j, KE / 2 - 1) * CB + chunk)];
+      if (KE / 2 < 2 * NP && half) srcp[NP - 1] = zrow | (zrow << 16);   // an odd number of pairs
+    }
+    const uint32_t cm = (P.meta + cp->meta_off)[(uint32_t)chunk];
+    __syncthreads();   // the previous run's readers of St are done
+    if (tid == 0) *(double2*)(St + zrow) = make_double2(0.0, 0.0);
+    for (; it < it1; ++it) {
+      const auto ip = cst(P.items + it);
+      if (ip->ctx != ctx) break;
+      const bool hs = ip->in_s >= 0, hf = ip->in_f >= 0;
+      const double ks = ip->ks, kf = ip->kf;
+      // the records are decoded again for every item: hoisted addresses would
+      // cost more registers than the integer operations they save
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) asm volatile("" : "+v"(qr[k].x), "+v"(qr[k].y), "+v"(qr[k].z), "+v"(qr[k].w));
+#pragma unroll
+      for (int j = 0; j < NP; ++j) asm volatile("" : "+v"(srcp[j]));
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) {
+        if (tid + k * BT < n_opp)
+          *(double2*)(St + rko[k]) = make_double2(hs ? ks * lp[k] * vs[k] : 0.0, hf ? kf * lp[k] * vf[k] : 0.0);
+      }
+      {
+        // the next item's inputs (the last item's again, at the end)
+        const auto np = cst(P.items + min(it + 1, it1 - 1));
+        const double* ps = in + max(np->in_s, (int64_t)0);
+        const double* pf = in + max(np->in_f, (int64_t)0);
+#pragma unroll
+        for (int k = 0; k < KQ; ++k) {
+          const uint32_t h = (uint32_t)min(tid + k * BT, np->n_opp - 1);
+          vs[k] = ps[h];
+          vf[k] = pf[h];
+        }
+      }
+      __syncthreads();
+      double ev[2 * NP], ts = 0.0, tf = 0.0;
+      if (wlive) {
+#pragma unroll
+        for (int i = 0; i < 2 * NP; ++i) {
+          const double2 v = *(const double2*)(St + ((i & 1) ? srcp[i / 2] >> 16 : srcp[i / 2] & 0xffffu));
+          ev[i] = v.x;
+          ts += v.x;
+          tf += v.y;
+        }
+      }
+      double es, ef;
+      block_seg_scan_x<8>((int)((cm >> 8) & 1u) & (half ^ 1), ts, tf, scr, es, ef);
+      if (hs && wlive) {
+        double run = es;
+#pragma unroll
+        for (int i = 0; i < 2 * NP; ++i) {
+          const int e = half * 2 * NP + i;
+          if (2 * NP * 2 <= KE || e < KE) R[e * CB + chunk] = run;
+          run += ev[i];
+        }
+      }
+      const int endseg = (int)((cm >> 16) & 255u);
+      if (half && endseg) segT[endseg - 1] = make_double2(es + ts, ef + tf);
+      __syncthreads();
+      const double2 T0 = segT[0];
+      const int last = ip->last, stride = ip->stride;
+      double* __restrict__ dst = (last == 2 ? P.part : out) + ip->out;
+#pragma unroll
+      for (int k = 0; k < KQ; ++k) {
+        const uint4 r = qr[k];
+        const int h = tid + k * BT;
+        if (h < n_own && r.x != 0xffffffffu) {
+          const double2 Ta = segT[1 + (r.w & 63)];
+          double2 Tb = make_double2(0.0, 0.0);
+          if (cph == 2) Tb = segT[1 + ((r.w >> 6) & 63)];
+          double v = 0.0;
+          if (hs) {
+            double sd = (R[r.x & 0xffffu] + R[r.x >> 16] - T0.x) - (R[r.y & 0xffffu] + R[r.y >> 16] - Ta.x);
+            if (cph == 2) sd -= R[r.z & 0xffffu] + R[r.z >> 16] - Tb.x;
+            v = sd;
+          }
+          if (hf) {
+            double fo = T0.y - Ta.y - Tb.y;
+            if (cph == 2 && (r.w & (1u << 12))) {
+              // global entry i sits at slot (i % KE) * CB + i / KE; its staging row is strength position i's
+              const uint32_t s0 = r.w >> 14;
+              const int i = (int)(s0 % (uint32_t)CB) * KE + (int)(s0 / (uint32_t)CB);
+              fo += ((const double2*)St)[i + (i >> 4)].y;
+            }
+            v += fo;
+          }
+          acc[k] += v;
+        }
+        if (last) {
+          if (h < stride) dst[(uint32_t)h] = h < n_own ? P.scale * lo[k] * acc[k] : 0.0;
+          acc[k] = 0.0;
+        }
+        __builtin_amdgcn_sched_barrier(0);   // one hand's LDS reads in flight at a time (registers)
+      }
+      __syncthreads();   // the next item's staging and slots overwrite what the queries read
     }
   }
 }
@@ -2080,6 +2271,10 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
   DBuf<GRed> red;
   int n_red = 0, red_blocks = 0;
   DBuf<double> part[2];
+  // FP64 products: row chunks (DevDir::items) per class
+  std::vector<int32_t> f64_h[kGrpClasses];
+  DBuf<int32_t> f64[kGrpClasses], f64_act[kGrpClasses];
+  int n_f64[kGrpClasses] = {}, n_f64_act[kGrpClasses] = {};
   bool built = false;
 };
 
@@ -2307,15 +2502,16 @@ static int upload_grp_active(Game* g, int d) {
       if (rc) return rc;
       E.count_act[kind][c] = (int)L.size() / 4;
     }
-  for (int c = 0; c < kGrpClasses; ++c) {
-    std::vector<int32_t> L;
-    const std::vector<int32_t>& F = E.cut_h[c];
-    for (size_t i = 0; i + 3 < F.size(); i += 4)
-      if (all || g->listed[F[i + 2]]) L.insert(L.end(), F.begin() + i, F.begin() + i + 4);
-    int rc = E.cut_act[c].upload(L);
-    if (rc) return rc;
-    E.n_cut_act[c] = (int)L.size() / 4;
-  }
+  for (int c = 0; c < kGrpClasses; ++c)
+    for (int f64 = 0; f64 < 2; ++f64) {
+      std::vector<int32_t> L;
+      const std::vector<int32_t>& F = f64 ? E.f64_h[c] : E.cut_h[c];
+      for (size_t i = 0; i + 3 < F.size(); i += 4)
+        if (all || g->listed[F[i + 2]]) L.insert(L.end(), F.begin() + i, F.begin() + i + 4);
+      int rc = (f64 ? E.f64_act : E.cut_act)[c].upload(L);
+      if (rc) return rc;
+      (f64 ? E.n_f64_act : E.n_cut_act)[c] = (int)L.size() / 4;
+    }
   return PMX_OK;
 }
 
@@ -2426,9 +2622,19 @@ static int upload_grp(Game* g, int d) {
   if ((rc = E.ctx.upload(M.ctx)) || (rc = E.groups.upload(groups)) || (rc = E.q.upload(M.q)) ||
       (rc = E.src.upload(M.src)) || (rc = E.meta.upload(M.meta)) || (rc = E.rk.upload(M.rk)))
     return rc;
+  // the FP64 products' row chunks by class
+  const MvDir& D = hg.dir[d];
+  for (auto& v : E.f64_h) v.clear();
+  for (size_t b = 0; b + 1 < D.blk.size(); ++b) {
+    int ctx = -1;
+    for (int it = D.blk[b]; it < D.blk[b + 1] && ctx < 0; ++it) ctx = D.items[it].ctx;
+    E.f64_h[M.inst_cls[D.blk_inst[b]]].insert(E.f64_h[M.inst_cls[D.blk_inst[b]]].end(),
+                                              {D.blk[b], D.blk[b + 1], D.blk_inst[b], ctx});
+  }
   for (int c = 0; c < kGrpClasses; ++c) {
-    if ((rc = E.cut[c].upload(E.cut_h[c]))) return rc;
+    if ((rc = E.cut[c].upload(E.cut_h[c])) || (rc = E.f64[c].upload(E.f64_h[c]))) return rc;
     E.n_cut[c] = (int)E.cut_h[c].size() / 4;
+    E.n_f64[c] = (int)E.f64_h[c].size() / 4;
   }
   for (int kind = 0; kind < GrpDir::kKinds; ++kind)
     for (int c = 0; c < kGrpClasses; ++c) {
@@ -2449,9 +2655,9 @@ static int upload_dir(Game* g, int d) {
   if ((rc = E.red.upload(D.red))) return rc;
   E.nred = (int)D.red.size();
   if ((rc = E.part.alloc((size_t)std::max<int64_t>(D.part_elems, 1)))) return rc;
-  g->dg[d].built = false;
-  if (hg.mv_kernel == 4 && (rc = upload_grp(g, d))) return rc;
-  return upload_mc(g, d);
+  if ((rc = upload_grp(g, d))) return rc;   // also the contexts of the FP64 products
+  g->dm[d].block = 0;
+  return hg.mv_kernel == 4 ? PMX_OK : upload_mc(g, d);
 }
 
 // Block records of one player's regret launches for the instances marked in
@@ -2682,14 +2888,13 @@ static McParams mc_params(Game* g, int d, const MvParams& like, int c) {
   McParams P;
   P.items = g->dd[d].items.p;
   // the solver's launches (active flags set) take the lists without retired
-  // instances; the FP64 gap takes the full lists
+  // instances
   const bool solver = like.active != nullptr;
   P.chunks = (const int4*)(solver ? E.chunks_act[c].p : E.chunks[c].p);
   P.ctx = E.ctx.p;
   P.q = (const uint4*)E.q.p;
   P.pos = (const uint2*)E.pos.p;
   P.meta = E.meta.p;
-  P.lam = g->lam.p;
   P.lamf = g->lamf.p;
   P.active = like.active;
   P.part = g->dd[d].part.p;
@@ -2706,17 +2911,16 @@ static constexpr size_t mc_lds() {
 }
 
 // LDS bytes of the largest class a launch of the chunk-aligned kernel needs.
-template <typename IO>
 static size_t mc_lds_max(Game* g) {
   size_t m = 0;
   for (int c = 0; c < kMcClasses; ++c) {
     if (!g->dm[0].count[c] && !g->dm[1].count[c]) continue;
     size_t b = 0;
     if (g->dm[0].block == 512)
-      b = c == 0 ? mc_lds<512, 1, IO>() : c == 1 ? mc_lds<512, 2, IO>() : mc_lds<512, 3, IO>();
+      b = c == 0 ? mc_lds<512, 1, float>() : c == 1 ? mc_lds<512, 2, float>() : mc_lds<512, 3, float>();
     else
-      b = c == 0 ? mc_lds<256, 1, IO>() : c == 1 ? mc_lds<256, 2, IO>() : c == 2 ? mc_lds<256, 3, IO>()
-        : c == 3 ? mc_lds<256, 4, IO>() : mc_lds<256, 5, IO>();
+      b = c == 0 ? mc_lds<256, 1, float>() : c == 1 ? mc_lds<256, 2, float>() : c == 2 ? mc_lds<256, 3, float>()
+        : c == 3 ? mc_lds<256, 4, float>() : mc_lds<256, 5, float>();
     m = std::max(m, b);
   }
   return m;
@@ -2789,6 +2993,17 @@ static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, 
   return PMX_OK;
 }
 
+// Rows cut into parts: sum the partial rows (after the join into s).
+template <typename IO>
+static void launch_mv_reduce(Game* g, const MvParams& P0, IO* out0, const MvParams& P1, IO* out1, int n_launched,
+                             hipStream_t s) {
+  const int nr0 = P0.nblk > 0 ? g->dd[P0.dir].nred : 0, nr1 = P1.nblk > 0 ? g->dd[P1.dir].nred : 0;
+  if (n_launched > 0 && nr0 + nr1 > 0)
+    hipLaunchKernelGGL((k_mv_reduce<IO>), dim3(nr0 + nr1), dim3(256), 0, s, g->dd[P0.dir].red.p, nr0,
+                       (const IO*)g->dd[P0.dir].part.p, out0, g->dd[P1.dir].red.p,
+                       (const IO*)g->dd[P1.dir].part.p, out1, P0.active);
+}
+
 template <typename IO>
 static int launch_mc(Game* g, const MvParams& P0, const IO* in0, IO* out0, const MvParams& P1, const IO* in1,
                      IO* out1, hipStream_t s, double* tick) {
@@ -2828,12 +3043,7 @@ static int launch_mc(Game* g, const MvParams& P0, const IO* in0, IO* out0, const
   if (rc) return rc;
   // every instance retired from the lists: the iteration still counts
   if (n == 0 && tick) hipLaunchKernelGGL(k_add1, dim3(1), dim3(1), 0, s, tick);
-  // rows cut into parts: sum the partial rows (after the join into s)
-  const int nr0 = P0.nblk > 0 ? g->dd[P0.dir].nred : 0, nr1 = P1.nblk > 0 ? g->dd[P1.dir].nred : 0;
-  if (n > 0 && nr0 + nr1 > 0)
-    hipLaunchKernelGGL((k_mv_reduce<IO>), dim3(nr0 + nr1), dim3(256), 0, s, g->dd[P0.dir].red.p, nr0,
-                       (const IO*)g->dd[P0.dir].part.p, out0, g->dd[P1.dir].red.p,
-                       (const IO*)g->dd[P1.dir].part.p, out1, P0.active);
+  launch_mv_reduce(g, P0, out0, P1, out1, n, s);
   HIP_TRY(hipGetLastError());
   return PMX_OK;
 }
@@ -2974,18 +3184,73 @@ static int launch_grp(Game* g, const MvParams& P0, const float* in0, float* out0
   return PMX_OK;
 }
 
-template <typename IO>
-static int launch_mv(Game* g, MvParams P0, const IO* in0, IO* out0, MvParams P1, const IO* in1,
-                     IO* out1, hipStream_t s, double* tick = nullptr) {
-  const int nb = P0.nblk + P1.nblk;
-  if (nb == 0) return PMX_OK;
-  if constexpr (sizeof(IO) == 4) {
-    if (g->hg.mv_kernel == 4) return launch_grp(g, P0, in0, out0, P1, in1, out1, s, tick);
+static DParams mvd_params(Game* g, int d, const MvParams& like, int c) {
+  DevGrp& E = g->dg[d];
+  const bool listed = like.active != nullptr;
+  DParams P;
+  P.items = g->dd[d].items.p;
+  P.chunks = (const int4*)(listed ? E.f64_act[c].p : E.f64[c].p);
+  P.ctx = E.ctx.p;
+  P.q = (const uint4*)E.q.p;
+  P.rk = E.rk.p;
+  P.src = E.src.p;
+  P.meta = E.meta.p;
+  P.lam = g->lam.p;
+  P.active = like.active;
+  P.part = g->dd[d].part.p;
+  P.scale = like.scale;
+  P.nchunk = like.nblk > 0 ? (listed ? E.n_f64_act[c] : E.n_f64[c]) : 0;
+  return P;
+}
+
+// FP64 products (the gap, precision checks): one launch per hands-per-thread
+// class of the grouped layout, the classes concurrently, then the sums of
+// partial rows.
+static int launch_mvd(Game* g, const MvParams& P0, const double* in0, double* out0, const MvParams& P1,
+                      const double* in1, double* out1, hipStream_t s) {
+  int cls[kGrpClasses], n = 0;
+  int64_t work[kGrpClasses], wgs = 0;
+  for (int c = 0; c < kGrpClasses; ++c) {
+    const int nc = mvd_params(g, P0.dir, P0, c).nchunk + mvd_params(g, P1.dir, P1, c).nchunk;
+    if (nc == 0) continue;
+    work[n] = (int64_t)nc * kGrpKE[c];
+    wgs += nc;
+    cls[n++] = c;
   }
+  const int rc = fork_launches(g, s, n, work, wgs, [&](int i, hipStream_t st, bool) {
+    const int c = cls[i];
+    const DParams A = mvd_params(g, P0.dir, P0, c), B = mvd_params(g, P1.dir, P1, c);
+    auto go = [&](auto kern, size_t lds) {
+      hipLaunchKernelGGL(kern, dim3(A.nchunk + B.nchunk), dim3(512), lds, st, A, in0, out0, B, in1, out1);
+    };
+    switch (c) {
+      case 0: go(k_mvd<1>, mvd_lds<1>()); break;
+      case 1: go(k_mvd<2>, mvd_lds<2>()); break;
+      case 2: go(k_mvd<3>, mvd_lds<3>()); break;
+      case 3: go(k_mvd<4>, mvd_lds<4>()); break;
+      default: go(k_mvd<5>, mvd_lds<5>()); break;
+    }
+    return PMX_OK;
+  });
+  if (rc) return rc;
+  launch_mv_reduce(g, P0, out0, P1, out1, n, s);
+  HIP_TRY(hipGetLastError());
+  return PMX_OK;
+}
+
+static int launch_mv(Game* g, MvParams P0, const float* in0, float* out0, MvParams P1, const float* in1, float* out1,
+                     hipStream_t s, double* tick = nullptr) {
+  if (P0.nblk + P1.nblk == 0) return PMX_OK;
+  if (g->hg.mv_kernel == 4) return launch_grp(g, P0, in0, out0, P1, in1, out1, s, tick);
   if (g->hg.mv_kernel < 2 || g->hg.mv_kernel > 4) return fail(PMX_ESTATE, "no matvec schedule set");
-  if (mc_lds_max<IO>(g) > (size_t)g->max_lds)
+  if (mc_lds_max(g) > (size_t)g->max_lds)
     return fail(PMX_EINVAL, "matvec workgroup needs more LDS than this device gives a workgroup");
-  return launch_mc<IO>(g, P0, in0, out0, P1, in1, out1, s, tick);
+  return launch_mc<float>(g, P0, in0, out0, P1, in1, out1, s, tick);
+}
+static int launch_mv(Game* g, MvParams P0, const double* in0, double* out0, MvParams P1, const double* in1,
+                     double* out1, hipStream_t s) {
+  if (P0.nblk + P1.nblk == 0) return PMX_OK;
+  return launch_mvd(g, P0, in0, out0, P1, in1, out1, s);
 }
 
 static MvParams empty_params(const MvParams& like) {
@@ -3312,7 +3577,7 @@ int game_tune(Game* g, int32_t kernel, int32_t rows_per_chunk) {
   }
   g->hg.mv_kernel = kernel;
   if (kernel == 4) {
-    g->hg.groups_per_chunk = rows_per_chunk;   // the FP64 products keep their chunk-aligned layout
+    g->hg.groups_per_chunk = rows_per_chunk;   // the FP64 products keep their row chunks
   } else {
     g->hg.rows_per_block = rows_per_chunk;
     g->hg.mc_block = kernel == 3 ? 512 : 256;
@@ -3396,7 +3661,7 @@ int matvec_A(Game* g, const float* y, float* out, void* stream) {
   if (rc) return rc;
   if (!y || !out) return fail(PMX_EINVAL, "null vector");
   MvParams P = mv_params(g, 0, 1.0);
-  return launch_mv<float>(g, P, y, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
+  return launch_mv(g, P, y, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
 }
 
 int matvec_AT(Game* g, const float* x, float* out, void* stream) {
@@ -3404,7 +3669,7 @@ int matvec_AT(Game* g, const float* x, float* out, void* stream) {
   if (rc) return rc;
   if (!x || !out) return fail(PMX_EINVAL, "null vector");
   MvParams P = mv_params(g, 1, 1.0);
-  return launch_mv<float>(g, P, x, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
+  return launch_mv(g, P, x, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
 }
 
 int matvec_A_f64(Game* g, const double* y, double* out, void* stream) {
@@ -3412,7 +3677,7 @@ int matvec_A_f64(Game* g, const double* y, double* out, void* stream) {
   if (rc) return rc;
   if (!y || !out) return fail(PMX_EINVAL, "null vector");
   MvParams P = mv_params(g, 0, 1.0);
-  return launch_mv<double>(g, P, y, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
+  return launch_mv(g, P, y, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
 }
 
 int matvec_AT_f64(Game* g, const double* x, double* out, void* stream) {
@@ -3420,14 +3685,14 @@ int matvec_AT_f64(Game* g, const double* x, double* out, void* stream) {
   if (rc) return rc;
   if (!x || !out) return fail(PMX_EINVAL, "null vector");
   MvParams P = mv_params(g, 1, 1.0);
-  return launch_mv<double>(g, P, x, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
+  return launch_mv(g, P, x, out, empty_params(P), nullptr, nullptr, (hipStream_t)stream);
 }
 
 int matvec_pair(Game* g, const float* y, const float* x, float* Ay, float* ATx, void* stream) {
   int rc = ensure_device(g);
   if (rc) return rc;
   if (!y || !x || !Ay || !ATx) return fail(PMX_EINVAL, "null vector");
-  return launch_mv<float>(g, mv_params(g, 0, 1.0), y, Ay, mv_params(g, 1, 1.0), x, ATx,
+  return launch_mv(g, mv_params(g, 0, 1.0), y, Ay, mv_params(g, 1, 1.0), x, ATx,
                           (hipStream_t)stream);
 }
 
@@ -3653,11 +3918,11 @@ static int enqueue_iteration(Game* g, hipStream_t s) {
   int rc;
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, -1.0);
   PA.active = PT.active = g->active.p;
-  if ((rc = launch_mv<float>(g, PA, g->x[1].p, g->grad[0].p, empty_params(PA), nullptr, nullptr, s,
+  if ((rc = launch_mv(g, PA, g->x[1].p, g->grad[0].p, empty_params(PA), nullptr, nullptr, s,
                              g->tdev.p)))
     return rc;
   if ((rc = rm_update(g, 0, s))) return rc;
-  if ((rc = launch_mv<float>(g, PT, g->x[0].p, g->grad[1].p, empty_params(PT), nullptr, nullptr, s)))
+  if ((rc = launch_mv(g, PT, g->x[0].p, g->grad[1].p, empty_params(PT), nullptr, nullptr, s)))
     return rc;
   if ((rc = rm_update(g, 1, s))) return rc;
   return PMX_OK;
@@ -3777,7 +4042,7 @@ static int gap_launches(Game* g, const double* xsum, const double* ysum, const i
                         const GapBufs& B) {
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, 1.0);
   PA.active = PT.active = need_dev;
-  const int rc = launch_mv<double>(g, PA, ysum, B.gd[0], PT, xsum, B.gd[1], s);
+  const int rc = launch_mv(g, PA, ysum, B.gd[0], PT, xsum, B.gd[1], s);
   return rc ? rc : br_values(g, B.gd, B.br, s, need_dev);
 }
 

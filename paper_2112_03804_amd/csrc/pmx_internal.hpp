@@ -267,6 +267,7 @@ struct GrpDir {
   static constexpr int kKinds = 4;
   std::vector<int32_t> chunks[kKinds][kGrpClasses];
   int max_chunk[kGrpClasses] = {0, 0, 0, 0, 0};
+  std::vector<int> inst_cls;            // hands-per-thread class of each instance
 };
 
 // Technique B's explicit factors of a one-instance river endgame (host and
@@ -393,7 +394,7 @@ struct HostGame {
   int64_t elems[2] = {0, 0};
   int mv_kernel = 4;                    // FP32 products: 2 / 3 chunk-aligned layout with 256 / 512
                                         // threads, 4 grouped layout
-  int rows_per_block = 1;               // chunk-aligned layout (also the FP64 products): rows per chunk
+  int rows_per_block = 1;               // row chunks of the chunk-aligned layout and the FP64 products
   int mc_block = 256;                   // chunk-aligned layout: threads per workgroup
   int groups_per_chunk = 1;             // kernel 4: groups per workgroup
   MvDir dir[2];

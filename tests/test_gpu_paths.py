@@ -141,3 +141,36 @@ def test_network_inference(rows):
     assert ((got - ref).abs() <= 512 * 2.0 ** -24 * mag + 2 * 2.0 ** -8 * top).all()
     # and nearly all of them by the summation order alone
     assert ((got - ref).abs() <= 512 * 2.0 ** -24 * mag).float().mean() > 0.98
+
+
+# FP64 products: both sides of every hands-per-thread class and of the 512
+# threads of a workgroup, one hand, one-card hands, several items per chunk
+F64_CASES = ([("n%d_%d" % n, lambda n=n: I.river_config(seed=n[0], n_keep=n, bet_fracs=(0.5,), max_raises=0))
+              for n in [(1, 1081), (2, 1), (255, 256), (257, 512), (513, 511), (768, 769), (1024, 1025), (1081, 1023)]]
+             + [("cards1", lambda: I.small_river(2, deck_size=40, cards_per_hand=1)),
+                ("runouts", lambda: I.small_turn_river(6, deck_size=16, n_board=3, cards_per_hand=2, stack=12.0,
+                                                       zero_frac=0.2))])
+
+
+@pytest.mark.parametrize("name,fn", F64_CASES, ids=[c[0] for c in F64_CASES])
+def test_fp64_products(name, fn):
+    d = fn()
+    g = _game([d, I.small_river(0)])
+    per, (x, y) = _vectors(g, 11, np.float64)
+    Ay, ATx = torch.full_like(x, 7.0), torch.full_like(y, 7.0)
+    g.matvec_A_f64(y, Ay)
+    g.matvec_AT_f64(x, ATx)
+    got_A, got_AT = g.unpack(0, Ay.cpu().numpy()), g.unpack(1, ATx.cpu().numpy())
+    for i, di in enumerate((d, I.small_river(0))):
+        o = payoff.Game(di)
+        xi, yi = per[0][i], per[1][i]
+        lim_A = 1e-12 * payoff.abs_matvec_A(o, yi) + 1e-15 * o.abs_row_sums().max() * yi.max()
+        lim_AT = 1e-12 * payoff.abs_matvec_AT(o, xi) + 1e-15 * o.abs_col_sums().max() * xi.max()
+        assert (np.abs(got_A[i] - o.matvec_A(yi)) <= lim_A).all()
+        assert (np.abs(got_AT[i] - o.matvec_AT(xi)) <= lim_AT).all()
+    # padding is written as 0
+    for p, v in ((0, Ay), (1, ATx)):
+        flat = v.cpu().numpy()
+        for L in (l[p] for l in g.layouts):
+            rows = flat[L["vec_offset"]:L["vec_offset"] + L["n_seq"] * L["stride"]].reshape(L["n_seq"], L["stride"])
+            assert (rows[:, L["n_hands"]:] == 0).all()
