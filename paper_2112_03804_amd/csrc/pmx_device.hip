@@ -573,14 +573,6 @@ __device__ inline const __attribute__((address_space(4))) T* cst(const T* p) {
   return (const __attribute__((address_space(4))) T*)p;
 }
 
-// Loads issued whatever the condition (at index 0 when it fails) and
-// selected afterwards, so that no branch waits on them.
-template <typename T>
-__device__ inline T ld_sel(const T* p, int64_t i, bool ok, T zero) {
-  const T v = p[ok ? i : 0];
-  return ok ? v : zero;
-}
-
 // A group record in scalar registers.
 struct GGroupS {
   int32_t in[kGrpComps], out[kGrpComps];
@@ -787,13 +779,14 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
     for (int k = 0; k < (CARRY ? KH : 1); ++k) acc[o][k] = 0.0;
   {
     const GGroupS G = load_group(P.groups + g0);
+    // raw loads at in-bounds hands, masked when they are staged: a select here
+    // would wait for them before the context's records are asked for
 #pragma unroll
-    for (int j = 0; j < NC; ++j)
+    for (int j = 0; j < NC; ++j) {
+      const float* __restrict__ row = in + max(G.in[j], 0);
 #pragma unroll
-      for (int k = 0; k < KH; ++k) {
-        const int h = tid + k * BLK;
-        v[j][k] = ld_sel(in, G.in[j] + h, G.in[j] >= 0 && h < G.n_in, 0.f);
-      }
+      for (int k = 0; k < KH; ++k) v[j][k] = row[(uint32_t)min(tid + k * BLK, G.n_in - 1)];
+    }
   }
   int gi = g0;
   while (gi < g1) {
@@ -802,7 +795,6 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
     const auto cp = cst(P.ctx + ctx);
     const int n_own = cp->n_own, n_opp = cp->n_opp, cph = cp->cph, n_chunk = cp->n_chunk;
     const int zrow = cp->zrow;
-    const uint32_t trash = (uint32_t)cp->trash;
     uint32_t rko[KH], srcp[KE / 2];
     float lop[KH], low[KH];
     uint4 qr[KH];
@@ -814,14 +806,14 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       const uint32_t* sp = P.src + cp->src_off;
 #pragma unroll
       for (int k = 0; k < KH; ++k) {
-        const int h = tid + k * BLK;
-        rko[k] = h < n_opp ? (uint32_t)ld_sel(rk, h, h < n_opp, (uint16_t)0) : trash;
-        lop[k] = ld_sel(lopp, h, h < n_opp, 0.f);
-        qr[k] = ld_sel(qp, h, h < n_own, make_uint4(0xffffffffu, 0u, 0u, 0u));
-        low[k] = ld_sel(lown, h, h < n_own, 0.f);
+        const uint32_t ho = (uint32_t)min(tid + k * BLK, n_opp - 1), hw = (uint32_t)min(tid + k * BLK, n_own - 1);
+        rko[k] = rk[ho];
+        lop[k] = lopp[ho];
+        qr[k] = qp[hw];
+        low[k] = lown[hw];
       }
 #pragma unroll
-      for (int j = 0; j < KE / 2; ++j) srcp[j] = sp[j * BLK + tid];
+      for (int j = 0; j < KE / 2; ++j) srcp[j] = sp[(uint32_t)(j * BLK + tid)];
     }
     const uint32_t cm = P.meta[cp->meta_off + tid];
     const bool wlive = (tid & ~63) < n_chunk;
@@ -852,7 +844,7 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
         if (h < n_opp) {
           float w[NC];
 #pragma unroll
-          for (int j = 0; j < NC; ++j) w[j] = lop[k] * v[j][k];
+          for (int j = 0; j < NC; ++j) w[j] = G.in[j] >= 0 ? lop[k] * v[j][k] : 0.f;
           GSlot<NC>::st(St + (rko[k] >> SH), w);
         }
       }
@@ -864,12 +856,11 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       }
       if (gi + 1 < g1) {
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
+        for (int j = 0; j < NC; ++j) {
+          const float* __restrict__ row = in + max(nin[j], 0);
 #pragma unroll
-          for (int k = 0; k < KH; ++k) {
-            const int h = tid + k * BLK;
-            v[j][k] = ld_sel(in, nin[j] + h, nin[j] >= 0 && h < nn_in, 0.f);
-          }
+          for (int k = 0; k < KH; ++k) v[j][k] = row[(uint32_t)min(tid + k * BLK, nn_in - 1)];
+        }
       }
       __syncthreads();
       // gather the chunk and sum it (the entries of the components with
