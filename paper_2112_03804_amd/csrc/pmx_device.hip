@@ -1211,15 +1211,17 @@ struct TpParams {
   const int2* blocks;
 };
 
-// Per-iteration constants of the regret update and the averaging weight.
+// Weight of iteration t's plan in the average: t^gamma (gamma 1 for RM+).
+__device__ inline double avg_weight(int gamma, double t) {
+  return gamma == 1 ? t : (gamma == 2 ? t * t : t * t * t);
+}
+// Per-iteration constants of the regret update.
 struct RmStep {
-  double w;                  // weight of this iteration's plan in the average
   float dp, dn;              // factors for positive / other regrets
   bool floor;                // RM+: clip regrets at 0
 };
-__device__ inline RmStep rm_step(int dcfr, int gamma, float alpha, float beta, double t) {
+__device__ inline RmStep rm_step(int dcfr, float alpha, float beta, double t) {
   RmStep r;
-  r.w = gamma == 1 ? t : (gamma == 2 ? t * t : t * t * t);
   r.dp = 1.f;
   r.dn = 1.f;
   r.floor = !dcfr;
@@ -1283,7 +1285,7 @@ struct RmParams {
   const int32_t* active;        // per-instance flag (NULL: all)
   int32_t stage_stride;
   int32_t max_rows, max_ext;    // LDS layout of the launch
-  int32_t dcfr, gamma;
+  int32_t dcfr;
   float alpha, beta;
 };
 constexpr int RMW = kRmGroups;              // wavefronts per block, one per subtree group
@@ -1466,12 +1468,12 @@ __device__ inline void rm_merge(float* __restrict__ rsm, int grpv, int col, bool
 // MODE 0: bottom-up and top-down of a piece with no external parent (pulls
 // from deeper pieces first); 1: bottom-up of a deep piece (root values to the
 // stage buffer); 2: top-down of a deep piece (parent weights from x).  The
-// running average takes the previous plan (weight K.w) in the pass that
-// overwrites x.  DC: discounted CFR regrets (else RM+).
+// previous plan is not read: k_avg takes the plans into the running average.
+// DC: discounted CFR regrets (else RM+).
 template <int MODE, bool DC>
 __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict__ g, float* __restrict__ R,
-                                                  float* __restrict__ x, double* __restrict__ xs,
-                                                  float* __restrict__ stage, const double* __restrict__ tdev) {
+                                                  float* __restrict__ x, float* __restrict__ stage,
+                                                  const double* __restrict__ tdev) {
   extern __shared__ float rsm[];
   const RmTask T = P.blocks[blockIdx.x].t;
   const int h0 = P.blocks[blockIdx.x].h0;
@@ -1486,7 +1488,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
   float* Al = rsm + kRmRowLocal * 64;       // [max_rows][64]: g, then the new x
   float* Rl = Al + P.max_rows * 64;         // [max_rows][64]
   const int64_t base = T.vec_base + h, stride = T.stride;
-  const RmStep K = rm_step(DC, P.gamma, P.alpha, P.beta, *tdev);
+  const RmStep K = rm_step(DC, P.alpha, P.beta, *tdev);
   // row ids, one per lane (a second for rows 64 + lane when pieces may
   // exceed 64 rows): computed for contiguous pieces, else from the table
   static_assert(kTaskRowsMax <= 128, "row ids are held in at most two registers");
@@ -1501,10 +1503,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
                        ? (MODE == 1 ? P.ext_slot[T.ext_off + lane] : P.ext_seq[T.ext_off + lane]) : 0;
   // loads at in-bounds hands (clamped) of the wavefront's rows, all issued
   // before the first is waited for (the rows past the piece's end are not
-  // loaded: a uniform exit, no wait); the old plan and the running average
-  // stay in registers until the stores at the end
-  float c[RMR];
-  double d[RMR];
+  // loaded: a uniform exit, no wait)
   {
     float a[RMR], b[RMR];
     const int64_t cbase = T.vec_base + (act ? h : T.n_hands - 1);
@@ -1515,10 +1514,6 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
       const int64_t idx = cbase + (int64_t)row_id(r) * stride;
       if (MODE != 2) a[k] = g[idx];
       b[k] = R[idx];
-      if (MODE != 1) {
-        c[k] = x[idx];
-        d[k] = xs[idx];
-      }
     }
     if (MODE == 2 && wv == 0 && T.n_ext > 0) {
       // parent weights of the external parents, all loads in flight at once
@@ -1601,10 +1596,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
       if (r < SL) {
         const int64_t idx = base + (int64_t)row_id(r) * stride;
         if (MODE != 2) R[idx] = b[k];
-        if (MODE != 1) {
-          x[idx] = a[k];
-          xs[idx] = d[k] + K.w * (double)c[k];
-        }
+        if (MODE != 1) x[idx] = a[k];
       }
     }
   }
@@ -1697,8 +1689,8 @@ __device__ inline void rmq_down(float* __restrict__ Al, const float* __restrict_
 
 template <int MODE, bool DC, int ROWS = kTaskRowsMax>
 __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict__ g, float* __restrict__ R,
-                                                  float* __restrict__ x, double* __restrict__ xs,
-                                                  float* __restrict__ stage, const double* __restrict__ tdev) {
+                                                  float* __restrict__ x, float* __restrict__ stage,
+                                                  const double* __restrict__ tdev) {
   extern __shared__ float rsm[];
   const RmTask T = P.blocks[blockIdx.x >> 2].t;
   const int h0 = P.blocks[blockIdx.x >> 2].h0 + RQH * (int)(blockIdx.x & 3);
@@ -1716,7 +1708,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   float* Rl = Al + P.max_rows * RQH;
   const int64_t hc = act ? h : T.n_hands - 1;   // in-bounds hand for loads
   const int64_t stride = T.stride;
-  const RmStep K = rm_step(DC, P.gamma, P.alpha, P.beta, *tdev);
+  const RmStep K = rm_step(DC, P.alpha, P.beta, *tdev);
   const int rowv = T.row0 >= 0 ? T.row0 + lane : (lane < SL ? P.rows[T.rows_off + lane] : 0);
   const int infv = lane < T.n_inf ? P.infs[T.inf_off + lane] : 0;
   const bool grouped = T.grp_off >= 0;
@@ -1727,8 +1719,6 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   // row 4 (wv + RMW k) + q of hand hl
   constexpr int RQK = ROWS / (4 * RMW);
   static_assert(ROWS == kTaskRowsMax || MODE == 0, "whole-treeplex pieces have no external parents");
-  float c[RQK];
-  double d[RQK];
   int rid[RQK];
   {
     float a[RQK], b[RQK];
@@ -1739,10 +1729,6 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
       const int64_t idx = T.vec_base + hc + (int64_t)rid[k] * stride;
       if (MODE != 2) a[k] = g[idx];
       b[k] = R[idx];
-      if (MODE != 1) {
-        c[k] = x[idx];
-        d[k] = xs[idx];
-      }
     }
     if (MODE == 2 && wv == 0 && T.n_ext > 0) {
       float xe[kTaskExtMax];
@@ -1820,12 +1806,74 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
       if (r < SL) {
         const int64_t idx = T.vec_base + h + (int64_t)rid[k] * stride;
         if (MODE != 2) R[idx] = b[k];
-        if (MODE != 1) {
-          x[idx] = a[k];
-          xs[idx] = d[k] + K.w * (double)c[k];
-        }
+        if (MODE != 1) x[idx] = a[k];
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Running averages.  An iteration's plan is weighted into the FP64 sums not by
+// the update that overwrites it (16 of that update's 36 bytes per element
+// were the sums' read and write, 4 more the old plan's) but for several
+// iterations at once: the plans of a segment of m iterations lie in m buffers
+// (the first in the plan's own), and this kernel adds them in iteration order,
+// one FMA each, the same sums bit for bit.  HBM-bound: 16 + 4 m bytes per
+// element and segment, 6 per iteration at m = 8, read and written as whole
+// rows (16-byte accesses: rows are multiples of four elements).
+// Batch of 512 (36.6 M elements): 401 us per segment of 8, 4.4 TB/s; the
+// updates fell from 270 to 204 us per iteration.  Turn + river game: 427 us,
+// and 428 to 328 us.
+// ---------------------------------------------------------------------------
+struct AvgChunk {
+  int64_t off;                  // element offset, a multiple of four
+  int32_t n, inst;              // elements, a multiple of four
+};
+struct AvgSide {
+  const float* x0;              // the segment's first plan
+  const float* ring;            // the others, `stride` elements apart
+  int64_t stride;
+  double* xs;
+};
+constexpr int kAvgChunk = 4096;
+
+// *tdev = iterations completed before the segment's last one.
+template <int M>
+__global__ __launch_bounds__(256) void k_avg(const AvgChunk* __restrict__ c0, int n0, AvgSide A,
+                                             const AvgChunk* __restrict__ c1, AvgSide B,
+                                             const int32_t* __restrict__ active, const double* __restrict__ tdev,
+                                             int m, int gamma) {
+  const bool second = (int)blockIdx.x >= n0;
+  const AvgSide S = second ? B : A;
+  const AvgChunk C = second ? c1[blockIdx.x - n0] : c0[blockIdx.x];
+  if (!active[C.inst]) return;
+  const double t0 = tdev[0] - (double)(m - 1);
+  double2* __restrict__ xs = (double2*)(S.xs + C.off);
+  const float4* __restrict__ x0 = (const float4*)(S.x0 + C.off);
+  const float4* __restrict__ xr = (const float4*)(S.ring + C.off);
+  const int64_t st = S.stride / 4;
+  for (int i = threadIdx.x; i < C.n / 4; i += 256) {
+    double2 a = xs[2 * i], b = xs[2 * i + 1];
+    auto add = [&](const float4& v, int k) {
+      const double w = avg_weight(gamma, t0 + (double)(k + 1));
+      a.x = fma(w, (double)v.x, a.x);
+      a.y = fma(w, (double)v.y, a.y);
+      b.x = fma(w, (double)v.z, b.x);
+      b.y = fma(w, (double)v.w, b.y);
+    };
+    if (M > 0) {   // m == M
+      float4 v[M > 0 ? M : 1];
+#pragma unroll
+      for (int k = 0; k < M; ++k) v[k] = k == 0 ? x0[i] : xr[(k - 1) * st + i];
+#pragma unroll
+      for (int k = 0; k < M; ++k) add(v[k], k);
+    } else {
+      add(x0[i], 0);
+#pragma unroll 4
+      for (int k = 1; k < m; ++k) add(xr[(k - 1) * st + i], k);
+    }
+    xs[2 * i] = a;
+    xs[2 * i + 1] = b;
   }
 }
 
@@ -2307,6 +2355,10 @@ struct Game {
   std::vector<int64_t> lam_off[2];   // per player: offset of each instance's lambdas
   // solver state
   DBuf<float> R[2], x[2], grad[2];
+  DBuf<float> ring[2];              // plans 1 .. avg_seg - 1 of a segment (k_avg)
+  int avg_seg = 1;                  // iterations per segment at most
+  DBuf<AvgChunk> avg_chunk[2];
+  int n_avg[2] = {0, 0};
   DBuf<double> xs[2], gd[2], sd[2], br_inst;
   int t = 0;
   double wsum = 0.0;                // averaging weight total of the iterations so far
@@ -2759,6 +2811,8 @@ static int upload_rm(Game* g, int p) {
   return E.stage.alloc((size_t)std::max(T.n_slot, 1) * E.stage_stride);
 }
 
+static void fill_f32(float* p, int64_t n, float v, hipStream_t s);
+
 static int upload_game(Game* g) {
   HostGame& hg = g->hg;
   // lambda of both players, all instances
@@ -2803,6 +2857,22 @@ static int upload_game(Game* g) {
     if ((rc = g->R[p].alloc(n)) || (rc = g->x[p].alloc(n)) || (rc = g->grad[p].alloc(n)) ||
         (rc = g->xs[p].alloc(n)) || (rc = g->gd[p].alloc(n)) || (rc = g->sd[p].alloc(n)))
       return rc;
+  }
+  // segments of the running averages: 32 iterations while the plans are small
+  // (one launch per solver graph or check), else 8 (28 bytes per element, and
+  // the sums cost 6 bytes per element and iteration instead of 20)
+  g->avg_seg = hg.elems[0] + hg.elems[1] <= (1 << 18) ? 32 : 8;
+  for (int p = 0; p < 2; ++p) {
+    const size_t n = (size_t)hg.elems[p];
+    if ((rc = g->ring[p].alloc(n * (g->avg_seg - 1)))) return rc;
+    fill_f32(g->ring[p].p, (int64_t)(n * (g->avg_seg - 1)), 0.f, nullptr);   // padding stays 0
+    std::vector<AvgChunk> ch;
+    for (size_t i = 0; i < hg.inst.size(); ++i) {
+      const int64_t b = hg.inst[i].vec_off[p], e = b + (int64_t)hg.inst[i].sf.n_seq[p] * hg.inst[i].stride[p];
+      for (int64_t o = b; o < e; o += kAvgChunk) ch.push_back({o, (int32_t)std::min<int64_t>(kAvgChunk, e - o), (int32_t)i});
+    }
+    if ((rc = g->avg_chunk[p].upload(ch))) return rc;
+    g->n_avg[p] = (int)ch.size();
   }
   if ((rc = g->br_inst.alloc(2 * hg.inst.size()))) return rc;
   if ((rc = g->tdev.alloc(1))) return rc;
@@ -3278,16 +3348,15 @@ static RmParams rm_params(Game* g, int p, int depth, int first_block) {
   P.max_rows = E.max_rows[depth];
   P.max_ext = E.max_ext[depth];
   P.dcfr = g->dcfr;
-  P.gamma = g->gamma;
   P.alpha = (float)g->alpha;
   P.beta = (float)g->beta;
   return P;
 }
 
-// One player's regret update: bottom-up passes of the deep pieces (deepest
+// One player's regret update, the new plan to x: bottom-up passes of the deep pieces (deepest
 // first), the pieces without external parents, then the top-down passes of
 // the deep pieces (shallowest first).
-static int rm_update(Game* g, int p, hipStream_t s) {
+static int rm_update(Game* g, int p, float* x, hipStream_t s) {
   DevRm& E = g->drm[p];
   float* gr = g->grad[p].p;
   const double* td = g->tdev.p;
@@ -3304,8 +3373,8 @@ static int rm_update(Game* g, int p, hipStream_t s) {
     const bool quad = whole || nb <= g->hg.rm_quad_max;
     const size_t lds = sizeof(float) * (quad ? RQH : 64) * (size_t)(kRmRowLocal + 2 * P.max_rows);
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(quad ? 4 * nb : nb), dim3(64 * RMW), lds, s, P, gr, g->R[p].p, g->x[p].p,
-                         g->xs[p].p, E.stage.p, td);
+      hipLaunchKernelGGL(kern, dim3(quad ? 4 * nb : nb), dim3(64 * RMW), lds, s, P, gr, g->R[p].p, x,
+                         E.stage.p, td);
     };
     if (whole) {
       // one piece per treeplex: the fused pass only
@@ -3902,20 +3971,56 @@ int solver_set_active(Game* g, const int32_t* active_host, void* stream) {
 }
 
 // One alternating RM+ iteration, enqueued on s: g1 = A y_t (its launch also
-// advances the device iteration index t, read by the updates as the
-// averaging weight, so a captured sequence of iterations replays correctly)
-// and Player 1's update, then g2 = -A^T x_{t+1} and Player 2's update.
-static int enqueue_iteration(Game* g, hipStream_t s) {
+// advances the device iteration index t, read by the updates for their
+// discounts, so a captured sequence of iterations replays correctly) and
+// Player 1's update, then g2 = -A^T x_{t+1} and Player 2's update.  The plans
+// y_t, x_t are read from `in` and the new ones written to `out`.
+static int enqueue_iteration(Game* g, const float* const in[2], float* const out[2], hipStream_t s) {
   int rc;
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, -1.0);
   PA.active = PT.active = g->active.p;
-  if ((rc = launch_mv(g, PA, g->x[1].p, g->grad[0].p, empty_params(PA), nullptr, nullptr, s,
-                             g->tdev.p)))
-    return rc;
-  if ((rc = rm_update(g, 0, s))) return rc;
-  if ((rc = launch_mv(g, PT, g->x[0].p, g->grad[1].p, empty_params(PT), nullptr, nullptr, s)))
-    return rc;
-  if ((rc = rm_update(g, 1, s))) return rc;
+  if ((rc = launch_mv(g, PA, in[1], g->grad[0].p, empty_params(PA), nullptr, nullptr, s, g->tdev.p))) return rc;
+  if ((rc = rm_update(g, 0, out[0], s))) return rc;
+  if ((rc = launch_mv(g, PT, out[0], g->grad[1].p, empty_params(PT), nullptr, nullptr, s))) return rc;
+  if ((rc = rm_update(g, 1, out[1], s))) return rc;
+  return PMX_OK;
+}
+
+// A segment of m <= avg_seg iterations: iteration i writes the plans to buffer
+// i, the last one back to the plans' own buffer, whose old content (the
+// segment's first plan) k_avg has taken by then with the others.  Between
+// segments, and so between calls, the state is whole.
+static int enqueue_segment(Game* g, int m, hipStream_t s) {
+  auto buf = [&](int p, int i) { return i == 0 ? g->x[p].p : g->ring[p].p + (size_t)(i - 1) * g->hg.elems[p]; };
+  for (int i = 1; i <= m; ++i) {
+    if (i == m && g->n_avg[0] + g->n_avg[1] > 0) {
+      AvgSide S[2];
+      for (int p = 0; p < 2; ++p) S[p] = {g->x[p].p, g->ring[p].p, g->hg.elems[p], g->xs[p].p};
+      const dim3 grid(g->n_avg[0] + g->n_avg[1]);
+      auto go = [&](auto kern) {
+        hipLaunchKernelGGL(kern, grid, dim3(256), 0, s, g->avg_chunk[0].p, g->n_avg[0], S[0], g->avg_chunk[1].p, S[1],
+                           g->active.p, g->tdev.p, m, g->gamma);
+      };
+      if (m == 8) go(k_avg<8>);
+      else go(k_avg<0>);
+    }
+    const float* in[2] = {buf(0, i - 1), buf(1, i - 1)};
+    float* out[2] = {buf(0, i == m ? 0 : i), buf(1, i == m ? 0 : i)};
+    const int rc = enqueue_iteration(g, in, out, s);
+    if (rc) return rc;
+  }
+  HIP_TRY(hipGetLastError());
+  return PMX_OK;
+}
+
+// n iterations in segments of about equal length.
+static int enqueue_iterations(Game* g, int n, hipStream_t s) {
+  for (int segs = (n + g->avg_seg - 1) / g->avg_seg; segs > 0; --segs) {
+    const int m = (n + segs - 1) / segs;
+    const int rc = enqueue_segment(g, m, s);
+    if (rc) return rc;
+    n -= m;
+  }
   return PMX_OK;
 }
 
@@ -3925,8 +4030,7 @@ static int capture_graph(Game* g) {
   if (g->graph_exec) return PMX_OK;
   if (!g->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&g->cap_stream, hipStreamNonBlocking));
   HIP_TRY(hipStreamBeginCapture(g->cap_stream, hipStreamCaptureModeRelaxed));
-  int rc = PMX_OK;
-  for (int i = 0; i < kGraphIters && rc == PMX_OK; ++i) rc = enqueue_iteration(g, g->cap_stream);
+  const int rc = enqueue_iterations(g, kGraphIters, g->cap_stream);
   hipGraph_t graph = nullptr;
   hipError_t e = hipStreamEndCapture(g->cap_stream, &graph);
   if (rc) {
@@ -3958,8 +4062,7 @@ int solver_step(Game* g, int32_t n_iters, void* stream) {
       left -= g->graph_iters;
     }
   }
-  for (int i = 0; i < left; ++i)
-    if ((rc = enqueue_iteration(g, s))) return rc;
+  if ((rc = enqueue_iterations(g, left, s))) return rc;
   double w = 0.0;
   for (int i = 0; i < n_iters; ++i) {
     g->t += 1;

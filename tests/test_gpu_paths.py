@@ -174,3 +174,40 @@ def test_fp64_products(name, fn):
         for L in (l[p] for l in g.layouts):
             rows = flat[L["vec_offset"]:L["vec_offset"] + L["n_seq"] * L["stride"]].reshape(L["n_seq"], L["stride"])
             assert (rows[:, L["n_hands"]:] == 0).all()
+
+
+# running averages over segments of iterations: any split of the same
+# iterations into calls gives the same bits, captured or not, with retired
+# instances, for every weight power
+AVG_CASES = [
+    ("tiny", lambda: [I.tiny_config()], dict(kind="rm+")),
+    ("batch", lambda: I.batched_configs(3, seed=8, n_lo=40, n_hi=300), dict(kind="dcfr", gamma=3)),
+    ("long_segments", lambda: [I.river_config(seed=4, n_keep=(211, 97), max_raises=2)], dict(kind="dcfr", gamma=2)),
+    ("short_segments", lambda: [I.river_config(seed=6, bet_fracs=(0.33, 0.5, 1.0, 2.0), max_raises=4, stack=900.0)],
+     dict(kind="rm+")),
+]
+
+
+@pytest.mark.parametrize("name,fn,rule", AVG_CASES, ids=[c[0] for c in AVG_CASES])
+def test_averages_do_not_depend_on_the_split(name, fn, rule):
+    descs = fn()
+    states = []
+    for split in ([1] * 41, [41], [8, 33], [7, 9, 25], [32, 8, 1]):
+        g = _game(descs)
+        g.solver_set_params(**rule)
+        done = 0
+        for n in split:
+            g.solver_step(n)
+            done += n
+        if len(descs) > 1:
+            g.solver_set_active([1, 0, 1])
+            g.solver_step(10)
+        torch.cuda.synchronize()
+        states.append([g.solver_get_state(p) for p in range(2)] + [g.solver_get_weights()])
+        g.close()
+    for st in states[1:]:
+        for p in range(2):
+            for k in ("regret", "plan", "avg_sum"):
+                assert np.array_equal(st[p][k], states[0][p][k]), (p, k)
+            assert (st[p]["t"], st[p]["wsum"]) == (states[0][p]["t"], states[0][p]["wsum"])
+        assert np.array_equal(st[2], states[0][2])
