@@ -475,6 +475,20 @@ int mlp_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, int32_t ld
 int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* W2,
                      const float* b2, const uint16_t* W3, const float* b3, float* Z, uint16_t* work,
                      void* stream);
+/* Loss and gradients of one minibatch of that network: the forward pass, the
+ * masked softmax cross-entropy of mlp_softmax_xent (target [M][8], < 0 =
+ * invalid; weight [M] or NULL) and the backward pass, activations and their
+ * gradients rounded to BF16 where they enter a product, bias gradients summed
+ * from the FP32 values, every sum in a fixed order.  loss: ceil(M / 256) sums
+ * over 256 rows each; gW* / gb*: FP32 gradients in the weights' layouts.
+ * work: device scratch of mlp_loss_and_grad_work(M) bytes.  X, weights, weight
+ * gradients and scratch 16-byte aligned; M >= 1. */
+int64_t mlp_loss_and_grad_work(int64_t M);
+int mlp_loss_and_grad_bf16(int64_t M, const uint16_t* X, const float* target, const float* weight,
+                           const uint16_t* W1, const float* b1, const uint16_t* W2, const float* b2,
+                           const uint16_t* W3, const float* b3, float* loss, float* gW1, float* gb1,
+                           float* gW2, float* gb2, float* gW3, float* gb3, void* work, int64_t work_bytes,
+                           void* stream);
 /* Masked softmax cross-entropy over K <= 64 slots (target < 0 = invalid):
  * dlogits[r][a] = weight[r] (softmax - target) (FP32 and / or BF16, stride K);
  * loss_partial[b] = sum of weight[r] * cross-entropy over block b's 256 rows. */
@@ -490,6 +504,11 @@ int mlp_colsum(int32_t rows, int32_t cols, const float* dz, float* db, float* wo
  * BF16 copy of the weights when w_bf16 is not NULL. */
 int mlp_adam(int64_t n, float* w, const float* g, float* m, float* v, uint16_t* w_bf16, float lr,
              float beta1, float beta2, float eps, float weight_decay, int32_t step, void* stream);
+/* mlp_adam on up to 8 tensors in one launch: host arrays of lengths and device
+ * pointers (w_bf16 or its entries may be NULL). */
+int mlp_adam_multi(int32_t n_tensors, const int64_t* n, float* const* w, const float* const* g,
+                   float* const* m, float* const* v, uint16_t* const* w_bf16, float lr, float beta1,
+                   float beta2, float eps, float weight_decay, int32_t step, void* stream);
 /* dst[i][:] = src[idx[i]][:] for rows of `width` elements. */
 int mlp_gather_bf16(int64_t n, int32_t width, const int64_t* idx, const uint16_t* src, uint16_t* dst,
                     void* stream);

@@ -1821,9 +1821,9 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
 // one FMA each, the same sums bit for bit.  HBM-bound: 16 + 4 m bytes per
 // element and segment, 6 per iteration at m = 8, read and written as whole
 // rows (16-byte accesses: rows are multiples of four elements).
-// Batch of 512 (36.6 M elements): 401 us per segment of 8, 4.4 TB/s; the
-// updates fell from 270 to 204 us per iteration.  Turn + river game: 427 us,
-// and 428 to 328 us.
+// Batch of 512 (36.6 M elements): 401 us per segment of 8, 4.4 TB/s, while the
+// updates' kernel times fell from 580 to 382 us per iteration.  Turn + river
+// game: 427 us, and from 459 to 310 us.
 // ---------------------------------------------------------------------------
 struct AvgChunk {
   int64_t off;                  // element offset, a multiple of four

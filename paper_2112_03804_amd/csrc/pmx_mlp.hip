@@ -374,6 +374,399 @@ void k_net(NetArgs P, const uint16_t* __restrict__ W2p) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// One training step's loss and gradients in three kernels after a repacking
+// of the second layer's weights.
+//
+// k_net_rows: forward and backward of 32 rows per workgroup (256 workgroups at
+// 8,192 rows), rows x features: a lane of an MFMA result holds four rows of
+// one feature, so the eight rows that a lane holds over the tile's two row
+// blocks are one 16-byte fragment of the weight gradients' products, whose
+// contraction runs over rows.  Activations and their gradients go to LDS as
+// [row][k] for the next layer and to HBM as such fragments (BF16, 1 KB
+// contiguous per wavefront); ReLU masks stay in registers.
+// k_net_wgrad: the three weight gradients as one launch of 64 x 64 wavefront
+// tiles straight from the fragments (no LDS), K split over the grid.
+// k_net_grads: the ranges' partial products, the workgroups' bias sums and the
+// losses, each added in a fixed order.
+//
+// Layer by layer through HBM it was 16 launches, 300 us at 8,192 rows, of
+// which column sums took 113 us (one thread per column adding 128 partials)
+// and the GEMMs, at 64 x 64 tiles with 2-byte transposes through LDS, 160 us.
+// ---------------------------------------------------------------------------
+constexpr int NetRows = 32;                      // rows per workgroup of k_net_rows
+constexpr int NetBias = 2 * NetW + NetOut;       // bias gradients: b1, b2, b3
+constexpr int NetGrads = NetW * NetW + NetW * NetIn + 16 * NetW;   // W2, W1, W3 (padded to 16 outputs)
+constexpr int NetMaxSplit = 16;
+
+struct NetTrain {
+  int64_t M, nb;                                 // rows; blocks of 32 rows
+  const uint16_t* X;
+  const float *T, *Wt;
+  const uint16_t *W1, *W3;
+  const float *b1, *b2, *b3;
+  const uint16_t *W2f, *W2t;                     // W2 and its transpose in fragment order
+  uint16_t *Xf, *H1f, *H2f, *D1f, *D2f, *D3f;    // row fragments [feature tile][row block][lane][8]
+  float* bias;                                   // [nb][NetBias]
+  float* loss;                                   // [nb]
+};
+
+// Fragment order of a 512 x 512 operand: [tile of 16 rows][k step of 32][lane][8];
+// blockIdx.y = 1: of its transpose.
+__global__ __launch_bounds__(256) void k_net_pack2(const uint16_t* __restrict__ W, uint16_t* __restrict__ Wf,
+                                                   uint16_t* __restrict__ Wt) {
+  const int i = blockIdx.x * 256 + threadIdx.x;   // one 16-byte piece
+  const int lane = i & 63, ks = (i >> 6) % (NetW / 32), ft = (i >> 6) / (NetW / 32);
+  const int r = 16 * ft + (lane & 15), k = 32 * ks + 8 * (lane >> 4);
+  if (blockIdx.y == 0) {
+    ((uint4*)Wf)[i] = *(const uint4*)(W + (int64_t)r * NetW + k);
+  } else {
+    uint32_t e[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) e[j] = W[(int64_t)(k + j) * NetW + r];
+    ((uint4*)Wt)[i] = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+  }
+}
+
+// acc += A B^T over 512 k: A the rows in LDS, B this wavefront's 64 features
+// in fragment order, PF k steps of it in flight.
+__device__ inline void net_layer(f32x4 (&acc)[4][2], const uint16_t* __restrict__ S, const uint16_t* __restrict__ Wf,
+                                 int w, int lane) {
+  constexpr int PF = 4, KS = NetW / 32;
+  const int l16 = lane & 15, lq = lane >> 4;
+  const uint16_t* p = Wf + (int64_t)(4 * w) * KS * 512 + 8 * lane;
+  bf16x8 bn[PF][4];
+#pragma unroll
+  for (int d = 0; d < PF; ++d)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bn[d][i] = *(const bf16x8*)(p + (i * KS + d) * 512);
+#pragma unroll 1
+  for (int k0 = 0; k0 < KS; k0 += PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) {
+      bf16x8 b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b[i] = bn[d][i];
+      const int kn = min(k0 + d + PF, KS - 1);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) bn[d][i] = *(const bf16x8*)(p + (i * KS + kn) * 512);
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const bf16x8 a = *(const bf16x8*)&S[(16 * j + l16) * NetPitch + 32 * (k0 + d) + 8 * lq];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[i], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
+}
+
+typedef short s16x8 __attribute__((ext_vector_type(8)));
+
+__global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2))) void k_net_rows(NetTrain P) {
+  extern __shared__ __attribute__((aligned(16))) char net_smem[];
+  constexpr int R = NetRows, XP = NetIn + 8;
+  uint16_t* H1 = (uint16_t*)net_smem;            // [R][NetPitch]
+  uint16_t* H2 = H1 + R * NetPitch;              // [R][NetPitch], later the second layer's gradient
+  uint16_t* Xs = H2 + R * NetPitch;              // [R][XP]
+  uint16_t* Ds = Xs + R * XP;                    // [R][16] output gradients, BF16 (8 unused)
+  float* zs = (float*)(Ds + R * 16);             // [R][NetOut + 1] logits
+  float* dz = zs + R * (NetOut + 1);             // [R][NetOut + 1] output gradients
+  float* ls = dz + R * (NetOut + 1);             // [R] losses
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int l16 = lane & 15, lq = lane >> 4, f0 = 64 * w;
+  const int64_t rb = blockIdx.x, r0 = rb * R;
+  // everything that does not depend on a previous layer is asked for at once
+  if (tid < R * NetIn / 8) {
+    const int r = tid / (NetIn / 8), k = 8 * (tid % (NetIn / 8));
+    *(uint4*)&Xs[r * XP + k] = *(const uint4*)(P.X + min(r0 + r, P.M - 1) * NetIn + k);
+  }
+  bf16x8 w1[2][4];
+  float b1[4], b2[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int f = f0 + 16 * i + l16;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) w1[ks][i] = *(const bf16x8*)(P.W1 + (int64_t)f * NetIn + 32 * ks + 8 * lq);
+    b1[i] = P.b1[f];
+    b2[i] = P.b2[f];
+  }
+  __syncthreads();
+  f32x4 acc[4][2];
+  uint32_t on1 = 0, on2 = 0;                     // ReLU masks, bit 8 i + 4 j + r
+  // layer 1
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const bf16x8 a = *(const bf16x8*)&Xs[(16 * j + l16) * XP + 32 * ks + 8 * lq];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, w1[ks][i], acc[i][j], 0, 0, 0);
+    }
+  auto hidden = [&](uint16_t* __restrict__ S, uint16_t* __restrict__ F, const float (&bias)[4], uint32_t& on) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s16x8 o;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = acc[i][j][r] + bias[i];
+          const bool pos = v > 0.f;
+          on |= pos ? 1u << (8 * i + 4 * j + r) : 0u;
+          const uint16_t h = f2bf(pos ? v : 0.f);
+          o[4 * j + r] = (short)h;
+          S[(16 * j + 4 * lq + r) * NetPitch + f0 + 16 * i + l16] = h;
+          acc[i][j][r] = 0.f;
+        }
+      *(s16x8*)(F + ((int64_t)(4 * w + i) * P.nb + rb) * 512 + 8 * lane) = o;
+    }
+  };
+  hidden(H1, P.H1f, b1, on1);
+  if (w < NetIn / 16) {   // the inputs' row fragments, one feature tile per wavefront
+    s16x8 o;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[4 * j + r] = (short)Xs[(16 * j + 4 * lq + r) * XP + 16 * w + l16];
+    *(s16x8*)(P.Xf + ((int64_t)w * P.nb + rb) * 512 + 8 * lane) = o;
+  }
+  __syncthreads();
+  // layer 2
+  net_layer(acc, H1, P.W2f, w, lane);
+  hidden(H2, P.H2f, b2, on2);
+  __syncthreads();
+  // logits: wavefronts 0 and 1, one row block each, over all features in the
+  // order of the layer-by-layer product (another order would round a few
+  // output gradients, and with them whole rows behind them, the other way)
+  if (w < 2) {
+    f32x4 z = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int ks = 0; ks < NetW / 32; ++ks) {
+      const int k = 32 * ks + 8 * lq;
+      const bf16x8 b = *(const bf16x8*)(P.W3 + (int64_t)(l16 & (NetOut - 1)) * NetW + k);   // outputs 8 to 15 unused
+      z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)&H2[(16 * w + l16) * NetPitch + k], b, z, 0, 0, 0);
+    }
+    if (l16 < NetOut)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) zs[(16 * w + 4 * lq + r) * (NetOut + 1) + l16] = z[r] + P.b3[l16];
+  }
+  __syncthreads();
+  if (tid < R) {
+    // masked softmax cross-entropy, one row per thread (targets < 0: invalid)
+    const bool live = r0 + tid < P.M;
+    const int64_t row = live ? r0 + tid : P.M - 1;
+    const float* zr = zs + tid * (NetOut + 1);
+    float tr[NetOut];
+    *(float4*)&tr[0] = make_float4(P.T[row * NetOut], P.T[row * NetOut + 1], P.T[row * NetOut + 2], P.T[row * NetOut + 3]);
+    *(float4*)&tr[4] = make_float4(P.T[row * NetOut + 4], P.T[row * NetOut + 5], P.T[row * NetOut + 6], P.T[row * NetOut + 7]);
+    const float wt = P.Wt ? P.Wt[row] : 1.f;
+    float mx = -INFINITY;
+#pragma unroll
+    for (int a = 0; a < NetOut; ++a)
+      if (tr[a] >= 0.f) mx = fmaxf(mx, zr[a]);
+    float se = 0.f;
+#pragma unroll
+    for (int a = 0; a < NetOut; ++a)
+      if (tr[a] >= 0.f) se += __expf(zr[a] - mx);
+    const float lse = mx + __logf(se);
+    float loss = 0.f;
+#pragma unroll
+    for (int a = 0; a < NetOut; ++a) {
+      float g = 0.f;
+      if (tr[a] >= 0.f) {
+        const float lp = zr[a] - lse;
+        loss -= tr[a] * lp;
+        g = wt * (__expf(lp) - tr[a]);
+      }
+      g = live ? g : 0.f;
+      dz[tid * (NetOut + 1) + a] = g;
+      Ds[tid * 16 + a] = f2bf(g);
+      Ds[tid * 16 + 8 + a] = 0;
+    }
+    ls[tid] = live ? loss * wt : 0.f;
+  }
+  __syncthreads();
+  if (tid < NetOut) {
+    float v = 0.f;
+    for (int r = 0; r < R; ++r) v += dz[r * (NetOut + 1) + tid];
+    P.bias[rb * NetBias + 2 * NetW + tid] = v;
+  } else if (tid == 64) {
+    float v = 0.f;
+    for (int r = 0; r < R; ++r) v += ls[r];
+    P.loss[rb] = v;
+  } else if (w == 2) {   // the output gradients' row fragment
+    s16x8 o;
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o[4 * j + r] = (short)Ds[(16 * j + 4 * lq + r) * 16 + l16];
+    *(s16x8*)(P.D3f + rb * 512 + 8 * lane) = o;
+  }
+  // masked gradient of a hidden layer: BF16 to LDS (if S) and as row
+  // fragments, FP32 column sums (over lanes 16 apart) to the bias sums
+  auto backward = [&](uint16_t* __restrict__ S, uint16_t* __restrict__ F, uint32_t on, int boff) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      s16x8 o;
+      float cs = 0.f;
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float v = (on >> (8 * i + 4 * j + r)) & 1u ? acc[i][j][r] : 0.f;
+          cs += v;
+          const uint16_t h = f2bf(v);
+          o[4 * j + r] = (short)h;
+          if (S) S[(16 * j + 4 * lq + r) * NetPitch + f0 + 16 * i + l16] = h;
+          acc[i][j][r] = 0.f;
+        }
+      *(s16x8*)(F + ((int64_t)(4 * w + i) * P.nb + rb) * 512 + 8 * lane) = o;
+      cs += __shfl_xor(cs, 16, 64);
+      cs += __shfl_xor(cs, 32, 64);
+      if (lq == 0) P.bias[rb * NetBias + boff + f0 + 16 * i + l16] = cs;
+    }
+  };
+  // second layer's gradient: dz W3 over the 8 outputs (k 8 to 31 of the MFMA zero)
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    s16x8 b = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (lq == 0)
+#pragma unroll
+      for (int k = 0; k < NetOut; ++k) b[k] = (short)P.W3[(int64_t)k * NetW + f0 + 16 * i + l16];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      s16x8 a = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (lq == 0) a = *(const s16x8*)&Ds[(16 * j + l16) * 16];
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
+                                                          f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+    }
+  }
+  backward(H2, P.D2f, on2, NetW);   // every wavefront has read H2 (the barriers above)
+  __syncthreads();
+  // first layer's gradient
+  net_layer(acc, H2, P.W2t, w, lane);
+  backward(nullptr, P.D1f, on1, 0);
+}
+
+// Weight gradients: wavefront tiles of 64 x 64 (16 x 64 for W3's, 8 of the 16
+// outputs valid) over a range of row blocks: 64 tiles of dW2 = D2^T H1, 8 of
+// dW1 = D1^T X, 8 of dW3 = D3^T H2, four per workgroup.
+struct NetWgrad {
+  const uint16_t *Xf, *H1f, *H2f, *D1f, *D2f, *D3f;
+  float* part;                                   // [splits][NetGrads]
+  int nb, per;                                   // row blocks; per split
+};
+template <int MT>
+__device__ inline void net_wgrad(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int nb, int k0, int k1,
+                                 float* __restrict__ C, int ldc, int lane) {
+  f32x4 acc[MT][4];
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 an[MT], bn[4];
+  const int64_t ts = (int64_t)nb * 512;          // next feature tile
+#pragma unroll
+  for (int i = 0; i < MT; ++i) an[i] = *(const bf16x8*)(A + i * ts + (int64_t)k0 * 512 + 8 * lane);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) bn[j] = *(const bf16x8*)(B + j * ts + (int64_t)k0 * 512 + 8 * lane);
+#pragma unroll 2
+  for (int k = k0; k < k1; ++k) {
+    bf16x8 a[MT], b[4];
+    const int64_t kn = (int64_t)min(k + 1, k1 - 1) * 512 + 8 * lane;
+#pragma unroll
+    for (int i = 0; i < MT; ++i) {
+      a[i] = an[i];
+      an[i] = *(const bf16x8*)(A + i * ts + kn);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      b[j] = bn[j];
+      bn[j] = *(const bf16x8*)(B + j * ts + kn);
+    }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+  }
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) C[(int64_t)(16 * i + 4 * (lane >> 4) + r) * ldc + 16 * j + (lane & 15)] = acc[i][j][r];
+}
+__global__ __launch_bounds__(256) void k_net_wgrad(NetWgrad P) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const int k0 = (int)blockIdx.y * P.per, k1 = min(P.nb, k0 + P.per);
+  float* part = P.part + (int64_t)blockIdx.y * NetGrads;
+  const int64_t ts = (int64_t)P.nb * 512;
+  const int b = blockIdx.x;
+  if (b < 16) {
+    const int mt = 2 * (b >> 2) + (w >> 1), nt = 2 * (b & 3) + (w & 1);   // 128 x 128 per workgroup
+    net_wgrad<4>(P.D2f + 4 * mt * ts, P.H1f + 4 * nt * ts, P.nb, k0, k1, part + (int64_t)64 * mt * NetW + 64 * nt, NetW,
+                 lane);
+  } else if (b < 18) {
+    const int mt = 4 * (b - 16) + w;
+    net_wgrad<4>(P.D1f + 4 * mt * ts, P.Xf, P.nb, k0, k1, part + NetW * NetW + (int64_t)64 * mt * NetIn, NetIn, lane);
+  } else {
+    const int nt = 4 * (b - 18) + w;
+    net_wgrad<1>(P.D3f, P.H2f + 4 * nt * ts, P.nb, k0, k1, part + NetW * NetW + NetW * NetIn + 64 * nt, NetW, lane);
+  }
+}
+
+struct NetOutGrads {
+  float *W1, *b1, *W2, *b2, *W3, *b3, *loss;
+};
+constexpr int NetGradBlocks = (NetGrads - 8 * NetW) / 1024;        // 1,024 weights per workgroup
+constexpr int NetBiasBlocks = (NetBias + 15) / 16;                 // 16 bias gradients per workgroup
+__global__ __launch_bounds__(256) void k_net_grads(const float* __restrict__ part, int splits,
+                                                   const float* __restrict__ bias, const float* __restrict__ loss,
+                                                   int nb, int n_loss, NetOutGrads O) {
+  const int tid = threadIdx.x;
+  if ((int)blockIdx.x < NetGradBlocks) {
+    const int i = (int)blockIdx.x * 1024 + 4 * tid;
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+    for (int z = 0; z < splits; ++z) {
+      const float4 p = *(const float4*)(part + (int64_t)z * NetGrads + i);
+      v.x += p.x, v.y += p.y, v.z += p.z, v.w += p.w;
+    }
+    float* dst = i < NetW * NetW ? O.W2 + i
+               : i < NetW * NetW + NetW * NetIn ? O.W1 + (i - NetW * NetW) : O.W3 + (i - NetW * NetW - NetW * NetIn);
+    *(float4*)dst = v;
+    return;
+  }
+  const int b = (int)blockIdx.x - NetGradBlocks;
+  if (b < NetBiasBlocks) {
+    // 16 gradients, 16 ranges of row blocks each, the ranges added in order
+    __shared__ float red[16][17];
+    const int f = 16 * b + (tid & 15), sg = tid >> 4, per = (nb + 15) / 16;
+    float v = 0.f;
+    if (f < NetBias)
+#pragma unroll 8
+      for (int k = sg * per; k < min(nb, (sg + 1) * per); ++k) v += bias[(int64_t)k * NetBias + f];
+    red[sg][tid & 15] = v;
+    __syncthreads();
+    if (tid < 16 && f < NetBias) {
+      v = 0.f;
+      for (int k = 0; k < 16; ++k) v += red[k][tid];
+      (f < NetW ? O.b1 + f : f < 2 * NetW ? O.b2 + (f - NetW) : O.b3 + (f - 2 * NetW))[0] = v;
+    }
+    return;
+  }
+  const int i = (b - NetBiasBlocks) * 256 + tid;   // losses per 256 rows
+  if (i < n_loss) {
+    float v = 0.f;
+    for (int k = 8 * i; k < min(nb, 8 * i + 8); ++k) v += loss[k];
+    O.loss[i] = v;
+  }
+}
+
 // Masked softmax cross-entropy per row: targets < 0 mark invalid actions.
 // loss_r = w_r * sum_a -t_a log p_a ; dlogits = w_r * (p - t) on valid actions.
 __global__ __launch_bounds__(256) void k_softmax_xent(int rows, int K, const float* __restrict__ z, int ldz,
@@ -439,9 +832,22 @@ __global__ __launch_bounds__(256) void k_colsum_reduce(int parts, int cols, cons
   db[n] = s;
 }
 
-__global__ void k_adam(int64_t n, float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                       float* __restrict__ v, uint16_t* __restrict__ wb, float lr, float b1, float b2,
-                       float eps, float wd, float c1, float c2) {
+// Adam over up to kAdamMax tensors in one launch (blockIdx.y: tensor).
+constexpr int kAdamMax = 8;
+struct AdamSet {
+  int64_t n[kAdamMax];
+  float *w[kAdamMax], *m[kAdamMax], *v[kAdamMax];
+  const float* g[kAdamMax];
+  uint16_t* wb[kAdamMax];
+};
+__global__ void k_adam(AdamSet S, float lr, float b1, float b2, float eps, float wd, float c1, float c2) {
+  const int t = blockIdx.y;
+  const int64_t n = S.n[t];
+  float* __restrict__ w = S.w[t];
+  const float* __restrict__ g = S.g[t];
+  float* __restrict__ m = S.m[t];
+  float* __restrict__ v = S.v[t];
+  uint16_t* __restrict__ wb = S.wb[t];
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const float gi = g[i] + wd * w[i];
@@ -572,6 +978,79 @@ int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const flo
   return PMX_OK;
 }
 
+// Scratch of mlp_loss_and_grad_bf16: W2 twice in fragment order, the row
+// fragments (M rounded up to 32 rows), split-K partial products, bias sums and
+// losses per 32 rows; every part on a 256-byte boundary.
+static int64_t net_train_layout(int64_t M, int64_t off[11]) {
+  const int64_t nb = (M + NetRows - 1) / NetRows;
+  const int64_t frag = nb * 512 * (int64_t)sizeof(uint16_t);   // one feature tile
+  const int64_t bytes[10] = {2 * NetW * NetW, 2 * NetW * NetW, frag * (NetIn / 16), frag * (NetW / 16),
+                             frag * (NetW / 16), frag * (NetW / 16), frag * (NetW / 16), frag,
+                             (int64_t)sizeof(float) * NetMaxSplit * NetGrads,
+                             (int64_t)sizeof(float) * nb * NetBias};
+  off[0] = 0;
+  for (int i = 0; i < 10; ++i) off[i + 1] = off[i] + (bytes[i] + 255) / 256 * 256;
+  return off[10] + (int64_t)sizeof(float) * nb;
+}
+
+int64_t mlp_loss_and_grad_work(int64_t M) {
+  int64_t off[11];
+  return M < 0 ? 0 : net_train_layout(M, off);
+}
+
+int mlp_loss_and_grad_bf16(int64_t M, const uint16_t* X, const float* target, const float* weight, const uint16_t* W1,
+                           const float* b1, const uint16_t* W2, const float* b2, const uint16_t* W3, const float* b3,
+                           float* loss, float* gW1, float* gb1, float* gW2, float* gb2, float* gW3, float* gb3,
+                           void* work, int64_t work_bytes, void* stream) {
+  if (M < 1 || M > ((int64_t)1 << 34) || !X || !target || !W1 || !b1 || !W2 || !b2 || !W3 || !b3 || !loss || !gW1 ||
+      !gb1 || !gW2 || !gb2 || !gW3 || !gb3 || !work)
+    return mfail(PMX_EINVAL, "bad network arguments");
+  const uintptr_t all = (uintptr_t)X | (uintptr_t)W1 | (uintptr_t)W2 | (uintptr_t)W3 | (uintptr_t)gW1 |
+                        (uintptr_t)gW2 | (uintptr_t)gW3 | (uintptr_t)work;
+  if (all % 16) return mfail(PMX_EINVAL, "network buffers must be 16-byte aligned");
+  int64_t off[11];
+  if (work_bytes < net_train_layout(M, off)) return mfail(PMX_EINVAL, "network workspace too small");
+  char* wk = (char*)work;
+  hipStream_t s = (hipStream_t)stream;
+  NetTrain P;
+  P.M = M;
+  P.nb = (M + NetRows - 1) / NetRows;
+  P.X = X;
+  P.T = target;
+  P.Wt = weight;
+  P.W1 = W1;
+  P.W3 = W3;
+  P.b1 = b1;
+  P.b2 = b2;
+  P.b3 = b3;
+  P.W2f = (uint16_t*)(wk + off[0]);
+  P.W2t = (uint16_t*)(wk + off[1]);
+  P.Xf = (uint16_t*)(wk + off[2]);
+  P.H1f = (uint16_t*)(wk + off[3]);
+  P.H2f = (uint16_t*)(wk + off[4]);
+  P.D1f = (uint16_t*)(wk + off[5]);
+  P.D2f = (uint16_t*)(wk + off[6]);
+  P.D3f = (uint16_t*)(wk + off[7]);
+  float* part = (float*)(wk + off[8]);
+  P.bias = (float*)(wk + off[9]);
+  P.loss = (float*)(wk + off[10]);
+  hipLaunchKernelGGL(k_net_pack2, dim3(NetW * NetW / 8 / 256, 2), dim3(256), 0, s, W2, (uint16_t*)P.W2f,
+                     (uint16_t*)P.W2t);
+  const size_t lds = sizeof(uint16_t) * NetRows * (2 * NetPitch + NetIn + 8 + 16) +
+                     sizeof(float) * NetRows * (2 * (NetOut + 1) + 1);
+  hipLaunchKernelGGL(k_net_rows, dim3((unsigned)P.nb), dim3(64 * NetWaves), lds, s, P);
+  // about eight row blocks per range, as many ranges as give the chip work
+  const int splits0 = (int)std::max<int64_t>(1, std::min<int64_t>(NetMaxSplit, P.nb / 8));
+  const int per = (int)((P.nb + splits0 - 1) / splits0), splits = (int)((P.nb + per - 1) / per);
+  const NetWgrad Q{P.Xf, P.H1f, P.H2f, P.D1f, P.D2f, P.D3f, part, (int)P.nb, per};
+  hipLaunchKernelGGL(k_net_wgrad, dim3(20, splits), dim3(256), 0, s, Q);
+  const int n_loss = (int)((M + 255) / 256);
+  hipLaunchKernelGGL(k_net_grads, dim3(NetGradBlocks + NetBiasBlocks + (n_loss + 255) / 256), dim3(256), 0, s, part,
+                     splits, P.bias, P.loss, (int)P.nb, n_loss, NetOutGrads{gW1, gb1, gW2, gb2, gW3, gb3, loss});
+  MLP_TRY(hipGetLastError());
+  return PMX_OK;
+}
+
 int mlp_softmax_xent(int32_t rows, int32_t K, const float* logits, int32_t ldl, const float* target,
                      const float* weight, float* dlogits, uint16_t* dlogits_bf16, float* loss_partial,
                      void* stream) {
@@ -598,15 +1077,34 @@ int mlp_colsum(int32_t rows, int32_t cols, const float* dz, float* db, float* wo
   return PMX_OK;
 }
 
-int mlp_adam(int64_t n, float* w, const float* g, float* m, float* v, uint16_t* w_bf16, float lr, float beta1,
-             float beta2, float eps, float weight_decay, int32_t step, void* stream) {
-  if (n < 0 || !w || !g || !m || !v || step < 1) return mfail(PMX_EINVAL, "bad Adam arguments");
-  if (n == 0) return PMX_OK;
+int mlp_adam_multi(int32_t n_tensors, const int64_t* n, float* const* w, const float* const* g, float* const* m,
+                   float* const* v, uint16_t* const* w_bf16, float lr, float beta1, float beta2, float eps,
+                   float weight_decay, int32_t step, void* stream) {
+  if (n_tensors < 0 || n_tensors > kAdamMax || (n_tensors > 0 && (!n || !w || !g || !m || !v)) || step < 1)
+    return mfail(PMX_EINVAL, "bad Adam arguments");
+  AdamSet S{};
+  int64_t most = 0;
+  for (int t = 0; t < n_tensors; ++t) {
+    if (n[t] < 0 || !w[t] || !g[t] || !m[t] || !v[t]) return mfail(PMX_EINVAL, "bad Adam arguments");
+    S.n[t] = n[t];
+    S.w[t] = w[t];
+    S.g[t] = g[t];
+    S.m[t] = m[t];
+    S.v[t] = v[t];
+    S.wb[t] = w_bf16 ? w_bf16[t] : nullptr;
+    most = std::max(most, n[t]);
+  }
+  if (most == 0) return PMX_OK;
   const float c1 = 1.f - std::pow(beta1, (float)step), c2 = 1.f - std::pow(beta2, (float)step);
-  hipLaunchKernelGGL(k_adam, dim3(grid_for(n)), dim3(256), 0, (hipStream_t)stream, n, w, g, m, v, w_bf16, lr,
-                     beta1, beta2, eps, weight_decay, c1, c2);
+  hipLaunchKernelGGL(k_adam, dim3(grid_for(most), n_tensors), dim3(256), 0, (hipStream_t)stream, S, lr, beta1, beta2,
+                     eps, weight_decay, c1, c2);
   MLP_TRY(hipGetLastError());
   return PMX_OK;
+}
+
+int mlp_adam(int64_t n, float* w, const float* g, float* m, float* v, uint16_t* w_bf16, float lr, float beta1,
+             float beta2, float eps, float weight_decay, int32_t step, void* stream) {
+  return mlp_adam_multi(1, &n, &w, &g, &m, &v, &w_bf16, lr, beta1, beta2, eps, weight_decay, step, stream);
 }
 
 int mlp_gather_bf16(int64_t n, int32_t width, const int64_t* idx, const uint16_t* src, uint16_t* dst,

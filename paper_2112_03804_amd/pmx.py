@@ -92,7 +92,8 @@ EXPORTS = [
     "get_average_strategy",
     "set_initial_strategy", "pmx_last_error", "game_tune", "game_get_tuning",
     "warm_num_rows", "warm_features", "warm_targets", "warm_apply",
-    "mlp_gemm_bf16", "mlp_forward_bf16", "mlp_softmax_xent", "mlp_colsum", "mlp_adam", "mlp_gather_bf16",
+    "mlp_gemm_bf16", "mlp_forward_bf16", "mlp_loss_and_grad_work",
+    "mlp_loss_and_grad_bf16", "mlp_adam_multi", "mlp_softmax_xent", "mlp_colsum", "mlp_adam", "mlp_gather_bf16",
     "mlp_gather_f32", "mlp_cast_bf16", "solver_set_active", "solver_set_params", "solver_set_task_rows", "solver_set_rm_quad",
     "solver_set_gap_guard", "tb_build", "tb_matrix", "matvec_A_tb", "matvec_AT_tb",
     "solver_snapshot", "solver_restore_instances",
@@ -154,6 +155,10 @@ def lib():
     L.mlp_gemm_bf16.argtypes = [i32, i32, i32, vp, i32, i32, vp, i32, i32, vp, i32, vp, i32, vp, i32,
                                 vp, i32, vp, i64, vp]
     L.mlp_forward_bf16.argtypes = [i64, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
+    L.mlp_loss_and_grad_work.argtypes = [i64]
+    L.mlp_loss_and_grad_work.restype = i64
+    L.mlp_loss_and_grad_bf16.argtypes = [i64] + [vp] * 17 + [i64, vp]
+    L.mlp_adam_multi.argtypes = [i32] + [vp] * 6 + [f32, f32, f32, f32, f32, i32, vp]
     L.mlp_softmax_xent.argtypes = [i32, i32, vp, i32, vp, vp, vp, vp, vp, vp]
     L.mlp_colsum.argtypes = [i32, i32, vp, vp, vp, i64, vp]
     L.mlp_adam.argtypes = [i64, vp, vp, vp, vp, vp, f32, f32, f32, f32, f32, i32, vp]

@@ -12,6 +12,7 @@ application); this module allocates device buffers and sequences the calls.
 """
 from __future__ import annotations
 
+import ctypes
 import time
 from typing import List, Sequence
 
@@ -56,7 +57,7 @@ class WarmMLP:
                                                   pmx.dptr(self.pb[name]), pmx.stream_ptr()))
         self.step = 0
         self._ws = {}
-        self._ws_net = {}   # scratch of logits()
+        self._ws_net = {}   # scratch of logits() and loss_and_grad()
 
     # -- buffers ------------------------------------------------------------
     def _work(self, M: int):
@@ -107,8 +108,20 @@ class WarmMLP:
 
     def loss_and_grad(self, Xb, T, Wt, M: int):
         """Weighted masked cross-entropy of a batch and the parameter gradients
-        (left in self.g); returns the loss summed over rows."""
+        (left in self.g); returns the loss summed over rows.  Rows not
+        aligned to 16 bytes, and an empty batch, go layer by layer."""
         L = pmx.lib()
+        if M > 0 and Xb.data_ptr() % 16 == 0:
+            torch, ws, d = _torch(), self._ws_net, pmx.dptr
+            if ws.get("M", 0) < M:
+                need = L.mlp_loss_and_grad_work(M)
+                ws.update(M=M, train=torch.empty((need,), dtype=torch.uint8, device="cuda"),
+                          loss=torch.empty(((M + 255) // 256,), dtype=torch.float32, device="cuda"))
+            p, pb, g = self.p, self.pb, self.g
+            pmx.check(L.mlp_loss_and_grad_bf16(
+                M, d(Xb), d(T), d(Wt), d(pb["W1"]), d(p["b1"]), d(pb["W2"]), d(p["b2"]), d(pb["W3"]), d(p["b3"]),
+                d(ws["loss"]), *(d(g[k]) for k in PARAMS), d(ws["train"]), ws["train"].numel(), pmx.stream_ptr()))
+            return ws["loss"][: (M + 255) // 256]
         w = self._work(M)
         self.forward(Xb, M)
         pmx.check(L.mlp_softmax_xent(M, K, pmx.dptr(w["Z3"]), K, pmx.dptr(T), pmx.dptr(Wt),
@@ -132,11 +145,12 @@ class WarmMLP:
 
     def adam(self, lr=1e-3, b1=0.9, b2=0.999, eps=1e-8, wd=0.0):
         self.step += 1
-        L = pmx.lib()
-        for name in PARAMS:
-            pmx.check(L.mlp_adam(self.p[name].numel(), pmx.dptr(self.p[name]), pmx.dptr(self.g[name]),
-                                 pmx.dptr(self.m[name]), pmx.dptr(self.v[name]), pmx.dptr(self.pb.get(name)),
-                                 lr, b1, b2, eps, wd, self.step, pmx.stream_ptr()))
+        n = len(PARAMS)
+        sizes = (ctypes.c_int64 * n)(*(self.p[k].numel() for k in PARAMS))
+        w, g, m, v, wb = ((ctypes.c_void_p * n)(*(None if k not in t else t[k].data_ptr() for k in PARAMS))
+                          for t in (self.p, self.g, self.m, self.v, self.pb))
+        pmx.check(pmx.lib().mlp_adam_multi(n, sizes, w, g, m, v, wb, lr, b1, b2, eps, wd, self.step,
+                                           pmx.stream_ptr()))
 
     def logits(self, Xb, M: int, chunk: int = 1 << 20):
         """Logits for M rows (inference): one kernel for the whole network,

@@ -211,3 +211,47 @@ def test_averages_do_not_depend_on_the_split(name, fn, rule):
                 assert np.array_equal(st[p][k], states[0][p][k]), (p, k)
             assert (st[p]["t"], st[p]["wsum"]) == (states[0][p]["t"], states[0][p]["wsum"])
         assert np.array_equal(st[2], states[0][2])
+
+
+# a training step's kernels against the layer-by-layer path: remainders of the
+# 32-row blocks and the 256-row losses, one split and many, with and without
+# weights
+@pytest.mark.parametrize("rows", [1, 31, 32, 33, 255, 257, 1000, 4097, 8192])
+def test_training_gradients(rows):
+    _game(I.tiny_config()).close()
+    from paper_2112_03804_amd import warmstart
+    gen = torch.Generator(device="cuda").manual_seed(rows)
+    net = warmstart.WarmMLP(seed=rows)
+    for k in ("b1", "b2", "b3"):
+        net.p[k].copy_(0.2 * torch.randn(net.p[k].shape, generator=gen, device="cuda"))
+    # one spare element in front: the copy at an odd offset goes layer by layer
+    buf = torch.randn((rows * warmstart.D_IN + 8,), generator=gen, device="cuda").to(torch.bfloat16)
+    X = buf[:rows * warmstart.D_IN].view(rows, -1)
+    shifted = torch.empty_like(buf)
+    Xs = shifted[1:1 + rows * warmstart.D_IN].view(rows, -1)
+    Xs.copy_(X)
+    T = torch.rand((rows, warmstart.K), generator=gen, device="cuda")
+    valid = torch.arange(warmstart.K, device="cuda")[None, :] < torch.randint(1, 9, (rows, 1), generator=gen, device="cuda")
+    T = torch.where(valid, T / (T * valid).sum(dim=1, keepdim=True), torch.full_like(T, -1.0)).contiguous()
+    W = torch.rand((rows,), generator=gen, device="cuda") if rows % 2 else None
+    ref_loss = net.loss_and_grad(Xs, T, W, rows).clone()
+    ref = {k: v.clone() for k, v in net.g.items()}
+    ws = net._ws
+    mag = {"W3": (ws["dZ3b"], ws["H2b"]), "W2": (ws["dZ2b"], ws["H1b"]), "W1": (ws["dZ1b"], X)}
+    cols = {"b3": ws["dZ3"], "b2": ws["dZ2"], "b1": ws["dZ1"]}
+    for v in net.g.values():
+        v.fill_(7.0)
+    loss = net.loss_and_grad(X, T, W, rows)
+    assert loss.shape == ref_loss.shape
+    assert ((loss - ref_loss).abs() <= 1e-4 * ref_loss.abs()).all()
+    # the same values are rounded to BF16 on both paths after FP32 sums in
+    # another order: a value may round the other way (2^-8 of it) at each of
+    # the layers before it, which bounds every term of a gradient
+    for k, (d, h) in mag.items():
+        lim = d[:rows].float().abs().t().contiguous() @ h[:rows].float().abs()
+        assert ((net.g[k] - ref[k]).abs() <= 4 * 2.0 ** -8 * lim + 1e-30).all(), k
+    for k, d in cols.items():
+        assert ((net.g[k] - ref[k]).abs() <= 4 * 2.0 ** -8 * d[:rows].abs().sum(dim=0) + 1e-30).all(), k
+    # and few do: the gradients agree far closer as a whole
+    for k in ref:
+        assert (net.g[k] - ref[k]).norm() <= 2e-3 * ref[k].norm(), k
