@@ -2309,6 +2309,7 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
   int n_cut[kGrpClasses] = {}, n_cut_act[kGrpClasses] = {};
   DBuf<GRed> red;
   int n_red = 0, red_blocks = 0;
+  double cut_us = 0;            // estimated time of the longest sequence when it is carried
   DBuf<double> part[2];
   // FP64 products: row chunks (DevDir::items) per class
   std::vector<int32_t> f64_h[kGrpClasses];
@@ -2558,13 +2559,17 @@ static int upload_grp_active(Game* g, int d) {
   return PMX_OK;
 }
 
-// Groups a sequence must have before its product cuts it.  A sequence's
-// groups otherwise run one after another in one workgroup, about 9 us each
-// at 1,128 hands: the turn + river game's 8 sequences of 49 groups took
-// 431 us of a 450 us product whose other 7,000 groups took 160 us.  Cut, they
-// are 392 workgroups beside the others and a sum of 7 us: 145 us per product.
-// Below some eight groups the fork, the join and the sum cost what they save.
-static constexpr int kCutMinGroups = 8;
+// A sequence's groups run one after another in one workgroup, about 0.45 us
+// per scan entry of a thread (8.6 us a group at 1,128 hands): the turn + river
+// game's 8 sequences of 49 groups took 431 us of a 450 us product whose other
+// 7,000 groups took 160 us.  Cut, they are 392 workgroups beside the others and
+// a sum of 7 us: 145 us per product.  The sum is one more launch, and in a
+// product of the caller's the fork to the side stream that orders the term
+// buffer costs some 20 us (a turn game of 8 river cards and 28 hands, 9 groups
+// of 2 us: 99 us an iteration carried, 115 cut with forks, 82 cut without), so
+// a product cuts when its longest sequence takes more than that.
+static constexpr double kCutGroupUs = 0.45;      // per scan entry of a thread and group
+static constexpr double kCutSolverUs = 10.0, kCutForkUs = 30.0;
 
 // Cuts the carrying sequences (kind 1) of a direction into their groups when
 // one of them is long: every group becomes a chunk of its own that writes its
@@ -2577,7 +2582,8 @@ static int cut_sequences(Game* g, int d, std::vector<GGroup>& groups) {
   const GrpDir& M = g->hg.grp[d];
   std::vector<GRed> red;
   std::vector<std::array<std::array<int, 2>, kGrpComps>> term;   // (row in red, term of the row) per output of a cut group
-  int longest = 0, max_stride = 0;
+  int max_stride = 0;
+  double longest = 0;                         // microseconds of the longest sequence
   const size_t n_uncut = groups.size();
   for (int c = 0; c < kGrpClasses; ++c) {
     E.cut_h[c].clear();
@@ -2611,7 +2617,7 @@ static int cut_sequences(Game* g, int d, std::vector<GGroup>& groups) {
           tm[o] = {at[o], red[at[o]].n++};
           any = true;
         }
-        longest = std::max(longest, len + 1);
+        longest = std::max(longest, (len + 1) * kGrpKE[c] * kCutGroupUs);
         if (!any) continue;
         E.cut_h[c].insert(E.cut_h[c].end(), {(int32_t)groups.size(), (int32_t)groups.size() + 1, F[i + 2], G.ctx});
         groups.push_back(G);
@@ -2622,7 +2628,8 @@ static int cut_sequences(Game* g, int d, std::vector<GGroup>& groups) {
   int64_t elems = 0;
   for (const GRed& r : red) elems += (int64_t)r.n * r.stride;
   E.n_red = 0;
-  if (longest < kCutMinGroups || elems >= ((int64_t)1 << 31)) {
+  E.cut_us = longest;
+  if (longest < kCutSolverUs || elems >= ((int64_t)1 << 31)) {
     for (auto& v : E.cut_h) v.clear();
     groups.resize(n_uncut);
     return PMX_OK;
@@ -3004,13 +3011,15 @@ static void launch_mc_class(const McParams& A, const IO* in0, IO* out0, const Mc
 // Under stream capture the fork and join become graph edges.  A class's
 // tail then overlaps the others' work, and workgroups of different classes
 // share a CU's LDS.  `launch(i, stream, first)` enqueues launch i; `first`
-// marks the one launch that carries the iteration tick.  `pinned` launches
-// (the first n_pinned) go to side stream 0 whatever the load, in order: work
-// on buffers of the game's own that successive products share is so ordered,
-// whatever streams those products are called on.
+// marks the one launch that carries the iteration tick.  The first n_pinned
+// launches stay in order on one stream, a side stream if the product is
+// spread at all.  pin_side: they always go to side stream 0, which orders
+// work on buffers of the game's own that successive products share, whatever
+// streams those products are called on.
 template <typename F>
 static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, int64_t workgroups, F&& launch,
-                         int n_pinned = 0) {
+                         int n_pinned = 0, bool pin_side = false) {
+  pin_side = pin_side && n_pinned > 0;
   std::lock_guard<std::mutex> lock(g->fork_mu);
   int order[32];
   int64_t work[32];
@@ -3026,16 +3035,16 @@ static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, 
     }
   // a fork and join cost about ten microseconds: small products (a single
   // river endgame's) stay on the caller's stream
-  if (n_pinned && !g->fork_ok) return fail(PMX_ESTATE, "no side streams");
-  const int ns = (g->fork_ok && workgroups >= kForkMinWorkgroups) ? std::max(std::min(n, kForkStreams), n_pinned ? 2 : 1)
-               : n_pinned ? 2 : 1;
+  if (pin_side && !g->fork_ok) return fail(PMX_ESTATE, "no side streams");
+  const int ns = (g->fork_ok && workgroups >= kForkMinWorkgroups) ? std::max(std::min(n, kForkStreams), pin_side ? 2 : 1)
+               : pin_side ? 2 : 1;
   int on[32];
   int64_t load[kForkStreams] = {};
   for (int i = 0; i < n; ++i) {
     int best = 0;
     for (int k = 1; k < ns; ++k)
       if (load[k] < load[best]) best = k;
-    if (i < n_pinned) best = 1;
+    if (i < n_pinned) best = ns > 1 ? 1 : 0;
     on[i] = best;
     load[best] += work[i];
   }
@@ -3166,7 +3175,8 @@ static int launch_grp(Game* g, const MvParams& P0, const float* in0, float* out0
   if (!g->dg[0].built || !g->dg[1].built) return fail(PMX_ESTATE, "grouped matvec layout not built");
   // long carrying sequences are cut, except in a product the caller captures
   const int nr0 = P0.nblk > 0 ? g->dg[P0.dir].n_red : 0, nr1 = P1.nblk > 0 ? g->dg[P1.dir].n_red : 0;
-  bool cut = nr0 + nr1 > 0;
+  const double cut_us = std::max(nr0 ? g->dg[P0.dir].cut_us : 0.0, nr1 ? g->dg[P1.dir].cut_us : 0.0);
+  bool cut = nr0 + nr1 > 0 && (P0.active || cut_us >= kCutForkUs);
   if (cut && !P0.active) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(s, &st));
@@ -3237,7 +3247,7 @@ static int launch_grp(Game* g, const MvParams& P0, const float* in0, float* out0
       }
     }
     return PMX_OK;
-  }, n_pinned);
+  }, n_pinned, P0.active == nullptr);
   if (rc) return rc;
   // every instance retired from the lists: the iteration still counts
   if (n == 0 && tick) hipLaunchKernelGGL(k_add1, dim3(1), dim3(1), 0, s, tick);

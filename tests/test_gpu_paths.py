@@ -25,12 +25,12 @@ def _vectors(g, seed, dtype):
     return per, [torch.from_numpy(g.pack(p, per[p], dtype=dtype)).cuda() for p in range(2)]
 
 
-# rows over many board contexts: a small turn game's sequences stay carried
-# (fewer than eight groups), longer ones are cut; a captured product carries
+# rows over many board contexts: short sequences stay carried, those of many
+# or large groups are cut; a captured product carries
 CUT_CASES = [
     ("carried", lambda: I.small_turn_river(1, deck_size=9, n_board=3, cards_per_hand=2, bet_fracs=(0.5,),
                                            max_raises=0, stack=8.0)),
-    ("cut_at_8", lambda: I.small_turn_river(2, deck_size=9, n_board=2, bet_fracs=(0.5, 1.0))),
+    ("carried_8", lambda: I.small_turn_river(2, deck_size=9, n_board=2, bet_fracs=(0.5, 1.0))),
     ("cut_20", lambda: I.small_turn_river(3, deck_size=23, n_board=3, cards_per_hand=2, bet_fracs=(0.5,),
                                           max_raises=1, stack=12.0, zero_frac=0.2)),
     ("cut_two_classes", lambda: [I.small_turn_river(4, deck_size=14, n_board=3, cards_per_hand=2, stack=9.0),
