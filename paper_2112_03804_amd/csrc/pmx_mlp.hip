@@ -26,12 +26,8 @@ static int mfail(int code, const char* m) {
     if (e_ != hipSuccess) return mfail(PMX_EDEVICE, hipGetErrorString(e_)); \
   } while (0)
 
-__device__ inline uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x7fffffu)) return (uint16_t)((u >> 16) | 0x40);
-  u += 0x7fffu + ((u >> 16) & 1u);   // round to nearest even
-  return (uint16_t)(u >> 16);
-}
+// Round to nearest even (one conversion instruction on gfx950; a NaN stays one).
+__device__ inline uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
 __device__ inline float bf2f(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ---------------------------------------------------------------------------
@@ -393,6 +389,9 @@ void k_net(NetArgs P, const uint16_t* __restrict__ W2p) {
 // Layer by layer through HBM it was 16 launches, 300 us at 8,192 rows, of
 // which column sums took 113 us (one thread per column adding 128 partials)
 // and the GEMMs, at 64 x 64 tiles with 2-byte transposes through LDS, 160 us.
+// Now 52 us with Adam's: k_net_rows 27 (every CU reads the second layer's
+// weights twice, 512 KB in 6.3 us each time), k_net_wgrad 18 (its fragments'
+// loads, 512 KB per workgroup), k_net_grads 5, Adam 4, packing 2.4.
 // ---------------------------------------------------------------------------
 constexpr int NetRows = 32;                      // rows per workgroup of k_net_rows
 constexpr int NetBias = 2 * NetW + NetOut;       // bias gradients: b1, b2, b3
@@ -468,7 +467,8 @@ __global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2
   uint16_t* H1 = (uint16_t*)net_smem;            // [R][NetPitch]
   uint16_t* H2 = H1 + R * NetPitch;              // [R][NetPitch], later the second layer's gradient
   uint16_t* Xs = H2 + R * NetPitch;              // [R][XP]
-  uint16_t* Ds = Xs + R * XP;                    // [R][16] output gradients, BF16 (8 unused)
+  uint16_t* W3 = Xs + R * XP;                    // [NetOut][NetPitch]
+  uint16_t* Ds = W3 + NetOut * NetPitch;         // [R][16] output gradients, BF16 (8 unused)
   float* zs = (float*)(Ds + R * 16);             // [R][NetOut + 1] logits
   float* dz = zs + R * (NetOut + 1);             // [R][NetOut + 1] output gradients
   float* ls = dz + R * (NetOut + 1);             // [R] losses
@@ -480,6 +480,8 @@ __global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2
     const int r = tid / (NetIn / 8), k = 8 * (tid % (NetIn / 8));
     *(uint4*)&Xs[r * XP + k] = *(const uint4*)(P.X + min(r0 + r, P.M - 1) * NetIn + k);
   }
+  *(uint4*)&W3[(tid / 64) * NetPitch + 8 * (tid % 64)] = *(const uint4*)(P.W3 + 8 * tid);
+  static_assert(NetOut * NetW == 8 * 64 * NetWaves, "one 16-byte piece of W3 per thread");
   bf16x8 w1[2][4];
   float b1[4], b2[4];
 #pragma unroll
@@ -547,7 +549,7 @@ __global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2
 #pragma unroll 4
     for (int ks = 0; ks < NetW / 32; ++ks) {
       const int k = 32 * ks + 8 * lq;
-      const bf16x8 b = *(const bf16x8*)(P.W3 + (int64_t)(l16 & (NetOut - 1)) * NetW + k);   // outputs 8 to 15 unused
+      const bf16x8 b = *(const bf16x8*)&W3[(l16 & (NetOut - 1)) * NetPitch + k];   // outputs 8 to 15 unused
       z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const bf16x8*)&H2[(16 * w + l16) * NetPitch + k], b, z, 0, 0, 0);
     }
     if (l16 < NetOut)
@@ -636,7 +638,7 @@ __global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2
     s16x8 b = {0, 0, 0, 0, 0, 0, 0, 0};
     if (lq == 0)
 #pragma unroll
-      for (int k = 0; k < NetOut; ++k) b[k] = (short)P.W3[(int64_t)k * NetW + f0 + 16 * i + l16];
+      for (int k = 0; k < NetOut; ++k) b[k] = (short)W3[k * NetPitch + f0 + 16 * i + l16];
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
       s16x8 a = {0, 0, 0, 0, 0, 0, 0, 0};
@@ -658,8 +660,9 @@ __global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2
 struct NetWgrad {
   const uint16_t *Xf, *H1f, *H2f, *D1f, *D2f, *D3f;
   float* part;                                   // [splits][NetGrads]
-  int nb, per;                                   // row blocks; per split
+  int nb, per, splits;                           // row blocks; per split
 };
+constexpr int NetWgradTiles = 20;                // workgroups per split
 template <int MT>
 __device__ inline void net_wgrad(const uint16_t* __restrict__ A, const uint16_t* __restrict__ B, int nb, int k0, int k1,
                                  float* __restrict__ C, int ldc, int lane) {
@@ -668,30 +671,40 @@ __device__ inline void net_wgrad(const uint16_t* __restrict__ A, const uint16_t*
   for (int i = 0; i < MT; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  bf16x8 an[MT], bn[4];
+  // PF row blocks of fragments in flight
+  constexpr int PF = 4;
+  bf16x8 an[PF][MT], bn[PF][4];
   const int64_t ts = (int64_t)nb * 512;          // next feature tile
 #pragma unroll
-  for (int i = 0; i < MT; ++i) an[i] = *(const bf16x8*)(A + i * ts + (int64_t)k0 * 512 + 8 * lane);
+  for (int d = 0; d < PF; ++d) {
+    const int64_t kd = (int64_t)min(k0 + d, k1 - 1) * 512 + 8 * lane;
 #pragma unroll
-  for (int j = 0; j < 4; ++j) bn[j] = *(const bf16x8*)(B + j * ts + (int64_t)k0 * 512 + 8 * lane);
-#pragma unroll 2
-  for (int k = k0; k < k1; ++k) {
-    bf16x8 a[MT], b[4];
-    const int64_t kn = (int64_t)min(k + 1, k1 - 1) * 512 + 8 * lane;
+    for (int i = 0; i < MT; ++i) an[d][i] = *(const bf16x8*)(A + i * ts + kd);
 #pragma unroll
-    for (int i = 0; i < MT; ++i) {
-      a[i] = an[i];
-      an[i] = *(const bf16x8*)(A + i * ts + kn);
+    for (int j = 0; j < 4; ++j) bn[d][j] = *(const bf16x8*)(B + j * ts + kd);
+  }
+#pragma unroll 1
+  for (int kb = k0; kb < k1; kb += PF) {
+#pragma unroll
+    for (int d = 0; d < PF; ++d) {
+      if (kb + d >= k1) break;
+      bf16x8 a[MT], b[4];
+      const int64_t kn = (int64_t)min(kb + d + PF, k1 - 1) * 512 + 8 * lane;
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        a[i] = an[d][i];
+        an[d][i] = *(const bf16x8*)(A + i * ts + kn);
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        b[j] = bn[d][j];
+        bn[d][j] = *(const bf16x8*)(B + j * ts + kn);
+      }
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      b[j] = bn[j];
-      bn[j] = *(const bf16x8*)(B + j * ts + kn);
-    }
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
   }
 #pragma unroll
   for (int i = 0; i < MT; ++i)
@@ -702,10 +715,14 @@ __device__ inline void net_wgrad(const uint16_t* __restrict__ A, const uint16_t*
 }
 __global__ __launch_bounds__(256) void k_net_wgrad(NetWgrad P) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int k0 = (int)blockIdx.y * P.per, k1 = min(P.nb, k0 + P.per);
-  float* part = P.part + (int64_t)blockIdx.y * NetGrads;
+  // workgroups go to the eight XCDs in turn: the tiles of one split, which
+  // read the same rows, share an XCD and its L2
+  const int q = (int)blockIdx.x >> 3, split = ((int)blockIdx.x & 7) + 8 * (q / NetWgradTiles);
+  if (split >= P.splits) return;
+  const int k0 = split * P.per, k1 = min(P.nb, k0 + P.per);
+  float* part = P.part + (int64_t)split * NetGrads;
   const int64_t ts = (int64_t)P.nb * 512;
-  const int b = blockIdx.x;
+  const int b = q % NetWgradTiles;
   if (b < 16) {
     const int mt = 2 * (b >> 2) + (w >> 1), nt = 2 * (b & 3) + (w & 1);   // 128 x 128 per workgroup
     net_wgrad<4>(P.D2f + 4 * mt * ts, P.H1f + 4 * nt * ts, P.nb, k0, k1, part + (int64_t)64 * mt * NetW + 64 * nt, NetW,
@@ -1036,14 +1053,14 @@ int mlp_loss_and_grad_bf16(int64_t M, const uint16_t* X, const float* target, co
   P.loss = (float*)(wk + off[10]);
   hipLaunchKernelGGL(k_net_pack2, dim3(NetW * NetW / 8 / 256, 2), dim3(256), 0, s, W2, (uint16_t*)P.W2f,
                      (uint16_t*)P.W2t);
-  const size_t lds = sizeof(uint16_t) * NetRows * (2 * NetPitch + NetIn + 8 + 16) +
+  const size_t lds = sizeof(uint16_t) * (NetRows * (2 * NetPitch + NetIn + 8 + 16) + NetOut * NetPitch) +
                      sizeof(float) * NetRows * (2 * (NetOut + 1) + 1);
   hipLaunchKernelGGL(k_net_rows, dim3((unsigned)P.nb), dim3(64 * NetWaves), lds, s, P);
   // about eight row blocks per range, as many ranges as give the chip work
   const int splits0 = (int)std::max<int64_t>(1, std::min<int64_t>(NetMaxSplit, P.nb / 8));
   const int per = (int)((P.nb + splits0 - 1) / splits0), splits = (int)((P.nb + per - 1) / per);
-  const NetWgrad Q{P.Xf, P.H1f, P.H2f, P.D1f, P.D2f, P.D3f, part, (int)P.nb, per};
-  hipLaunchKernelGGL(k_net_wgrad, dim3(20, splits), dim3(256), 0, s, Q);
+  const NetWgrad Q{P.Xf, P.H1f, P.H2f, P.D1f, P.D2f, P.D3f, part, (int)P.nb, per, splits};
+  hipLaunchKernelGGL(k_net_wgrad, dim3(8 * ((splits + 7) / 8) * NetWgradTiles), dim3(256), 0, s, Q);
   const int n_loss = (int)((M + 255) / 256);
   hipLaunchKernelGGL(k_net_grads, dim3(NetGradBlocks + NetBiasBlocks + (n_loss + 255) / 256), dim3(256), 0, s, part,
                      splits, P.bias, P.loss, (int)P.nb, n_loss, NetOutGrads{gW1, gb1, gW2, gb2, gW3, gb3, loss});
