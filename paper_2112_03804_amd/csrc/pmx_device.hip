@@ -499,10 +499,10 @@ struct GParams {
   int32_t nchunk;
 };
 
-// One step of an inclusive segmented scan of (flag, a[0..3]): the values of
-// the earlier lane are added unless this lane's run already holds a flag.
-// With every row enabled, a lane without a source reads 0 through the DPP
-// bound control, and no old value has to be set first.
+// One step of an inclusive segmented scan of a[0..NC): the values of the
+// earlier lane are added where `open`'s bit is set, i.e. where this lane's run
+// reaches back to it.  With every row enabled, a lane without a source reads 0
+// through the DPP bound control, and no old value has to be set first.
 template <int CTRL>
 __device__ inline int dpp_iz(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xf, 0xf, true);
@@ -512,57 +512,70 @@ __device__ inline double dpp_dz(double v) {
   return __hiloint2double(dpp_iz<CTRL>(__double2hiint(v)), dpp_iz<CTRL>(__double2loint(v)));
 }
 template <int CTRL, int RM, int NC>
-__device__ inline void seg_step4(int& f, double (&a)[NC]) {
-  const int f2 = RM == 0xf ? dpp_iz<CTRL>(f) : dpp_i<CTRL, RM>(f);
-  const double m = f ? 0.0 : 1.0;
+__device__ inline void seg_add(uint64_t open, double (&a)[NC]) {
+  const double m = __builtin_amdgcn_inverse_ballot_w64(open) ? 1.0 : 0.0;
 #pragma unroll
   for (int j = 0; j < NC; ++j) a[j] = fma(RM == 0xf ? dpp_dz<CTRL>(a[j]) : dpp_d<CTRL, RM>(a[j]), m, a[j]);
-  f |= f2;
 }
 
-// Exclusive segmented scan of NC values over the threads of a block (as
-// block_seg_scan_x): the exclusive sum is the inclusive one minus the own
-// value.  One barrier; `scr` holds 5 doubles per wavefront.
+// Exclusive segmented scan of NC values over the threads of a block of four
+// wavefronts (as block_seg_scan_x): the exclusive sum is the inclusive one
+// minus the own value.  One barrier; `scr` holds 5 doubles per wavefront.
+// The run flags are the layout's, so they live in scalar masks; a wavefront
+// whose runs within it have at most four lanes (the card segments: all
+// wavefronts but the global segment's) leaves out the steps over four and
+// eight lanes, which would add nothing; and the carry into a wavefront is one of four sums of the
+// wavefronts before it, chosen by scalar flags.  Sums and their order are
+// those of the six-step scan over lanes and the three-step scan over
+// wavefronts.
 template <int NW, int NC>
-__device__ inline void block_seg_scan4(int flag, const double (&a)[NC], double* scr, double (&e)[NC]) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  int f = flag;
+__device__ inline void block_seg_scan4(int flag, int n_chunk, const double (&a)[NC], double* scr, double (&e)[NC]) {
+  static_assert(NW == 4, "the carries are written out for four wavefronts");
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint64_t fm = __builtin_amdgcn_ballot_w64(flag != 0);
+  const int lim = n_chunk - 64 * wid;            // lanes past the last chunk belong to no run
+  uint64_t near = fm | 1 | (lim <= 0 ? ~0ull : lim >= 64 ? 0ull : ~0ull << lim);
+  near |= near << 1;
+  near |= near << 2;                             // lanes at most three past a run's start
   double ai[NC];
 #pragma unroll
   for (int j = 0; j < NC; ++j) ai[j] = a[j];
-  seg_step4<0x111, 0xf, NC>(f, ai);
-  seg_step4<0x112, 0xf, NC>(f, ai);
-  seg_step4<0x114, 0xf, NC>(f, ai);
-  seg_step4<0x118, 0xf, NC>(f, ai);
-  seg_step4<0x142, 0xa, NC>(f, ai);
-  seg_step4<0x143, 0xc, NC>(f, ai);
+  // f: lanes with a run start among themselves and the lanes already added
+  uint64_t f = fm;
+  seg_add<0x111, 0xf, NC>(~f, ai);
+  f |= (f << 1) & 0xfffefffefffefffeull;         // shifts stay within a row of 16
+  seg_add<0x112, 0xf, NC>(~f, ai);
+  f |= (f << 2) & 0xfffcfffcfffcfffcull;
+  if (near != ~0ull) seg_add<0x114, 0xf, NC>(~f, ai);
+  f |= (f << 4) & 0xfff0fff0fff0fff0ull;
+  if (near != ~0ull) seg_add<0x118, 0xf, NC>(~f, ai);
+  f |= (f << 8) & 0xff00ff00ff00ff00ull;
+  seg_add<0x142, 0xa, NC>(~f, ai);               // lane 15 of rows 0 and 2 to the next row
+  f |= ((f >> 15) & 1 ? 0x00000000ffff0000ull : 0) | ((f >> 47) & 1 ? 0xffff000000000000ull : 0);
+  seg_add<0x143, 0xc, NC>(~f, ai);               // lane 31 to rows 2 and 3
   if (lane == 63) {
-    scr[5 * wid] = (double)f;
+    scr[5 * wid] = fm != 0 ? 1.0 : 0.0;
 #pragma unroll
     for (int j = 0; j < NC; ++j) scr[5 * wid + 1 + j] = ai[j];
   }
   __syncthreads();
-  static_assert(NW <= 8, "wavefront totals are scanned within one DPP row");
-  int fw = 0;
-  double aw[NC];
+  double c[NC];
 #pragma unroll
-  for (int j = 0; j < NC; ++j) aw[j] = 0.0;
-  if (lane < NW) {
-    fw = scr[5 * lane] != 0.0;
+  for (int j = 0; j < NC; ++j) c[j] = 0.0;
+  if (wid > 0) {
 #pragma unroll
-    for (int j = 0; j < NC; ++j) aw[j] = scr[5 * lane + 1 + j];
+    for (int j = 0; j < NC; ++j) c[j] = scr[5 * (wid - 1) + 1 + j];
+    for (int w = wid - 1; w > 0; --w) {
+      if (__builtin_amdgcn_readfirstlane((int)scr[5 * w])) break;
+#pragma unroll
+      for (int j = 0; j < NC; ++j) c[j] += scr[5 * (w - 1) + 1 + j];
+    }
   }
-  seg_step4<0x111, 0xf, NC>(fw, aw);
-  seg_step4<0x112, 0xf, NC>(fw, aw);
-  seg_step4<0x114, 0xf, NC>(fw, aw);
-  const double m = (wid > 0 && !f) ? 1.0 : 0.0;
-  const int src = wid > 0 ? wid - 1 : 0;
+  // lanes before the wavefront's first run start continue the run before it
+  const uint64_t before = wid == 0 ? 0ull : fm ? (fm & (0 - fm)) - 1 : ~0ull;
+  const double m = __builtin_amdgcn_inverse_ballot_w64(before) ? 1.0 : 0.0;
 #pragma unroll
-  for (int j = 0; j < NC; ++j) {
-    const double c = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(aw[j]), src),
-                                      __builtin_amdgcn_readlane(__double2loint(aw[j]), src));
-    e[j] = fma(c, m, ai[j]) - a[j];
-  }
+  for (int j = 0; j < NC; ++j) e[j] = fma(c[j], m, ai[j]) - a[j];
 }
 
 // Records every lane reads at the same address (chunks, groups, contexts) are
@@ -885,7 +898,7 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       double a[NC], e[NC];
 #pragma unroll
       for (int j = 0; j < NC; ++j) a[j] = (double)s4[j];
-      block_seg_scan4<NW, NC>((int)((cm >> 8) & 1u), a, scr, e);
+      block_seg_scan4<NW, NC>((int)((cm >> 8) & 1u), n_chunk, a, scr, e);
       // every gather is done (the scan's barrier): the exclusive prefix sums
       // of the slotted components overwrite the staging rows (or fill their
       // own region), each the FP64 carry's FP32 head plus (remainder +
@@ -920,36 +933,33 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
 #pragma unroll
       for (int k = 0; k < KH; ++k) {
         const int h = tid + k * BLK;
-        // outputs: four in every kind; components: NC, NS of them with
+        // outputs: up to four in every kind; components: NC, NS of them with
         // prefix slots (with two, the outputs name their showdown component
         // as they name their fold component)
-        double val[kGrpComps];
+        double sd[NS], fo[NC];
 #pragma unroll
-        for (int o = 0; o < kGrpComps; ++o) val[o] = 0.0;
-        if (h < n_own && qr[k].x != 0xffffffffu) {
-          double sd[NS], fo[NC];
-          grp_query<KE, NC, NS>(R, St, segT, qr[k], cph, sd, fo);
+        for (int j = 0; j < NS; ++j) sd[j] = 0.0;
 #pragma unroll
-          for (int o = 0; o < kGrpComps; ++o) {
-            const int fj = (G.fc >> (2 * o)) & 3;
-            double f = fo[0];
-#pragma unroll
-            for (int c = 1; c < NC; ++c) f = fj == c ? fo[c] : f;
-            const double sv = NS == 2 ? (((G.sc >> (2 * o)) & 3) == 1 ? sd[1] : sd[0]) : sd[o % NS];
-            val[o] = G.ks[o] * sv + G.kf[o] * f;
-          }
-        }
+        for (int j = 0; j < NC; ++j) fo[j] = 0.0;
+        if (h < n_own && qr[k].x != 0xffffffffu) grp_query<KE, NC, NS>(R, St, segT, qr[k], cph, sd, fo);
         const double sl = P.scale * (double)low[k];
 #pragma unroll
         for (int o = 0; o < kGrpComps; ++o) {
+          if (G.out[o] < 0) continue;
+          const int fj = (G.fc >> (2 * o)) & 3;
+          double f = fo[0];
+#pragma unroll
+          for (int c = 1; c < NC; ++c) f = fj == c ? fo[c] : f;
+          const double sv = NS == 2 ? (((G.sc >> (2 * o)) & 3) == 1 ? sd[1] : sd[0]) : sd[o % NS];
+          const double val = G.ks[o] * sv + G.kf[o] * f;
           if (CARRY) {
-            acc[o][k] = ((G.acc & (1 << o)) ? 0.0 : acc[o][k]) + val[o];
-            if (G.out[o] >= 0 && (G.acc & (1 << (4 + o))) && h < G.stride) {
-              if (P.part) P.part[G.out[o] + h] = acc[o][k];
-              else out[G.out[o] + h] = h < n_own ? (float)(sl * acc[o][k]) : 0.f;
+            acc[o][k] = ((G.acc & (1 << o)) ? 0.0 : acc[o][k]) + val;
+            if ((G.acc & (1 << (4 + o))) && h < G.stride) {
+              if (P.part) (P.part + G.out[o])[(uint32_t)h] = acc[o][k];
+              else (out + G.out[o])[(uint32_t)h] = h < n_own ? (float)(sl * acc[o][k]) : 0.f;
             }
-          } else if (G.out[o] >= 0 && h < G.stride) {
-            out[G.out[o] + h] = h < n_own ? (float)(sl * val[o]) : 0.f;
+          } else if (h < G.stride) {
+            (out + G.out[o])[(uint32_t)h] = h < n_own ? (float)(sl * val) : 0.f;
           }
         }
         // one hand's LDS reads in flight at a time: the next hand's are not
