@@ -1298,6 +1298,20 @@ struct RmParams {
   int32_t dcfr;
   float alpha, beta;
 };
+// Block of a workgroup: the hardware deals workgroups to the eight XCDs in
+// turn, so that neighbouring hands of one piece (blocks are listed piece by
+// piece) would lie on different XCDs, and every line that two of them share
+// (rows start at 16-byte boundaries) be fetched, and written in part, by both.
+// Runs of eight blocks go to one XCD; what is left at the end stays in order.
+// Batch of 512: 279 -> 214 MB fetched by an iteration's updates (as counted by
+// FETCH_SIZE), 532 -> 521 us per iteration; turn + river game 618 -> 600 us;
+// runs of 32 or 128 gain no more.  Only k_rmp: a launch small enough for k_rmq
+// is bound by its slowest XCD, which runs make slower (the largest menu's
+// solve +2%).
+__device__ inline int rm_block(int b, int n) {
+  if (b >= (n & ~63)) return b;
+  return (b & ~63) + (b & 7) * 8 + ((b >> 3) & 7);
+}
 constexpr int RMW = kRmGroups;              // wavefronts per block, one per subtree group
 constexpr int RMR = kTaskRowsMax / RMW;     // rows loaded per wavefront
 
@@ -1485,8 +1499,9 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
                                                   float* __restrict__ x, float* __restrict__ stage,
                                                   const double* __restrict__ tdev) {
   extern __shared__ float rsm[];
-  const RmTask T = P.blocks[blockIdx.x].t;
-  const int h0 = P.blocks[blockIdx.x].h0;
+  const int bi = rm_block((int)blockIdx.x, (int)gridDim.x);
+  const RmTask T = P.blocks[bi].t;
+  const int h0 = P.blocks[bi].h0;
   if (P.active && !P.active[T.inst]) return;   // whole block: T is uniform
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

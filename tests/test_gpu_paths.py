@@ -213,6 +213,26 @@ def test_averages_do_not_depend_on_the_split(name, fn, rule):
         assert np.array_equal(st[2], states[0][2])
 
 
+# regret updates' blocks in the order of the XCDs: copies of one game, so that
+# launches have fewer blocks than a run, whole runs and a remainder; every copy
+# gives the same bits, in pieces of one and of two depths
+@pytest.mark.parametrize("copies", [2, 16, 37])
+@pytest.mark.parametrize("rows", [16, 64])
+def test_update_blocks_cover_every_copy(copies, rows):
+    d = I.river_config(seed=9, n_keep=(150, 61), max_raises=2)
+    g = _game([d] * copies)
+    g.solver_set_rm_quad(0)
+    g.solver_set_task_rows(rows)
+    g.solver_step(6)
+    torch.cuda.synchronize()
+    for p in range(2):
+        st = g.solver_get_state(p)
+        for k in ("regret", "plan", "avg_sum"):
+            v = st[k].reshape(copies, -1)
+            assert np.abs(v[0]).max() > 0
+            assert (v == v[0]).all(), (p, k)
+
+
 # a training step's kernels against the layer-by-layer path: remainders of the
 # 32-row blocks and the 256-row losses, one split and many, with and without
 # weights
