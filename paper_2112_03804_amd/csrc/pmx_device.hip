@@ -1635,7 +1635,12 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
 // steps across the quad.  A walk step so runs about a quarter of the
 // per-lane instructions of k_rmp.  Same pieces, tables and LDS row numbering
 // as k_rmp, with rows of 16 hands; a block record of 64 hands is taken by
-// four workgroups.
+// four workgroups.  Bound by latency: a single wavefront per SIMD, whose steps
+// depend on one another.  So a step reads LDS during the step before it, the
+// bottom-up step leaves the new behaviour for the top-down walk, which is then
+// a product per row, and the loads before the walk take three dependent round
+// trips.  River endgame (1081 hands): 8.4 -> 6.7 us per update; the many-size
+// river of 523 x 871 hands: 19.1 and 18.0 -> 13.3 and 12.6 us.
 // ---------------------------------------------------------------------------
 constexpr int RQH = 16;   // hands per workgroup
 
@@ -1645,70 +1650,185 @@ __device__ inline float quad_sum(float v) {
   return v;
 }
 
-// Bottom-up step for one hand's quad: actions q, q + 4, ... of the infoset.
-template <bool DC>
-__device__ inline void rmq_up(float* __restrict__ Al, float* __restrict__ Rl, float* __restrict__ rsm, int f,
-                              int n, int up, int q, int hl, const RmStep& K) {
-  const int na = (n + 3) >> 2;   // actions per lane
-  float rs = 0.f, dot = 0.f, gs = 0.f;
-  float rr[2], gg[2];
-#pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    const int a = q + 4 * c;
-    const int o = (f + min(a, n - 1)) * RQH + hl;
-    rr[c] = Rl[o];
-    gg[c] = Al[o];
-    const bool on = c < na && a < n;
-    const float r = on ? fmaxf(rr[c], 0.f) : 0.f;
-    rs += r;
-    dot += r * gg[c];
-    gs += on ? gg[c] : 0.f;
+// One infoset of the bottom-up walk, for one hand's quad: its action count,
+// the LDS places of actions q and q + 4 (positions past the last action take
+// the last one's) and of the receiving row, and what lies there.  A place's
+// regret lies RS after its value.
+struct RmqInf {
+  int n;
+  int at[2], to;
+  float rr[2], gg[2], pv;
+};
+template <int RS>
+__device__ inline void rmq_fetch(RmqInf& I, int v, const float* L, int q, int hl) {
+  const int f = (kRmRowLocal + (v & 255)) * RQH;
+  I.n = (v >> 8) & 255;
+  I.at[0] = f + (min(q, I.n - 1) * RQH + hl);
+  I.rr[0] = L[I.at[0] + RS];
+  I.gg[0] = L[I.at[0]];
+  I.at[1] = I.at[0];
+  if (I.n > 4) {
+    I.at[1] = f + (min(q + 4, I.n - 1) * RQH + hl);
+    I.rr[1] = L[I.at[1] + RS];
+    I.gg[1] = L[I.at[1]];
   }
-  for (int c = 2; c < na; ++c) {   // infosets of more than 8 actions
-    const int a = q + 4 * c;
-    const int o = (f + min(a, n - 1)) * RQH + hl;
-    const bool on = a < n;
-    const float r = on ? fmaxf(Rl[o], 0.f) : 0.f, gv = Al[o];
+  I.to = ((v >> 16) & 255) * RQH + hl;
+  I.pv = L[I.to];
+}
+
+// Behaviour of an infoset from the sum of its positive regrets: action a's is
+// ((pos ? r_a : 1) * sc) * rc.
+__device__ inline void rmq_norm(float rs, int n, bool& pos, float& sc, float& rc) {
+  pos = rs > 0.f;
+  rc = rm_rcp(pos ? rs : (float)n, sc);
+}
+__device__ inline float pos_part(float r) { return r > 0.f ? r : 0.f; }
+
+// Bottom-up step of an infoset of up to 4 (C = 1) or more actions: its value
+// into the receiving row (the quad's lanes agree and write it together; where
+// that is a row of the next infoset N, or its receiving row too, N takes it
+// over in registers), the new regrets, and, with BEH, the new behaviour into the rows
+// of g, which only the top-down walk reads from here on.  What is fused and
+// what is rounded is written out: the bits don't depend on how the walk is
+// scheduled.
+template <int C, bool DC, bool BEH, int RS>
+__device__ inline void rmq_up(const RmqInf& I, RmqInf& N, float* L, int q, const RmStep& K) {
+#pragma clang fp contract(off)
+  const int n = I.n, na = C == 1 ? 1 : (n + 3) >> 2;   // actions per lane
+  auto fresh = [&](float r, float gv, float V) {
+    const float inst = gv - V;
+    return DC ? __builtin_fmaf(r, r > 0.f ? K.dp : K.dn, inst) : pos_part(r + inst);
+  };
+  bool on[2];
+  float rs = 0.f, dot = 0.f, gs = 0.f;
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    on[c] = q + 4 * c < n;
+    const float r = on[c] ? pos_part(I.rr[c]) : 0.f, gv = on[c] ? I.gg[c] : 0.f;
+    rs = c ? rs + r : r;
+    dot = __builtin_fmaf(r, I.gg[c], dot);
+    gs = c ? gs + gv : gv;
+  }
+  // infosets of more than 8 actions
+  auto row = [&](int c) { return I.at[0] + (min(q + 4 * c, n - 1) - q) * RQH; };   // n > 4: at[0] is action q's
+  for (int c = 2; c < na; ++c) {
+    const int o = row(c);
+    const float r = q + 4 * c < n ? pos_part(L[o + RS]) : 0.f, gv = L[o];
     rs += r;
-    dot += r * gv;
-    gs += on ? gv : 0.f;
+    dot = __builtin_fmaf(r, gv, dot);
+    gs += q + 4 * c < n ? gv : 0.f;
   }
   rs = quad_sum(rs);
   dot = quad_sum(dot);
   gs = quad_sum(gs);
-  const bool pos = rs > 0.f;
-  float sc;
-  const float rc = rm_rcp(pos ? rs : (float)n, sc);
+  bool pos;
+  float sc, rc;
+  rmq_norm(rs, n, pos, sc, rc);
   const float V = ((pos ? dot : gs) * sc) * rc;
+  const float pn = I.pv + V;
   // positions past the last action rewrite the last action's row with the
   // value its own lane writes
+  float nr[2], ns = 0.f;
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
-    if (c < na) Rl[(f + min(q + 4 * c, n - 1)) * RQH + hl] = rm_new<DC>(rr[c], gg[c] - V, K);
-  for (int c = 2; c < na; ++c) {
-    const int o = (f + min(q + 4 * c, n - 1)) * RQH + hl;
-    Rl[o] = rm_new<DC>(Rl[o], Al[o] - V, K);
+  for (int c = 0; c < C; ++c) {
+    nr[c] = fresh(I.rr[c], I.gg[c], V);
+    const float r = on[c] ? pos_part(nr[c]) : 0.f;
+    ns = c ? ns + r : r;
   }
-  if (q == 0) rsm[up * RQH + hl] += V;
+  // N is waited for here: behind the step's writes the wait would be for them
+  N.gg[0] = N.at[0] == I.to ? pn : N.gg[0];
+  N.gg[1] = N.at[1] == I.to ? pn : N.gg[1];
+  N.pv = N.to == I.to ? pn : N.pv;
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int c = 0; c < C; ++c) L[I.at[c] + RS] = nr[c];
+  for (int c = 2; c < na; ++c) {
+    const int o = row(c);
+    const float r = fresh(L[o + RS], L[o], V);
+    ns += q + 4 * c < n ? pos_part(r) : 0.f;
+    L[o + RS] = r;
+  }
+  L[I.to] = pn;
+  if (BEH) {
+    rmq_norm(quad_sum(ns), n, pos, sc, rc);
+#pragma unroll
+    for (int c = 0; c < C; ++c) L[I.at[c]] = ((pos ? pos_part(nr[c]) : 1.f) * sc) * rc;
+    for (int c = 2; c < na; ++c) {
+      const int o = row(c);
+      L[o] = ((pos ? pos_part(L[o + RS]) : 1.f) * sc) * rc;
+    }
+  }
 }
 
-// Top-down step for one hand's quad.
-__device__ inline void rmq_down(float* __restrict__ Al, const float* __restrict__ Rl, const float* __restrict__ rsm,
-                                int f, int n, int dn, int q, int hl) {
-  const int na = (n + 3) >> 2;
+// Bottom-up walk of the infosets [i0, i1), last first.  A step's LDS reads are
+// issued during the step before it.
+template <bool DC, bool BEH, int RS>
+__device__ inline void rmq_walk_up(int infv, int i0, int i1, float* L, int q, int hl, const RmStep& K) {
+  if (i1 <= i0) return;
+  RmqInf I;
+  rmq_fetch<RS>(I, rl(infv, i1 - 1), L, q, hl);
+#pragma unroll 2
+  for (int i = i1 - 1;; --i) {
+    RmqInf N;
+    rmq_fetch<RS>(N, rl(infv, max(i - 1, i0)), L, q, hl);
+    if (I.n <= 4) rmq_up<1, DC, BEH, RS>(I, N, L, q, K);
+    else rmq_up<2, DC, BEH, RS>(I, N, L, q, K);
+    if (i == i0) break;
+    I = N;
+  }
+}
+
+// Behaviour of one infoset from its regrets, into its rows of values (pieces
+// whose regrets an earlier launch updated).
+template <int RS>
+__device__ inline void rmq_behave(int v, float* L, int q, int hl) {
+  const int f = kRmRowLocal + (v & 255), n = (v >> 8) & 255, na = (n + 3) >> 2;
   float rs = 0.f;
   for (int c = 0; c < na; ++c) {
     const int a = q + 4 * c;
-    rs += a < n ? fmaxf(Rl[(f + min(a, n - 1)) * RQH + hl], 0.f) : 0.f;
+    rs += a < n ? pos_part(L[(f + min(a, n - 1)) * RQH + hl + RS]) : 0.f;
   }
-  rs = quad_sum(rs);
-  const float xp = rsm[dn * RQH + hl];
-  const bool pos = rs > 0.f;
-  float sc;
-  const float rc = rm_rcp(pos ? rs : (float)n, sc);
+  bool pos;
+  float sc, rc;
+  rmq_norm(quad_sum(rs), n, pos, sc, rc);
   for (int c = 0; c < na; ++c) {
     const int o = (f + min(q + 4 * c, n - 1)) * RQH + hl;
-    Al[o] = xp * (((pos ? fmaxf(Rl[o], 0.f) : 1.f) * sc) * rc);
+    L[o] = ((pos ? pos_part(L[o + RS]) : 1.f) * sc) * rc;
+  }
+}
+
+// Top-down walk of the infosets [i0, i1): behaviour times the parent
+// sequence's weight.  The next infoset's behaviour is read a step ahead.
+__device__ inline void rmq_walk_down(int infv, int i0, int i1, float* L, int q, int hl) {
+  if (i1 <= i0) return;
+  int n, at;
+  float b;
+  auto fetch = [&](int v, int& m, int& a, float& t) {
+    m = (v >> 8) & 255;
+    a = (kRmRowLocal + (v & 255)) * RQH + (min(q, m - 1) * RQH + hl);
+    t = L[a];
+  };
+  int v = rl(infv, i0);
+  fetch(v, n, at, b);
+#pragma unroll 2
+  for (int i = i0;; ++i) {
+    const float xp = L[((uint32_t)v >> 24) * RQH + hl];
+    const int vn = rl(infv, min(i + 1, i1 - 1));
+    int nn, an;
+    float bn;
+    fetch(vn, nn, an, bn);
+    const float xa = xp * b;
+    asm volatile("" ::"v"(bn));   // waited for before the write, not behind it
+    L[at] = xa;
+    for (int a = 4; a < n; a += 4) {   // n > 4: at is action q's
+      const int o = at + (min(q + a, n - 1) - q) * RQH;
+      L[o] = xp * L[o];
+    }
+    if (i + 1 >= i1) break;
+    v = vn;
+    n = nn;
+    at = an;
+    b = bn;
   }
 }
 
@@ -1720,7 +1840,6 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   const RmTask T = P.blocks[blockIdx.x >> 2].t;
   const int h0 = P.blocks[blockIdx.x >> 2].h0 + RQH * (int)(blockIdx.x & 3);
   if (h0 >= T.n_hands) return;                 // whole block
-  if (P.active && !P.active[T.inst]) return;   // whole block: T is uniform
   const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int q = lane & 3, hl = lane >> 2;
@@ -1730,36 +1849,49 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   float* Xw = rsm + kRmRowSlot * RQH;
   float* Xl = rsm + kRmRowExt * RQH;
   float* Al = rsm + kRmRowLocal * RQH;
-  float* Rl = Al + P.max_rows * RQH;
+  constexpr int RS = ROWS * RQH;                // from a row's values to its regrets
+  float* Rl = Al + RS;
   const int64_t hc = act ? h : T.n_hands - 1;   // in-bounds hand for loads
   const int64_t stride = T.stride;
-  const RmStep K = rm_step(DC, P.alpha, P.beta, *tdev);
-  const int rowv = T.row0 >= 0 ? T.row0 + lane : (lane < SL ? P.rows[T.rows_off + lane] : 0);
+  // the loads in as few round trips as their addresses allow: the record;
+  // row ids (when they are in a table) and tables; rows
+  constexpr int RQK = ROWS / (4 * RMW);
+  static_assert(ROWS == kTaskRowsMax || MODE == 0, "whole-treeplex pieces have no external parents");
+  // rows 4 (wv + RMW k) + q for k < RQK, 16 hands each: lane (hl, q) takes
+  // row 4 (wv + RMW k) + q of hand hl
+  int rid[RQK];
+#pragma unroll
+  for (int k = 0; k < RQK; ++k) rid[k] = min(4 * (wv + RMW * k) + q, SL - 1);
+  if (T.row0 >= 0) {
+#pragma unroll
+    for (int k = 0; k < RQK; ++k) rid[k] += T.row0;
+  } else {
+#pragma unroll
+    for (int k = 0; k < RQK; ++k) rid[k] = P.rows[T.rows_off + rid[k]];
+  }
   const int infv = lane < T.n_inf ? P.infs[T.inf_off + lane] : 0;
   const bool grouped = T.grp_off >= 0;
   const int grpv = grouped ? P.grp[T.grp_off + lane] : 0;
   const int extv = (MODE != 0 && lane < T.n_ext)
                        ? (MODE == 1 ? P.ext_slot[T.ext_off + lane] : P.ext_seq[T.ext_off + lane]) : 0;
-  // rows 4 (wv + RMW k) + q for k < 4, 16 hands each: lane (hl, q) takes
-  // row 4 (wv + RMW k) + q of hand hl
-  constexpr int RQK = ROWS / (4 * RMW);
-  static_assert(ROWS == kTaskRowsMax || MODE == 0, "whole-treeplex pieces have no external parents");
-  int rid[RQK];
+  RmStep K;
   {
     float a[RQK], b[RQK];
 #pragma unroll
     for (int k = 0; k < RQK; ++k) {
-      const int r = min(4 * (wv + RMW * k) + q, SL - 1);
-      rid[k] = T.row0 >= 0 ? T.row0 + r : r < 64 ? __shfl(rowv, r, 64) : P.rows[T.rows_off + r];
       const int64_t idx = T.vec_base + hc + (int64_t)rid[k] * stride;
       if (MODE != 2) a[k] = g[idx];
       b[k] = R[idx];
     }
+    float xe[kTaskExtMax];
     if (MODE == 2 && wv == 0 && T.n_ext > 0) {
-      float xe[kTaskExtMax];
 #pragma unroll
       for (int k = 0; k < kTaskExtMax; ++k)
         xe[k] = x[T.vec_base + hc + (int64_t)rl(extv, min(k, T.n_ext - 1)) * stride];
+    }
+    K = rm_step(DC, P.alpha, P.beta, *tdev);
+    if (P.active && !P.active[T.inst]) return;   // whole block: T is uniform
+    if (MODE == 2 && wv == 0 && T.n_ext > 0) {
 #pragma unroll
       for (int k = 0; k < kTaskExtMax; ++k)
         if (k < T.n_ext && q == 0) Xl[k * RQH + hl] = xe[k];
@@ -1794,14 +1926,14 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
         if (wv == 0) rm_merge<RQH>(rsm, grpv, hl, q == 0);
       }
       if (ps == 1 && wv != 0) break;
-      const int i0 = ps ? tb : gb, i1 = ps ? te : ge;
-      for (int i = i1 - 1; i >= i0; --i) {
-        const int v = rl(infv, i);
-        rmq_up<DC>(Al, Rl, rsm, v & 255, (v >> 8) & 255, (v >> 16) & 255, q, hl, K);
-      }
+      rmq_walk_up<DC, MODE == 0, RS>(infv, ps ? tb : gb, ps ? te : ge, rsm, q, hl, K);
     }
     if (MODE == 1 && wv == 0 && act && q == 0)
       for (int k = 0; k < T.n_ext; ++k) stage[(int64_t)rl(extv, k) * P.stage_stride + h] = Xl[k * RQH + hl];
+  } else {
+    // the infosets' behaviours, every wavefront an equal share
+    for (int i = wv; i < T.n_inf; i += RMW) rmq_behave<RS>(rl(infv, i), rsm, q, hl);
+    __syncthreads();
   }
   if (MODE != 1) {
 #pragma unroll 1
@@ -1809,11 +1941,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
       if (ps == 1) __syncthreads();
       else if (wv != 0) continue;
       else if (q == 0) rsm[kRmRowOne * RQH + hl] = 1.f;
-      const int i0 = ps ? gb : tb, i1 = ps ? ge : te;
-      for (int i = i0; i < i1; ++i) {
-        const int v = rl(infv, i);
-        rmq_down(Al, Rl, rsm, v & 255, (v >> 8) & 255, (uint32_t)v >> 24, q, hl);
-      }
+      rmq_walk_down(infv, ps ? gb : tb, ps ? ge : te, rsm, q, hl);
     }
   }
   __syncthreads();
@@ -3406,7 +3534,9 @@ static int rm_update(Game* g, int p, float* x, hipStream_t s) {
     // four-lane form
     const bool whole = P.max_rows > kTaskRowsMax;
     const bool quad = whole || nb <= g->hg.rm_quad_max;
-    const size_t lds = sizeof(float) * (quad ? RQH : 64) * (size_t)(kRmRowLocal + 2 * P.max_rows);
+    // the four-lane form keeps the regrets a constant distance after the values
+    const int rows = !quad ? P.max_rows : whole ? kTaskRowsWhole : kTaskRowsMax;
+    const size_t lds = sizeof(float) * (quad ? RQH : 64) * (size_t)(kRmRowLocal + rows + P.max_rows);
     auto go = [&](auto kern) {
       hipLaunchKernelGGL(kern, dim3(quad ? 4 * nb : nb), dim3(64 * RMW), lds, s, P, gr, g->R[p].p, x,
                          E.stage.p, td);

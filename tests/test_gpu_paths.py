@@ -233,6 +233,44 @@ def test_update_blocks_cover_every_copy(copies, rows):
             assert (v == v[0]).all(), (p, k)
 
 
+# four lanes per hand: infosets of up to 4, 5 to 8 and more actions (one, two
+# and more per lane), whole and in pieces; a step from random regrets against
+# the oracle, the plan as the realization of the device's own regrets
+@pytest.mark.parametrize("kind", ["rm+", "dcfr"])
+@pytest.mark.parametrize("rows", [16, 64])
+@pytest.mark.parametrize("sizes,raises", [(1, 2), (2, 2), (3, 2), (5, 1), (7, 1), (11, 1)])
+def test_update_by_action_count(sizes, raises, rows, kind):
+    d = I.river_config(seed=12, n_keep=(37, 21), bet_fracs=tuple(0.25 * (i + 1) for i in range(sizes)),
+                       max_raises=raises, stack=500.0)
+    o = payoff.Game(d)
+    g = _game(d)
+    if rows < 64:
+        g.solver_set_task_rows(rows)
+    g.solver_set_params(kind)
+    rng = np.random.default_rng(sizes)
+    ref = solver.RMPlus(o, kind=kind)
+    for p in range(2):
+        R = ((rng.random((o.S[p], o.N[p])) - 0.2) * 3.0).astype(np.float32).astype(np.float64)
+        if kind == "rm+":
+            R = np.maximum(R, 0.0)
+        x = ref.tp[p].realization(ref.tp[p].behaviour_from_regret(R)).astype(np.float32).astype(np.float64)
+        ref.R[p], ref.x[p] = R, x
+        ref.sum[p] = np.zeros_like(x)
+        g.solver_set_state(p, regret=g.pack(p, [R]), plan=g.pack(p, [x]),
+                           avg_sum=g.pack(p, [ref.sum[p]], np.float64), t=4, wsum=10.0)
+    ref.t, ref.wsum = 4, 10.0
+    g.solver_step(1)
+    torch.cuda.synchronize()
+    ref.step()
+    for p in range(2):
+        st = g.solver_get_state(p)
+        R, x = g.unpack(p, st["regret"])[0], g.unpack(p, st["plan"])[0]
+        assert np.abs(R - ref.R[p]).max() <= 1e-5 * max(1.0, np.abs(ref.R[p]).max()), p
+        tp = ref.tp[p]
+        assert np.abs(x - tp.realization(tp.behaviour_from_regret(R))).max() <= 1e-5, p
+    g.close()
+
+
 # a training step's kernels against the layer-by-layer path: remainders of the
 # 32-row blocks and the 256-row losses, one split and many, with and without
 # weights
