@@ -497,6 +497,7 @@ struct GParams {
   double* part;                  // cut sequences: the groups' FP64 terms go here (NULL: carried)
   double scale;
   int32_t nchunk;
+  int32_t slices;                // workgroups per chunk, each with BLK of the own hands (1: all hands)
 };
 
 // One step of an inclusive segmented scan of a[0..NC): the values of the
@@ -520,7 +521,8 @@ __device__ inline void seg_add(uint64_t open, double (&a)[NC]) {
 
 // Exclusive segmented scan of NC values over the threads of a block of four
 // wavefronts (as block_seg_scan_x): the exclusive sum is the inclusive one
-// minus the own value.  One barrier; `scr` holds 5 doubles per wavefront.
+// minus the own value.  One barrier; `scr` holds 5 doubles per wavefront.  A
+// block of more wavefronts runs one scan per four, each on values of its own.
 // The run flags are the layout's, so they live in scalar masks; a wavefront
 // whose runs within it have at most four lanes (the card segments: all
 // wavefronts but the global segment's) leaves out the steps over four and
@@ -531,7 +533,7 @@ __device__ inline void seg_add(uint64_t open, double (&a)[NC]) {
 template <int NW, int NC>
 __device__ inline void block_seg_scan4(int flag, int n_chunk, const double (&a)[NC], double* scr, double (&e)[NC]) {
   static_assert(NW == 4, "the carries are written out for four wavefronts");
-  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & (NW - 1));
   const uint64_t fm = __builtin_amdgcn_ballot_w64(flag != 0);
   const int lim = n_chunk - 64 * wid;            // lanes past the last chunk belong to no run
   uint64_t near = fm | 1 | (lim <= 0 ? ~0ull : lim >= 64 ? 0ull : ~0ull << lim);
@@ -621,32 +623,67 @@ __device__ inline int xcd_chunk(int b, int n) {
   return x * q + min(x, r) + (b >> 3);
 }
 
-// LDS slots of a group: NC FP32 values (16 bytes for four components, 8 for
-// two).  The layout's byte offsets are built for 16-byte slots; a two-wide
-// launch halves them.
-template <int NC>
+// LDS slots of a group: one plane of NC FP32 values (16 bytes for four
+// components, 8 for two), or, where two sets of wavefronts scan a pair of
+// components each, two planes of 8 bytes, so that either set reads and writes
+// whole banks.  The layout's byte offsets are built for 16-byte slots; 8-byte
+// slots halve them.
+template <int W>
 struct GSlot;
 template <>
 struct GSlot<4> {
   static constexpr int SB = 16, SH = 0;
-  __device__ static void ld(const char* p, float (&v)[4]) {
+  __device__ static void ld(const char* p, float* v) {
     const float4 t = *(const float4*)p;
     v[0] = t.x, v[1] = t.y, v[2] = t.z, v[3] = t.w;
   }
-  __device__ static void st(char* p, const float (&v)[4]) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
+  __device__ static void st(char* p, const float* v) { *(float4*)p = make_float4(v[0], v[1], v[2], v[3]); }
 };
 template <>
 struct GSlot<2> {
   static constexpr int SB = 8, SH = 1;
-  __device__ static void ld(const char* p, float (&v)[2]) {
+  __device__ static void ld(const char* p, float* v) {
     const float2 t = *(const float2*)p;
     v[0] = t.x, v[1] = t.y;
   }
-  __device__ static void st(char* p, const float (&v)[2]) { *(float2*)p = make_float2(v[0], v[1]); }
+  __device__ static void st(char* p, const float* v) { *(float2*)p = make_float2(v[0], v[1]); }
 };
-template <int NC>
-__device__ inline void grp_slot(const char* R, uint32_t slot, float (&v)[NC]) {
-  GSlot<NC>::ld(R + GSlot<NC>::SB * slot, v);
+// All N components of a slot, W of them per plane.
+template <int N, int W>
+__device__ inline void grp_slot(const char* R, int plane, uint32_t slot, float (&v)[N]) {
+#pragma unroll
+  for (int p = 0; p < N / W; ++p) GSlot<W>::ld(R + p * plane + GSlot<W>::SB * slot, v + W * p);
+}
+
+// Threads of a launch.  The four-wide form (few workgroups: single river
+// endgames) takes 512: 256 scan two components, 256 the other two, a chunk of
+// entries per thread in either, and all 512 share the hands of the staging and
+// of the queries.  The forms that fill the chip take 256, where more
+// wavefronts per workgroup only wait for one another (the four-staged,
+// two-slotted form: a pair of products of 512 instances in 197 us, 214 us with
+// 512 threads; the carrying form: turn + river products 286 us, 290 us), and
+// so do games of one hand per thread.
+template <int KH, bool CARRY, int NC, int NS>
+constexpr int mvg_threads() {
+  return KH > 1 && !CARRY && NC == kGrpComps && NS == NC ? 2 * kGrpBlock : kGrpBlock;
+}
+// Planes of a launch's slots.
+template <int KH, bool CARRY, int NC, int NS>
+constexpr int mvg_planes() {
+  return mvg_threads<KH, CARRY, NC, NS>() / kGrpBlock;
+}
+
+// Bytes of a plane of prefix slots of W components.
+template <int KE, int W>
+constexpr int grp_plane() {
+  return GSlot<W>::SB * KE * kGrpBlock;
+}
+// Bytes of the staging region of a launch whose prefix slots hold fewer
+// components than it stages (NS < NC): 16-byte rows for KH * block hands,
+// one padding row per 16, the zero row and the trash row.
+template <int KH>
+constexpr int grp_stage_bytes() {
+  return 16 * (KH * kGrpBlock + KH * kGrpBlock / 16 + 2);
 }
 
 // Showdown values of the NS components held in prefix slots and fold values
@@ -655,15 +692,15 @@ __device__ inline void grp_slot(const char* R, uint32_t slot, float (&v)[NC]) {
 // is the difference of the prefix sums at its global entry and the next one;
 // with NS < NC (the fold-only components have no slots) it is read from its
 // staging row in St.
-template <int KE, int NC, int NS>
+template <int KE, int NP, int NC, int NS>
 __device__ inline void grp_query(const char* R, const char* St, const double* segT, uint4 r, int cph,
                                  double (&sd)[NS], double (&fo)[NC]) {
-  constexpr int BLK = kGrpBlock;
+  constexpr int BLK = kGrpBlock, W = NC / NP, WS = NS / NP, RP = grp_plane<KE, WS>();
   float g0[NS], g1[NS], a0[NS], a1[NS];
-  grp_slot<NS>(R, r.x & 0xffffu, g0);
-  grp_slot<NS>(R, r.x >> 16, g1);
-  grp_slot<NS>(R, r.y & 0xffffu, a0);
-  grp_slot<NS>(R, r.y >> 16, a1);
+  grp_slot<NS, WS>(R, RP, r.x & 0xffffu, g0);
+  grp_slot<NS, WS>(R, RP, r.x >> 16, g1);
+  grp_slot<NS, WS>(R, RP, r.y & 0xffffu, a0);
+  grp_slot<NS, WS>(R, RP, r.y >> 16, a1);
   const int c0 = r.w & 63, c1 = (r.w >> 6) & 63;
   const double* T = segT;   // NC doubles per segment
 #pragma unroll
@@ -675,8 +712,8 @@ __device__ inline void grp_query(const char* R, const char* St, const double* se
   for (int j = 0; j < NC; ++j) fo[j] = T[j] - T[NC * (1 + c0) + j];
   if (cph == 2) {
     float b0[NS], b1[NS], u[NC];
-    grp_slot<NS>(R, r.z & 0xffffu, b0);
-    grp_slot<NS>(R, r.z >> 16, b1);
+    grp_slot<NS, WS>(R, RP, r.z & 0xffffu, b0);
+    grp_slot<NS, WS>(R, RP, r.z >> 16, b1);
 #pragma unroll
     for (int j = 0; j < NC; ++j) u[j] = 0.f;
     if (r.w & (1u << 12)) {
@@ -687,8 +724,8 @@ __device__ inline void grp_query(const char* R, const char* St, const double* se
         // its chunk)
         const uint32_t s1 = (r.w & (1u << 13)) ? s0 - (uint32_t)((KE - 1) * BLK) + 1u : s0 + (uint32_t)BLK;
         float p0[NS], p1[NS];
-        grp_slot<NS>(R, s0, p0);
-        grp_slot<NS>(R, s1, p1);
+        grp_slot<NS, WS>(R, RP, s0, p0);
+        grp_slot<NS, WS>(R, RP, s1, p1);
 #pragma unroll
         for (int j = 0; j < NS; ++j) u[j] = p1[j] - p0[j];
       } else {
@@ -696,7 +733,7 @@ __device__ inline void grp_query(const char* R, const char* St, const double* se
         // row is the one of strength position i
         const int i = (int)(s0 % (uint32_t)BLK) * KE + (int)(s0 / (uint32_t)BLK);
         float uv[NC];
-        GSlot<NC>::ld(St + GSlot<NC>::SB * (i + (i >> 4)), uv);   // rows padded one per 16
+        grp_slot<NC, W>(St, 0, (uint32_t)(i + (i >> 4)), uv);   // rows padded one per 16
 #pragma unroll
         for (int j = 0; j < NC; ++j) u[j] = uv[j];
       }
@@ -708,7 +745,8 @@ __device__ inline void grp_query(const char* R, const char* St, const double* se
   }
 }
 
-// One workgroup per chunk of groups.  Per group: every opponent hand stages
+// One workgroup per chunk of groups (or one per chunk and block of own hands,
+// see launch_grp_class).  Per group: every opponent hand stages
 // its weighted values of the group's components (one 16-byte row at its
 // strength position), each thread gathers its chunk of the segmented entry
 // list from those rows and sums it, a segmented block scan carries the sums
@@ -729,29 +767,28 @@ __device__ inline void grp_query(const char* R, const char* St, const double* se
 // slots, only their segment totals and the identical hand's staging row.
 template <int KH, bool CARRY, int NC, int NS>
 constexpr int mvg_waves_per_simd() {
-  return NC == 2 ? (KH <= 2 ? 4 : 3)
+  return mvg_threads<KH, CARRY, NC, NS>() > kGrpBlock ? (KH <= 4 ? 4 : 2)
+       : NC == 2 ? (KH <= 2 ? 4 : 3)
        : NS == 2 ? (KH <= 2 ? 4 : KH <= 4 ? 3 : 2)
-                 : KH == 1 ? 4 : (KH == 2 || (KH == 3 && !CARRY)) ? 3 : (KH == 5 && CARRY) ? 1 : 2;
-}
-
-// Bytes of the staging region of a launch whose prefix slots hold fewer
-// components than it stages (NS < NC): 16-byte rows for KH * block hands,
-// one padding row per 16, the zero row and the trash row.
-template <int KH>
-constexpr int grp_stage_bytes() {
-  return 16 * (KH * kGrpBlock + KH * kGrpBlock / 16 + 2);
+                 : KH == 1 ? 4 : KH == 2 ? 3 : KH == 5 ? 1 : 2;
 }
 
 template <int KH, int KE, bool CARRY, int NC, int NS>
-__global__ __launch_bounds__(kGrpBlock) __attribute__((amdgpu_waves_per_eu(mvg_waves_per_simd<KH, CARRY, NC, NS>())))
+__global__ __launch_bounds__((mvg_threads<KH, CARRY, NC, NS>())) __attribute__((amdgpu_waves_per_eu(mvg_waves_per_simd<KH, CARRY, NC, NS>())))
 void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, GParams P1,
            const float* __restrict__ in1, float* __restrict__ out1, double* __restrict__ tick) {
-  constexpr int BLK = kGrpBlock, NW = BLK / 64, SH = GSlot<NC>::SH, SBS = GSlot<NS>::SB;
+  constexpr int BLK = kGrpBlock, NW = BLK / 64;
+  constexpr int T = mvg_threads<KH, CARRY, NC, NS>(), NP = mvg_planes<KH, CARRY, NC, NS>();
+  constexpr int KT = (KH * BLK + T - 1) / T;             // hands per thread
+  constexpr int W = NC / NP, WS = NS / NP;               // components per plane: staged, with prefix slots
+  constexpr int RP = grp_plane<KE, WS>();
+  constexpr int SH = GSlot<W>::SH;
   static_assert(NC == 2 || NC == kGrpComps, "two or four components");
   static_assert(NS == NC || (NC == kGrpComps && NS == 2 && !CARRY), "prefix slots for all, or two of four");
   static_assert(KE % 2 == 0, "entry sources are stored in pairs");
   if (tick && blockIdx.x == 0 && threadIdx.x == 0) tick[0] += 1.0;
-  const int b = xcd_chunk((int)blockIdx.x, P0.nchunk + P1.nchunk);
+  const int ns = T > BLK ? P0.slices : 1;
+  const int bs = xcd_chunk((int)blockIdx.x, (P0.nchunk + P1.nchunk) * ns), b = bs / ns, slice = bs - b * ns;
   const bool second = b >= P0.nchunk;
   const GParams& P = second ? P1 : P0;
   const float* __restrict__ in = second ? in1 : in0;
@@ -760,23 +797,28 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
   const int4 cr = make_int4(crp[0], crp[1], crp[2], crp[3]);
   if (P.active && !*cst(P.active + cr.z)) return;   // retired instance
   const int tid = threadIdx.x;
+  const int ct = tid & (BLK - 1);                        // the chunk of entries this thread scans,
+  const int pl = NP == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid / BLK);   //   and the plane
   extern __shared__ double smem[];
   double* segT = smem;                         // [kMcSegMax][NC] segment totals
-  double* scr = segT + NC * kMcSegMax;         // [5 * NW] scan scratch
-  char* R = (char*)(scr + 5 * NW);             // prefix slots (SBS bytes each), over the staging rows
-  char* St = NS < NC ? R + SBS * KE * BLK : R; //   or staging rows of their own (NS < NC)
+  double* scr = segT + NC * kMcSegMax;         // [NP][5 * NW] scan scratch
+  char* R = (char*)(scr + NP * 5 * NW);        // planes of prefix slots, over the staging rows
+  char* St = NS < NC ? R + RP : R;             //   or staging rows of their own (NS < NC)
 
   const int g0 = cr.x, g1 = cr.y;
+  // own hands of this workgroup
+  const int h0 = slice * BLK, h1 = ns > 1 ? h0 + BLK : 0x7fffffff;
   if (cr.w < 0) {
     // a chunk of rows without terms: zeros
+    if (slice) return;
     for (int gi = g0; gi < g1; ++gi) {
       const GGroupS G = load_group(P.groups + gi);
 #pragma unroll
       for (int o = 0; o < kGrpComps; ++o) {
         if (G.out[o] < 0) continue;
 #pragma unroll
-        for (int k = 0; k < KH; ++k) {
-          const int h = tid + k * BLK;
+        for (int k = 0; k < KT; ++k) {
+          const int h = tid + k * T;
           if (h < G.stride) out[G.out[o] + h] = 0.f;
         }
       }
@@ -784,12 +826,12 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
     return;
   }
 
-  double acc[CARRY ? kGrpComps : 1][CARRY ? KH : 1];   // sums of rows over several groups
-  float v[NC][KH];                             // the inputs of the group in flight
+  double acc[CARRY ? kGrpComps : 1][CARRY ? KT : 1];   // sums of rows over several groups
+  float v[NC][KT];                             // the inputs of the group in flight
 #pragma unroll
   for (int o = 0; o < (CARRY ? kGrpComps : 1); ++o)
 #pragma unroll
-    for (int k = 0; k < (CARRY ? KH : 1); ++k) acc[o][k] = 0.0;
+    for (int k = 0; k < (CARRY ? KT : 1); ++k) acc[o][k] = 0.0;
   {
     const GGroupS G = load_group(P.groups + g0);
     // raw loads at in-bounds hands, masked when they are staged: a select here
@@ -798,7 +840,7 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
     for (int j = 0; j < NC; ++j) {
       const float* __restrict__ row = in + max(G.in[j], 0);
 #pragma unroll
-      for (int k = 0; k < KH; ++k) v[j][k] = row[(uint32_t)min(tid + k * BLK, G.n_in - 1)];
+      for (int k = 0; k < KT; ++k) v[j][k] = row[(uint32_t)min(tid + k * T, G.n_in - 1)];
     }
   }
   int gi = g0;
@@ -808,9 +850,9 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
     const auto cp = cst(P.ctx + ctx);
     const int n_own = cp->n_own, n_opp = cp->n_opp, cph = cp->cph, n_chunk = cp->n_chunk;
     const int zrow = cp->zrow;
-    uint32_t rko[KH], srcp[KE / 2];
-    float lop[KH], low[KH];
-    uint4 qr[KH];
+    uint32_t rko[KT], srcp[KE / 2];
+    float lop[KT], low[KT];
+    uint4 qr[KT];
     {
       const uint16_t* rk = P.rk + cp->rk_off;
       const float* lopp = P.lamf + cp->lam_opp_off;
@@ -818,18 +860,19 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       const uint4* qp = P.q + cp->q_off;
       const uint32_t* sp = P.src + cp->src_off;
 #pragma unroll
-      for (int k = 0; k < KH; ++k) {
-        const uint32_t ho = (uint32_t)min(tid + k * BLK, n_opp - 1), hw = (uint32_t)min(tid + k * BLK, n_own - 1);
+      for (int k = 0; k < KT; ++k) {
+        const uint32_t ho = (uint32_t)min(tid + k * T, n_opp - 1);
         rko[k] = rk[ho];
         lop[k] = lopp[ho];
+        const uint32_t hw = (uint32_t)min(h0 + tid + k * T, n_own - 1);
         qr[k] = qp[hw];
         low[k] = lown[hw];
       }
 #pragma unroll
-      for (int j = 0; j < KE / 2; ++j) srcp[j] = sp[(uint32_t)(j * BLK + tid)];
+      for (int j = 0; j < KE / 2; ++j) srcp[j] = sp[(uint32_t)(j * BLK + ct)];
     }
-    const uint32_t cm = P.meta[cp->meta_off + tid];
-    const bool wlive = (tid & ~63) < n_chunk;
+    const uint32_t cm = P.meta[cp->meta_off + ct];
+    const bool wlive = (ct & ~63) < n_chunk;
     for (; gi < g1; ++gi) {
       const GGroupS G = load_group(P.groups + gi);
       if (G.ctx != ctx) break;
@@ -846,93 +889,94 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       // decoded LDS addresses out of the loop costs more registers than the
       // few integer operations it saves
 #pragma unroll
-      for (int k = 0; k < KH; ++k) asm volatile("" : "+v"(qr[k].x), "+v"(qr[k].y), "+v"(qr[k].z), "+v"(qr[k].w));
+      for (int k = 0; k < KT; ++k) asm volatile("" : "+v"(qr[k].x), "+v"(qr[k].y), "+v"(qr[k].z), "+v"(qr[k].w));
 #pragma unroll
       for (int j = 0; j < KE / 2; ++j) asm volatile("" : "+v"(srcp[j]));
       // stage the weighted components at the hands' strength positions, then
       // fetch the next group's inputs into the same registers
 #pragma unroll
-      for (int k = 0; k < KH; ++k) {
-        const int h = tid + k * BLK;
+      for (int k = 0; k < KT; ++k) {
+        const int h = tid + k * T;
         if (h < n_opp) {
           float w[NC];
 #pragma unroll
           for (int j = 0; j < NC; ++j) w[j] = G.in[j] >= 0 ? lop[k] * v[j][k] : 0.f;
-          GSlot<NC>::st(St + (rko[k] >> SH), w);
+#pragma unroll
+          for (int p = 0; p < NP; ++p) GSlot<W>::st(St + p * RP + (rko[k] >> SH), w + W * p);
         }
       }
       if (tid == 0) {
-        float z[NC];
+        const float z[W] = {};
 #pragma unroll
-        for (int j = 0; j < NC; ++j) z[j] = 0.f;
-        GSlot<NC>::st(St + (zrow >> SH), z);
+        for (int p = 0; p < NP; ++p) GSlot<W>::st(St + p * RP + (zrow >> SH), z);
       }
       if (gi + 1 < g1) {
 #pragma unroll
         for (int j = 0; j < NC; ++j) {
           const float* __restrict__ row = in + max(nin[j], 0);
 #pragma unroll
-          for (int k = 0; k < KH; ++k) v[j][k] = row[(uint32_t)min(tid + k * BLK, nn_in - 1)];
+          for (int k = 0; k < KT; ++k) v[j][k] = row[(uint32_t)min(tid + k * T, nn_in - 1)];
         }
       }
       __syncthreads();
       // gather the chunk and sum it (the entries of the components with
       // prefix slots stay in registers); carry the sums across the
       // segment's chunks
-      float ev[KE][NS];
-      float s4[NC];
+      float ev[KE][WS];
+      float s4[W];
 #pragma unroll
-      for (int j = 0; j < NC; ++j) s4[j] = 0.f;
+      for (int j = 0; j < W; ++j) s4[j] = 0.f;
       if (wlive) {
 #pragma unroll
         for (int i = 0; i < KE; ++i) {
           const uint32_t off = (i & 1) ? srcp[i / 2] >> 16 : srcp[i / 2] & 0xffffu;
-          float evf[NC];
-          GSlot<NC>::ld(St + (off >> SH), evf);
+          float evf[W];
+          GSlot<W>::ld(St + pl * RP + (off >> SH), evf);
 #pragma unroll
-          for (int j = 0; j < NC; ++j) s4[j] += evf[j];
+          for (int j = 0; j < W; ++j) s4[j] += evf[j];
 #pragma unroll
-          for (int j = 0; j < NS; ++j) ev[i][j] = evf[j];
+          for (int j = 0; j < WS; ++j) ev[i][j] = evf[j];
         }
       }
-      double a[NC], e[NC];
+      double a[W], e[W];
 #pragma unroll
-      for (int j = 0; j < NC; ++j) a[j] = (double)s4[j];
-      block_seg_scan4<NW, NC>((int)((cm >> 8) & 1u), n_chunk, a, scr, e);
+      for (int j = 0; j < W; ++j) a[j] = (double)s4[j];
+      block_seg_scan4<NW, W>((int)((cm >> 8) & 1u), n_chunk, a, scr + pl * 5 * NW, e);
       // every gather is done (the scan's barrier): the exclusive prefix sums
       // of the slotted components overwrite the staging rows (or fill their
       // own region), each the FP64 carry's FP32 head plus (remainder +
       // partial)
       if (wlive) {
-        float eh[NS], run[NS];
+        float eh[WS], run[WS];
 #pragma unroll
-        for (int j = 0; j < NS; ++j) {
+        for (int j = 0; j < WS; ++j) {
           eh[j] = (float)e[j];
           run[j] = (float)(e[j] - (double)eh[j]);
         }
 #pragma unroll
         for (int i = 0; i < KE; ++i) {
-          float w[NS];
+          float w[WS];
 #pragma unroll
-          for (int j = 0; j < NS; ++j) {
+          for (int j = 0; j < WS; ++j) {
             w[j] = eh[j] + run[j];
             run[j] += ev[i][j];
           }
-          GSlot<NS>::st(R + SBS * (i * BLK + tid), w);
+          GSlot<WS>::st(R + pl * RP + GSlot<WS>::SB * (i * BLK + ct), w);
         }
       }
       const int endseg = (int)((cm >> 16) & 255u);
       if (endseg) {
-        double* T = segT + NC * (endseg - 1);
+        double* ST = segT + NC * (endseg - 1) + W * pl;
 #pragma unroll
-        for (int j = 0; j < NC; ++j) T[j] = e[j] + a[j];
+        for (int j = 0; j < W; ++j) ST[j] = e[j] + a[j];
       }
       __syncthreads();
       // own hands: the outputs' values, stored (or carried to the next group
       // of the sequence)
 #pragma unroll
-      for (int k = 0; k < KH; ++k) {
-        const int h = tid + k * BLK;
+      for (int k = 0; k < KT; ++k) {
+        if (k > 0 && ns > 1) break;
+        const int h = h0 + tid + k * T;
         // outputs: up to four in every kind; components: NC, NS of them with
         // prefix slots (with two, the outputs name their showdown component
         // as they name their fold component)
@@ -941,7 +985,7 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
         for (int j = 0; j < NS; ++j) sd[j] = 0.0;
 #pragma unroll
         for (int j = 0; j < NC; ++j) fo[j] = 0.0;
-        if (h < n_own && qr[k].x != 0xffffffffu) grp_query<KE, NC, NS>(R, St, segT, qr[k], cph, sd, fo);
+        if (h < min(n_own, h1) && qr[k].x != 0xffffffffu) grp_query<KE, NP, NC, NS>(R, St, segT, qr[k], cph, sd, fo);
         const double sl = P.scale * (double)low[k];
 #pragma unroll
         for (int o = 0; o < kGrpComps; ++o) {
@@ -954,11 +998,11 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
           const double val = G.ks[o] * sv + G.kf[o] * f;
           if (CARRY) {
             acc[o][k] = ((G.acc & (1 << o)) ? 0.0 : acc[o][k]) + val;
-            if ((G.acc & (1 << (4 + o))) && h < G.stride) {
+            if ((G.acc & (1 << (4 + o))) && h < min(G.stride, h1)) {
               if (P.part) (P.part + G.out[o])[(uint32_t)h] = acc[o][k];
               else (out + G.out[o])[(uint32_t)h] = h < n_own ? (float)(sl * acc[o][k]) : 0.f;
             }
-          } else if (h < G.stride) {
+          } else if (h < min(G.stride, h1)) {
             (out + G.out[o])[(uint32_t)h] = h < n_own ? (float)(sl * val) : 0.f;
           }
         }
@@ -3296,13 +3340,23 @@ static GParams grp_params(Game* g, int d, const MvParams& like, int kind, int c,
   return P;
 }
 
+constexpr int kGrpSliceWgs = 256;   // one workgroup per CU
 template <int KH, bool CARRY, int NC, int NS = NC>
-static void launch_grp_class(const GParams& A, const float* in0, float* out0, const GParams& B, const float* in1,
+static void launch_grp_class(GParams A, const float* in0, float* out0, const GParams& B, const float* in1,
                              float* out1, hipStream_t s, double* tick) {
+  // A launch that leaves most CUs idle: the queries, whose scattered LDS reads
+  // are nearly half of a workgroup's time (7.5 of 17 thousand cycles with five
+  // hands per 256 threads, 2.4 of 12.5 when dealt), go to KH workgroups per
+  // chunk, which all scan it.  River endgame of 1081 hands: 9.2 -> 6.4 us per
+  // product, 8.5 -> 7.1 us per pair; where the chip is full the scans would be
+  // repeated for nothing.
+  const int chunks = A.nchunk + B.nchunk;
+  A.slices = mvg_threads<KH, CARRY, NC, NS>() > kGrpBlock && chunks * KH <= kGrpSliceWgs ? KH : 1;
   constexpr int KE = kGrpKE[KH - 1];
-  const size_t lds = sizeof(double) * (NC * kMcSegMax + 5 * (kGrpBlock / 64)) +
-                     (size_t)GSlot<NS>::SB * kGrpBlock * KE + (NS < NC ? (size_t)grp_stage_bytes<KH>() : 0);
-  hipLaunchKernelGGL((k_mvg<KH, KE, CARRY, NC, NS>), dim3(A.nchunk + B.nchunk), dim3(kGrpBlock), lds, s, A, in0,
+  constexpr int NP = mvg_planes<KH, CARRY, NC, NS>();
+  const size_t lds = sizeof(double) * (NC * kMcSegMax + NP * 5 * (kGrpBlock / 64)) +
+                     NP * (size_t)grp_plane<KE, NS / NP>() + (NS < NC ? (size_t)grp_stage_bytes<KH>() : 0);
+  hipLaunchKernelGGL((k_mvg<KH, KE, CARRY, NC, NS>), dim3(chunks * A.slices), dim3(mvg_threads<KH, CARRY, NC, NS>()), lds, s, A, in0,
                      out0, B, in1, out1, tick);
 }
 

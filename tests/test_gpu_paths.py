@@ -213,6 +213,32 @@ def test_averages_do_not_depend_on_the_split(name, fn, rule):
         assert np.array_equal(st[2], states[0][2])
 
 
+# a product's queries dealt to several workgroups per chunk (few chunks) and
+# not (copies of the game): the same bits, one to five hands per thread, own and
+# opponent hand counts on either side of a thread's
+@pytest.mark.parametrize("n_keep", [(257, 512), (513, 300), (700, 769), (1000, 1025), (1081, 1081), (256, 1030)])
+def test_sliced_queries(n_keep):
+    d = I.river_config(seed=31, n_keep=n_keep, bet_fracs=(0.5, 1.0), max_raises=2, stack=30.0)
+    res = []
+    for copies in (1, 70):
+        g = _game([d] * copies)
+        rng = np.random.default_rng(3)
+        one = [rng.random((g.layouts[0][p]["n_seq"], g.layouts[0][p]["n_hands"])).astype(np.float32) for p in range(2)]
+        x, y = (torch.from_numpy(g.pack(p, [one[p]] * copies, dtype=np.float32)).cuda() for p in range(2))
+        Ay, ATx = torch.full_like(x, 7.0), torch.full_like(y, 7.0)
+        g.matvec_A(y, Ay)
+        g.matvec_AT(x, ATx)
+        By, BTx = torch.full_like(x, 7.0), torch.full_like(y, 7.0)
+        g.matvec_pair(y, x, By, BTx)
+        torch.cuda.synchronize()
+        for u, v in ((Ay, By), (ATx, BTx)):
+            u, v = (t.cpu().numpy().reshape(copies, -1) for t in (u, v))
+            assert np.array_equal(u, v) and (u == u[0]).all()
+            res.append(u[0])
+        g.close()
+    assert np.array_equal(res[0], res[2]) and np.array_equal(res[1], res[3])
+
+
 # regret updates' blocks in the order of the XCDs: copies of one game, so that
 # launches have fewer blocks than a run, whole runs and a remainder; every copy
 # gives the same bits, in pieces of one and of two depths
