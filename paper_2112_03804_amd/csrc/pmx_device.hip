@@ -3217,6 +3217,7 @@ template <typename F>
 static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, int64_t workgroups, F&& launch,
                          int n_pinned = 0, bool pin_side = false) {
   pin_side = pin_side && n_pinned > 0;
+  if (n == 1 && !pin_side) return launch(0, s, true);
   std::lock_guard<std::mutex> lock(g->fork_mu);
   int order[32];
   int64_t work[32];
@@ -3315,8 +3316,17 @@ static int launch_mc(Game* g, const MvParams& P0, const IO* in0, IO* out0, const
   return PMX_OK;
 }
 
-// cut: the carrying sequences (kind 1) by their groups, terms to the term
-// buffer; otherwise carried.
+// Chunks of a direction's launch of one kind and class.  cut: the carrying
+// sequences (kind 1) by their groups, terms to the term buffer; otherwise
+// carried.
+static int grp_chunks(const Game* g, int d, const MvParams& like, int kind, int c, bool cut) {
+  const DevGrp& E = g->dg[d];
+  const bool solver = like.active != nullptr;
+  return like.nblk <= 0 ? 0
+         : cut && kind == 1 && E.n_red > 0 ? (solver ? E.n_cut_act[c] : E.n_cut[c])
+                                           : (solver ? E.count_act[kind][c] : E.count[kind][c]);
+}
+
 static GParams grp_params(Game* g, int d, const MvParams& like, int kind, int c, bool cut) {
   DevGrp& E = g->dg[d];
   GParams P;
@@ -3334,9 +3344,7 @@ static GParams grp_params(Game* g, int d, const MvParams& like, int kind, int c,
   P.active = like.active;
   P.part = cut ? E.part[solver ? 1 : 0].p : nullptr;
   P.scale = like.scale;
-  P.nchunk = like.nblk <= 0 ? 0
-             : cut ? (solver ? E.n_cut_act[c] : E.n_cut[c])
-                   : (solver ? E.count_act[kind][c] : E.count[kind][c]);
+  P.nchunk = grp_chunks(g, d, like, kind, c, cut);
   return P;
 }
 
@@ -3396,10 +3404,10 @@ static int launch_grp(Game* g, const MvParams& P0, const float* in0, float* out0
   const int kinds[GrpDir::kKinds] = {1, 0, 2, 3};
   for (int kind : kinds) {
     for (int c = 0; c < kGrpClasses; ++c) {
-      const GParams A = grp_params(g, P0.dir, P0, kind, c, cut), B = grp_params(g, P1.dir, P1, kind, c, cut);
-      if (A.nchunk + B.nchunk == 0) continue;
-      work[n] = grp_launch_weight(kind, c, A.nchunk + B.nchunk, A.nchunk > 0 && B.nchunk > 0);
-      wgs += A.nchunk + B.nchunk;
+      const int na = grp_chunks(g, P0.dir, P0, kind, c, cut), nb = grp_chunks(g, P1.dir, P1, kind, c, cut);
+      if (na + nb == 0) continue;
+      work[n] = grp_launch_weight(kind, c, na + nb, na > 0 && nb > 0);
+      wgs += na + nb;
       cls[n++] = kind * kGrpClasses + c;
     }
     if (kind == 1 && cut && n > 0) {
