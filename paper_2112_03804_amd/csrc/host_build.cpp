@@ -1886,7 +1886,7 @@ int build_game(const GameDesc* descs, int n, HostGame& hg, std::string& msg) {
     hg.mv_kernel = 4;
     hg.groups_per_chunk = 1;
     hg.mc_block = mc_kernel == 3 ? 512 : 256;
-    hg.rows_per_block = default_rows_per_block(rows, mc_kernel);
+    hg.rows_per_block = hg.rows_default = default_rows_per_block(rows, mc_kernel);
   }
   for (int d = 0; d < 2; ++d) {
     build_matvec_plan(hg, d, hg.rows_per_block);

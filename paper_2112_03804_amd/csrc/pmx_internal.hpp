@@ -395,6 +395,7 @@ struct HostGame {
   int mv_kernel = 4;                    // FP32 products: 2 / 3 chunk-aligned layout with 256 / 512
                                         // threads, 4 grouped layout
   int rows_per_block = 1;               // row chunks of the chunk-aligned layout and the FP64 products
+  int rows_default = 1;                 // row chunks by the game's size (the FP64 products' under kernel 4)
   int mc_block = 256;                   // chunk-aligned layout: threads per workgroup
   int groups_per_chunk = 1;             // kernel 4: groups per workgroup
   MvDir dir[2];

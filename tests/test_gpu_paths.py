@@ -239,6 +239,28 @@ def test_sliced_queries(n_keep):
     assert np.array_equal(res[0], res[2]) and np.array_equal(res[1], res[3])
 
 
+# the FP64 products don't depend on the schedules tried before the chosen one
+@pytest.mark.parametrize("tried", [(), ((3, 8),), ((2, 1), (3, 64))])
+@pytest.mark.parametrize("name,fn", CUT_CASES[1:3], ids=[c[0] for c in CUT_CASES[1:3]])
+def test_fp64_products_after_tuning(name, fn, tried):
+    d = fn()
+    g, h = _game(d), _game(d)
+    for k, r in tried:
+        g.game_tune(k, r)
+    g.game_tune(4, 2)
+    _, (x, y) = _vectors(g, 6, np.float64)
+    outs = []
+    for q in (g, h):
+        Ay, ATx = torch.full_like(x, 7.0), torch.full_like(y, 7.0)
+        q.matvec_A_f64(y, Ay)
+        q.matvec_AT_f64(x, ATx)
+        torch.cuda.synchronize()
+        outs.append((Ay.cpu().numpy(), ATx.cpu().numpy()))
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+    g.close()
+    h.close()
+
+
 # regret updates' blocks in the order of the XCDs: copies of one game, so that
 # launches have fewer blocks than a run, whole runs and a remainder; every copy
 # gives the same bits, in pieces of one and of two depths
