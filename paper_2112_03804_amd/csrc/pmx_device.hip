@@ -3867,7 +3867,7 @@ int game_tune(Game* g, int32_t kernel, int32_t rows_per_chunk) {
     g->hg.groups_per_chunk = rows_per_chunk;
     // the FP64 products' row chunks are the game's own, whatever was tried
     // before: a river tuned from 3:8 to 4:1 walked eight rows per workgroup
-    // (52 us for both directions, 13 us with one)
+    // (52 us for both directions, 14 us with one)
     g->hg.rows_per_block = g->hg.rows_default;
   } else {
     g->hg.rows_per_block = rows_per_chunk;
