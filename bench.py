@@ -35,9 +35,9 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E, published
 # known size (profiles/matvec_pair_traffic_counters.md).  They describe the
 # kernel sources whose code (comments and whitespace removed) has the SHA-1
 # recorded here and are reported as null for any other version of that code.
-TRAFFIC = {"sources_sha1": "3462011d327d0319e8dfb935a8eaffda120afead",
-           "river": {"4:1": 1422309, "3:1": 1635389},
-           "batch": {"4:1": 351534231, "4:2": 351215134}}
+TRAFFIC = {"sources_sha1": "4a459901936f2722d033e79fc67a953f6c05a9c2",
+           "river": {"4:1": 1422373, "3:1": 1635390},
+           "batch": {"4:1": 351534482, "4:2": 351211196}}
 TRAFFIC_SOURCES = ("paper_2112_03804_amd/csrc/pmx_device.hip", "paper_2112_03804_amd/csrc/host_build.cpp")
 # the schedules of the counter probe (the autotuner's usual choices; traffic
 # is reported for these only) and the batch schedule of the trace probe

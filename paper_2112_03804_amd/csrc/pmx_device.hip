@@ -497,7 +497,7 @@ struct GParams {
   double* part;                  // cut sequences: the groups' FP64 terms go here (NULL: carried)
   double scale;
   int32_t nchunk;
-  int32_t slices;                // workgroups per chunk, each with BLK of the own hands (1: all hands)
+  int32_t slices, slice_hands;   // workgroups per chunk, and the own hands of each
 };
 
 // One step of an inclusive segmented scan of a[0..NC): the values of the
@@ -807,7 +807,7 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
 
   const int g0 = cr.x, g1 = cr.y;
   // own hands of this workgroup
-  const int h0 = slice * BLK, h1 = ns > 1 ? h0 + BLK : 0x7fffffff;
+  const int hs = P0.slice_hands, h0 = slice * hs, h1 = ns > 1 ? h0 + hs : 0x7fffffff;
   if (cr.w < 0) {
     // a chunk of rows without terms: zeros
     if (slice) return;
@@ -975,7 +975,7 @@ void k_mvg(GParams P0, const float* __restrict__ in0, float* __restrict__ out0, 
       // of the sequence)
 #pragma unroll
       for (int k = 0; k < KT; ++k) {
-        if (k > 0 && ns > 1) break;
+        if (k > 0 && ns > 1 && k * T >= hs) break;
         const int h = h0 + tid + k * T;
         // outputs: up to four in every kind; components: NC, NS of them with
         // prefix slots (with two, the outputs name their showdown component
@@ -3352,14 +3352,18 @@ constexpr int kGrpSliceWgs = 256;   // one workgroup per CU
 template <int KH, bool CARRY, int NC, int NS = NC>
 static void launch_grp_class(GParams A, const float* in0, float* out0, const GParams& B, const float* in1,
                              float* out1, hipStream_t s, double* tick) {
-  // A launch that leaves most CUs idle: the queries, whose scattered LDS reads
-  // are nearly half of a workgroup's time (7.5 of 17 thousand cycles with five
-  // hands per 256 threads, 2.4 of 12.5 when dealt), go to KH workgroups per
-  // chunk, which all scan it.  River endgame of 1081 hands: 9.2 -> 6.4 us per
-  // product, 8.5 -> 7.1 us per pair; where the chip is full the scans would be
-  // repeated for nothing.
+  // A launch that leaves CUs idle: the queries, whose scattered LDS reads are
+  // nearly half of a workgroup's time (7.5 of 17 thousand cycles with five
+  // hands per 256 threads, 2.4 of 12.5 when dealt), go to up to KH workgroups
+  // per chunk, which all scan it, as long as a CU has one.  River endgame of
+  // 1081 hands: 9.2 -> 6.4 us per product, 8.5 -> 7.1 us per pair.  Beyond one
+  // workgroup per CU the repeated scans cost more than the queries gain (four
+  // such rivers, a product in each direction: 11.8 us with four, 19.2 us with five
+  // workgroups per chunk, 15.6 us with one).
   const int chunks = A.nchunk + B.nchunk;
-  A.slices = mvg_threads<KH, CARRY, NC, NS>() > kGrpBlock && chunks * KH <= kGrpSliceWgs ? KH : 1;
+  A.slices = mvg_threads<KH, CARRY, NC, NS>() > kGrpBlock ? std::max(1, std::min(KH, kGrpSliceWgs / std::max(chunks, 1)))
+                                                          : 1;
+  A.slice_hands = (KH * kGrpBlock / 64 + A.slices - 1) / A.slices * 64;
   constexpr int KE = kGrpKE[KH - 1];
   constexpr int NP = mvg_planes<KH, CARRY, NC, NS>();
   const size_t lds = sizeof(double) * (NC * kMcSegMax + NP * 5 * (kGrpBlock / 64)) +

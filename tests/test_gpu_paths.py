@@ -214,13 +214,14 @@ def test_averages_do_not_depend_on_the_split(name, fn, rule):
 
 
 # a product's queries dealt to several workgroups per chunk (few chunks) and
-# not (copies of the game): the same bits, one to five hands per thread, own and
-# opponent hand counts on either side of a thread's
+# not (many copies of the game; a few share what CUs there are): the same bits,
+# one to five hands per thread, own and opponent hand counts on either side of a
+# thread's
 @pytest.mark.parametrize("n_keep", [(257, 512), (513, 300), (700, 769), (1000, 1025), (1081, 1081), (256, 1030)])
 def test_sliced_queries(n_keep):
     d = I.river_config(seed=31, n_keep=n_keep, bet_fracs=(0.5, 1.0), max_raises=2, stack=30.0)
     res = []
-    for copies in (1, 70):
+    for copies in (1, 5, 9, 70):
         g = _game([d] * copies)
         rng = np.random.default_rng(3)
         one = [rng.random((g.layouts[0][p]["n_seq"], g.layouts[0][p]["n_hands"])).astype(np.float32) for p in range(2)]
@@ -236,7 +237,8 @@ def test_sliced_queries(n_keep):
             assert np.array_equal(u, v) and (u == u[0]).all()
             res.append(u[0])
         g.close()
-    assert np.array_equal(res[0], res[2]) and np.array_equal(res[1], res[3])
+    for k in range(2, 8, 2):
+        assert np.array_equal(res[0], res[k]) and np.array_equal(res[1], res[k + 1])
 
 
 # the FP64 products don't depend on the schedules tried before the chosen one
