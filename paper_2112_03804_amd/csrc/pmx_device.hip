@@ -1311,6 +1311,13 @@ constexpr int MAXA = 8;       // actions handled in registers by the walks
 __global__ void k_set1(double* tdev, double v) { tdev[0] = v; }
 __global__ void k_add1(double* tdev) { tdev[0] += 1.0; }
 
+// Zeros the entries of `rows` rows past their n hands (at most three a row).
+__global__ __launch_bounds__(256) void k_clear_pad(float* __restrict__ v, int rows, int stride, int n) {
+  const int64_t i = blockIdx.x * (int64_t)256 + threadIdx.x;
+  const int pad = stride - n;
+  if (i < (int64_t)rows * pad) v[i / pad * stride + n + i % pad] = 0.f;
+}
+
 // ---------------------------------------------------------------------------
 // regret update on treeplex pieces (RmTask): the piece's rows of g, R and x
 // for 64 hands live in LDS; every wavefront of the block loads and stores an
@@ -4591,6 +4598,19 @@ int solver_set_state(Game* g, int32_t player, const float* regret, const float* 
   const size_t n = (size_t)g->hg.elems[player];
   if (regret) HIP_TRY(hipMemcpy(g->R[player].p, regret, n * sizeof(float), hipMemcpyHostToDevice));
   if (plan) HIP_TRY(hipMemcpy(g->x[player].p, plan, n * sizeof(float), hipMemcpyHostToDevice));
+  if (plan) {
+    // padding is ignored on input: k_avg adds plans as flat vectors, so what
+    // the caller has there must not stay
+    for (const Built& b : g->hg.inst) {
+      const int rows = b.sf.n_seq[player], pad = b.stride[player] - b.inst.n[player];
+      const int64_t m = (int64_t)rows * pad;
+      if (m > 0)
+        hipLaunchKernelGGL(k_clear_pad, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, nullptr,
+                           g->x[player].p + b.vec_off[player], rows, b.stride[player], b.inst.n[player]);
+    }
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(nullptr));
+  }
   if (avg_sum) HIP_TRY(hipMemcpy(g->xs[player].p, avg_sum, n * sizeof(double), hipMemcpyHostToDevice));
   g->t = t;
   g->wsum = wsum;
