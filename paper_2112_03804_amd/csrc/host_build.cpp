@@ -1740,6 +1740,16 @@ int build_rm_plan(HostGame& hg, int p, int cap, std::string& msg) {
   return PMX_OK;
 }
 
+std::vector<int32_t> rm_pull_seqs(const RmPlan& P) {
+  std::vector<int32_t> slot_seq(std::max(P.n_slot, 1), 0), seqs(P.pulls.size(), 0);
+  for (const RmTask& t : P.tasks)
+    for (int k = 0; k < t.n_ext; ++k) slot_seq[P.ext_slot[t.ext_off + k]] = P.rows[t.rows_off + k];
+  for (const RmTask& t : P.tasks)
+    for (int i = kRmGroups; i < t.n_pull; ++i)
+      seqs[t.pull_off + i] = slot_seq[(uint32_t)P.pulls[t.pull_off + i] >> 8];
+  return seqs;
+}
+
 namespace {
 
 void build_treeplex_plan(HostGame& hg, int p) {

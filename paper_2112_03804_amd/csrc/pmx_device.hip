@@ -2100,7 +2100,8 @@ struct BrSide {
   const RmBlock* blocks;
   const int32_t* rows;
   const int32_t* infs;
-  const int32_t* pulls;         // as RmParams, with the pulled sequence in place of the stage row
+  const int32_t* pulls;         // as RmParams: the receiving rows are read
+  const int32_t* pull_seq;      // the pulled sequences
   const int32_t* grp;
   double* g;                    // the gradient; overwritten
 };
@@ -2153,6 +2154,7 @@ __global__ __launch_bounds__(64 * RMW) void k_brq(BrSide P0, BrSide P1, int n0,
   __syncthreads();
   if (T.n_pull > 0) {
     const int32_t* pl = P.pulls + T.pull_off;
+    const int32_t* pq = P.pull_seq + T.pull_off;
     const int hdr = lane < RMW ? pl[lane] : 0;
     int beg = RMW;
     for (int w = 0; w < wv; ++w) beg += rl(hdr, w);
@@ -2161,11 +2163,12 @@ __global__ __launch_bounds__(64 * RMW) void k_brq(BrSide P0, BrSide P1, int n0,
     int row = -1;
     for (int c0 = 0; c0 < cnt; c0 += 64) {
       const int pv = c0 + lane < cnt ? pl[beg + c0 + lane] : 0;
+      const int sq = c0 + lane < cnt ? pq[beg + c0 + lane] : 0;
       const int nn = min(64, cnt - c0);
       for (int j0 = 0; j0 < nn; j0 += 16) {
         double sv[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) sv[u] = gb[(int64_t)((uint32_t)rl(pv, min(j0 + u, nn - 1)) >> 8) * stride];
+        for (int u = 0; u < 16; ++u) sv[u] = gb[(int64_t)rl(sq, min(j0 + u, nn - 1)) * stride];
 #pragma unroll
         for (int u = 0; u < 16; ++u) {
           if (j0 + u < nn) {
@@ -2537,11 +2540,11 @@ struct DevRm {                  // regret-update pieces of one player
   std::vector<int> max_rows, max_ext;   // per depth
   DBuf<float> stage;
   int stage_stride = 1;
-  // FP64 best responses: blocks of every instance, pulls by sequence, and the
+  // FP64 best responses: blocks of every instance, pulled sequences, and the
   // rows of root values of each instance
   DBuf<RmBlock> br_blocks;
   std::vector<int> br_off;
-  DBuf<int32_t> br_pulls, br_seg_off;
+  DBuf<int32_t> br_pull_seq, br_seg_off;
   DBuf<BrSeg> br_seg;
 };
 
@@ -2948,21 +2951,18 @@ static int upload_rm_blocks(Game* g, int p, const std::vector<char>& act) {
 }
 
 // The best responses' view of the pieces: blocks of every instance by depth,
-// the pulls naming the sequence whose row of g holds the pulled value (a deep
-// piece's value of external parent k lies in its own row k), and the rows
-// that hold root values.
+// the sequences whose rows of g hold the pulled values, and the rows that hold
+// root values.
 static int upload_br(Game* g, int p) {
   const RmPlan& T = g->hg.rm[p];
   DevRm& E = g->drm[p];
   const int D = (int)T.by_depth.size(), nt = (int)T.tasks.size();
   std::vector<char> root(nt, 0);
-  std::vector<int32_t> slot_seq(std::max(T.n_slot, 1), 0);
   std::vector<BrSeg> segs;
   std::vector<int32_t> seg_off(g->hg.inst.size() + 1, 0);
   for (int id = 0; id < nt; ++id) {   // tasks are listed instance by instance
     const RmTask& t = T.tasks[id];
     for (int i = 0; i < t.n_inf; ++i) root[id] |= ((uint32_t)T.infs[t.inf_off + i] >> 24) == kRmRowOne;
-    for (int k = 0; k < t.n_ext; ++k) slot_seq[T.ext_slot[t.ext_off + k]] = T.rows[t.rows_off + k];
     if (root[id]) {
       BrSeg s{};
       s.off = t.vec_base + (int64_t)T.rows[t.rows_off + t.n_ext] * t.stride;
@@ -2972,12 +2972,6 @@ static int upload_br(Game* g, int p) {
     seg_off[t.inst + 1] = (int32_t)segs.size();
   }
   for (size_t i = 0; i < g->hg.inst.size(); ++i) seg_off[i + 1] = std::max(seg_off[i + 1], seg_off[i]);
-  std::vector<int32_t> pulls = T.pulls;
-  for (const RmTask& t : T.tasks)
-    for (int i = kRmGroups; i < t.n_pull; ++i) {
-      int32_t& v = pulls[t.pull_off + i];
-      v = (int32_t)((uint32_t)(v & 255) | ((uint32_t)slot_seq[(uint32_t)v >> 8] << 8));
-    }
   std::vector<RmBlock> blocks;
   E.br_off.assign(D + 1, 0);
   for (int d = 0; d < D; ++d) {
@@ -2993,7 +2987,7 @@ static int upload_br(Game* g, int p) {
   }
   E.br_off[D] = (int)blocks.size();
   int rc;
-  if ((rc = E.br_blocks.upload(blocks)) || (rc = E.br_pulls.upload(pulls)) || (rc = E.br_seg.upload(segs)) ||
+  if ((rc = E.br_blocks.upload(blocks)) || (rc = E.br_pull_seq.upload(rm_pull_seqs(T))) || (rc = E.br_seg.upload(segs)) ||
       (rc = E.br_seg_off.upload(seg_off)))
     return rc;
   return PMX_OK;
@@ -3674,7 +3668,8 @@ static int br_values(Game* g, double* const gd[2], double* br_out, hipStream_t s
     DevRm& E = g->drm[p];
     S[p].rows = E.rows.p;
     S[p].infs = E.infs.p;
-    S[p].pulls = E.br_pulls.p;
+    S[p].pulls = E.pulls.p;
+    S[p].pull_seq = E.br_pull_seq.p;
     S[p].grp = E.grp.p;
     S[p].g = gd[p];
   }

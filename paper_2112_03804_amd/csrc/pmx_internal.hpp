@@ -418,6 +418,10 @@ int default_rows_per_block(int64_t rows, int kernel);
 int default_mv_kernel(int64_t mean_hands);
 void build_matvec_plan(HostGame& hg, int d, int rows_per_block);
 int build_rm_plan(HostGame& hg, int p, int task_rows, std::string& msg);
+// Beside RmPlan::pulls, entry by entry: the sequence whose row of the gradient
+// holds the pulled value in the best responses, where a deep piece leaves the
+// value of external parent k in its own row k.  Counts are 0.
+std::vector<int32_t> rm_pull_seqs(const RmPlan& P);
 int build_mc_layout(HostGame& hg, int d, int block, std::string& msg);
 int build_grp_layout(HostGame& hg, int d, int groups_per_chunk, std::string& msg);
 // host_sparsify.cpp
