@@ -262,7 +262,10 @@ int matvec_A(Game* g, const float* y_dev, float* out_dev, void* stream);
 /* out = A^T x.  x: player 0's vectors, out: player 1's.  As matvec_A. */
 int matvec_AT(Game* g, const float* x_dev, float* out_dev, void* stream);
 
-/* FP64 forms (used for the saddle gap and for precision checks). */
+/* FP64 forms (used for the saddle gap and for precision checks).  Products
+ * of one game, FP32 or FP64, may be enqueued on several streams.  They may be
+ * captured, with no other call of the game until the capture ends; replays
+ * may overlap one another and other products of the game. */
 int matvec_A_f64(Game* g, const double* y_dev, double* out_dev, void* stream);
 int matvec_AT_f64(Game* g, const double* x_dev, double* out_dev, void* stream);
 
@@ -365,7 +368,8 @@ int saddle_gap(Game* g, double* gap, double* br1, double* br2, void* stream);
 int solver_set_gap_guard(Game* g, int32_t k);
 
 /* The same for given sequence-form strategies (device FP64 vectors of each
- * player, vec_elems each).  Synchronizes `stream`. */
+ * player, vec_elems each).  The gaps of one game share its scratch: calls
+ * that overlap (other threads) race.  Synchronizes `stream`. */
 int saddle_gap_of(Game* g, const double* x_dev, const double* y_dev, double* gap,
                   double* br1, double* br2, void* stream);
 

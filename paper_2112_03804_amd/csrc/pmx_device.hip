@@ -78,6 +78,8 @@ struct MvParams {
   int32_t nblk;              // row chunks of the direction (0: the direction is not launched)
   int32_t dir;
   const int32_t* active;     // per-instance flag (NULL: all); inactive chunks are skipped
+  int32_t part;              // buffer of partial rows: 0 callers' products, 1 the solver's, 2 the gap's
+  bool whole;                // rows cut into parts as whole rows (order_parts)
 };
 
 __device__ inline int lo16(uint32_t v) { return (int)(int16_t)(v & 0xffffu); }
@@ -2485,8 +2487,17 @@ struct DBuf {
 struct DevDir {                 // the row chunks of one direction (the layouts' shared item list)
   DBuf<MvItem> items;
   DBuf<MvRed> red;              // rows summed from partial rows
-  DBuf<double> part;            // partial rows (FP32 products use the first half)
+  // partial rows: the callers' products', in their order (order_parts; FP32
+  // products use the first half); the solver's (FP32, kernels 2 and 3); the
+  // gap's, beside its gradients
+  DBuf<double> part[3];
   int nblk = 0, nred = 0;
+  // rows cut into parts, whole: copies [it0, it1) at the end of the item list
+  // of the items of the row chunks from item `first` on
+  struct Whole {
+    int32_t first, it0, it1;
+  };
+  std::vector<Whole> whole;
 };
 
 struct DevMc {                  // chunk-aligned matvec layout of one direction
@@ -2496,6 +2507,8 @@ struct DevMc {                  // chunk-aligned matvec layout of one direction
   int count[kMcClasses] = {0, 0, 0, 0, 0};
   DBuf<int32_t> chunks_act[kMcClasses];   // the solver's lists: chunks of active instances only
   int count_act[kMcClasses] = {0, 0, 0, 0, 0};
+  DBuf<int32_t> chunks_whole[kMcClasses];   // no row cut into parts
+  int count_whole[kMcClasses] = {0, 0, 0, 0, 0};
   int block = 0;                // 0: not built
 };
 
@@ -2520,8 +2533,8 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
   DBuf<double> part[2];
   // FP64 products: row chunks (DevDir::items) per class
   std::vector<int32_t> f64_h[kGrpClasses];
-  DBuf<int32_t> f64[kGrpClasses], f64_act[kGrpClasses];
-  int n_f64[kGrpClasses] = {}, n_f64_act[kGrpClasses] = {};
+  DBuf<int32_t> f64[kGrpClasses], f64_act[kGrpClasses], f64_whole[kGrpClasses];   // whole: no row cut into parts
+  int n_f64[kGrpClasses] = {}, n_f64_act[kGrpClasses] = {}, n_f64_whole[kGrpClasses] = {};
   bool built = false;
 };
 
@@ -2631,6 +2644,8 @@ struct Game {
   hipEvent_t fork_ev = nullptr, join_ev[kSide] = {};
   bool fork_ok = false;
   std::mutex fork_mu;               // the side streams and their events, one product at a time
+  std::mutex part_mu;               // DevDir::part, one product at a time:
+  hipEvent_t part_ev = nullptr;     //   recorded behind the last product that uses it
   ~Game() {
     if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
     if (graph) (void)hipGraphDestroy(graph);
@@ -2640,6 +2655,7 @@ struct Game {
       if (join_ev[i]) (void)hipEventDestroy(join_ev[i]);
     }
     if (fork_ev) (void)hipEventDestroy(fork_ev);
+    if (part_ev) (void)hipEventDestroy(part_ev);
   }
 };
 
@@ -2654,6 +2670,7 @@ constexpr int kForkMinWorkgroups = 512;
 static int ensure_fork(Game* g) {
   if (g->fork_ok) return PMX_OK;
   HIP_TRY(hipEventCreateWithFlags(&g->fork_ev, hipEventDisableTiming));
+  HIP_TRY(hipEventCreateWithFlags(&g->part_ev, hipEventDisableTiming));
   for (int i = 0; i < Game::kSide; ++i) {
     HIP_TRY(hipStreamCreateWithFlags(&g->side[i], hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&g->join_ev[i], hipEventDisableTiming));
@@ -2704,6 +2721,25 @@ static int upload_mc_active(Game* g, int d) {
   return PMX_OK;
 }
 
+// A class's row chunks with the rows cut into parts as whole rows (first: they
+// take longest).
+static std::vector<int32_t> whole_chunks(const Game* g, int d, const std::vector<int32_t>& F) {
+  const MvDir& D = g->hg.dir[d];
+  const std::vector<DevDir::Whole>& W = g->dd[d].whole;   // by `first`
+  std::vector<int32_t> L, rest;
+  for (size_t i = 0; i + 3 < F.size(); i += 4) {
+    if (D.items[F[i + 1] - 1].last != 2) {
+      rest.insert(rest.end(), F.begin() + i, F.begin() + i + 4);
+      continue;
+    }
+    const auto w = std::lower_bound(W.begin(), W.end(), F[i],
+                                    [](const DevDir::Whole& a, int32_t it) { return a.first < it; });
+    if (w != W.end() && w->first == F[i]) L.insert(L.end(), {w->it0, w->it1, F[i + 2], F[i + 3]});
+  }
+  L.insert(L.end(), rest.begin(), rest.end());
+  return L;
+}
+
 static int upload_mc(Game* g, int d) {
   HostGame& hg = g->hg;
   DevMc& E = g->dm[d];
@@ -2733,6 +2769,9 @@ static int upload_mc(Game* g, int d) {
   for (int c = 0; c < kMcClasses; ++c) {
     if ((rc = E.chunks[c].upload(M.chunks[c]))) return rc;
     E.count[c] = (int)M.chunks[c].size() / 4;
+    const std::vector<int32_t> L = g->dd[d].nred ? whole_chunks(g, d, M.chunks[c]) : std::vector<int32_t>();
+    if ((rc = E.chunks_whole[c].upload(L))) return rc;
+    E.count_whole[c] = (int)L.size() / 4;
   }
   E.block = block;
   return upload_mc_active(g, d);
@@ -2892,6 +2931,9 @@ static int upload_grp(Game* g, int d) {
     if ((rc = E.cut[c].upload(E.cut_h[c])) || (rc = E.f64[c].upload(E.f64_h[c]))) return rc;
     E.n_cut[c] = (int)E.cut_h[c].size() / 4;
     E.n_f64[c] = (int)E.f64_h[c].size() / 4;
+    const std::vector<int32_t> L = g->dd[d].nred ? whole_chunks(g, d, E.f64_h[c]) : std::vector<int32_t>();
+    if ((rc = E.f64_whole[c].upload(L))) return rc;
+    E.n_f64_whole[c] = (int)L.size() / 4;
   }
   for (int kind = 0; kind < GrpDir::kKinds; ++kind)
     for (int c = 0; c < kGrpClasses; ++c) {
@@ -2907,11 +2949,32 @@ static int upload_dir(Game* g, int d) {
   HostGame& hg = g->hg;
   const MvDir& D = hg.dir[d];
   DevDir& E = g->dd[d];
-  if ((rc = E.items.upload(D.items))) return rc;
+  std::vector<MvItem> items = D.items;
+  E.whole.clear();
+  size_t row = 0;
+  for (size_t b = 0; b + 1 < D.blk.size(); ++b) {
+    if (D.items[D.blk[b + 1] - 1].last != 2) continue;
+    // the row's parts are successive chunks
+    const MvRed& r = D.red[row++];
+    const int first = D.blk[b], end = D.blk[b + r.n_parts], to = (int)items.size();
+    for (int it = first; it < end; ++it) {
+      MvItem m = D.items[it];
+      m.out = r.out;
+      m.last = it + 1 == end ? 1 : 0;
+      m.run_end += to - first;
+      items.push_back(m);
+    }
+    E.whole.push_back({first, to, (int32_t)items.size()});
+    b += r.n_parts - 1;
+  }
+  if ((rc = E.items.upload(items))) return rc;
   E.nblk = (int)D.blk.size() - 1;
   if ((rc = E.red.upload(D.red))) return rc;
   E.nred = (int)D.red.size();
-  if ((rc = E.part.alloc((size_t)std::max<int64_t>(D.part_elems, 1)))) return rc;
+  if ((rc = E.part[0].alloc((size_t)D.part_elems)) ||
+      (rc = E.part[1].alloc(hg.mv_kernel == 4 ? 0 : (size_t)(D.part_elems + 1) / 2)) ||
+      (rc = E.part[2].alloc((size_t)D.part_elems)))
+    return rc;
   if ((rc = upload_grp(g, d))) return rc;   // also the contexts of the FP64 products
   g->dm[d].block = 0;
   return hg.mv_kernel == 4 ? PMX_OK : upload_mc(g, d);
@@ -3145,6 +3208,8 @@ static MvParams mv_params(Game* g, int d, double scale) {
   P.scale = scale;
   P.dir = d;
   P.active = nullptr;
+  P.part = 0;
+  P.whole = false;
   P.nblk = g->dd[d].nblk;
   return P;
 }
@@ -3156,16 +3221,16 @@ static McParams mc_params(Game* g, int d, const MvParams& like, int c) {
   // the solver's launches (active flags set) take the lists without retired
   // instances
   const bool solver = like.active != nullptr;
-  P.chunks = (const int4*)(solver ? E.chunks_act[c].p : E.chunks[c].p);
+  P.chunks = (const int4*)(like.whole ? E.chunks_whole[c].p : solver ? E.chunks_act[c].p : E.chunks[c].p);
   P.ctx = E.ctx.p;
   P.q = (const uint4*)E.q.p;
   P.pos = (const uint2*)E.pos.p;
   P.meta = E.meta.p;
   P.lamf = g->lamf.p;
   P.active = like.active;
-  P.part = g->dd[d].part.p;
+  P.part = g->dd[d].part[like.part].p;
   P.scale = like.scale;
-  P.nchunk = like.nblk > 0 ? (solver ? E.count_act[c] : E.count[c]) : 0;
+  P.nchunk = like.nblk > 0 ? (like.whole ? E.count_whole[c] : solver ? E.count_act[c] : E.count[c]) : 0;
   return P;
 }
 
@@ -3262,15 +3327,43 @@ static int fork_launches(Game* g, hipStream_t s, int n, const int64_t* work_in, 
   return PMX_OK;
 }
 
+// Rows of a direction that a launch sums from partial rows.
+static int part_rows(const Game* g, const MvParams& P) { return P.nblk > 0 && !P.whole ? g->dd[P.dir].nred : 0; }
+
 // Rows cut into parts: sum the partial rows (after the join into s).
 template <typename IO>
 static void launch_mv_reduce(Game* g, const MvParams& P0, IO* out0, const MvParams& P1, IO* out1, int n_launched,
                              hipStream_t s) {
-  const int nr0 = P0.nblk > 0 ? g->dd[P0.dir].nred : 0, nr1 = P1.nblk > 0 ? g->dd[P1.dir].nred : 0;
+  const int nr0 = part_rows(g, P0), nr1 = part_rows(g, P1);
+  auto part = [&](const MvParams& P) { return (const IO*)g->dd[P.dir].part[P.part].p; };
   if (n_launched > 0 && nr0 + nr1 > 0)
-    hipLaunchKernelGGL((k_mv_reduce<IO>), dim3(nr0 + nr1), dim3(256), 0, s, g->dd[P0.dir].red.p, nr0,
-                       (const IO*)g->dd[P0.dir].part.p, out0, g->dd[P1.dir].red.p,
-                       (const IO*)g->dd[P1.dir].part.p, out1, P0.active);
+    hipLaunchKernelGGL((k_mv_reduce<IO>), dim3(nr0 + nr1), dim3(256), 0, s, g->dd[P0.dir].red.p, nr0, part(P0), out0,
+                       g->dd[P1.dir].red.p, part(P1), out1, P0.active);
+}
+
+// Enqueues a product that may write partial rows.  A product of the caller's
+// that does writes them to the game's buffer, behind the last such product on
+// whatever stream that was: an event is recorded behind each and waited for by
+// the next (3 us a product; the side stream that orders the grouped kernel's
+// terms would cost a fork and a join).  Replays of a captured product may
+// overlap anything, so a captured one leaves its rows whole (FP64 pair of the
+// turn + river game: 418 us cut, 436 us whole; with 24 cards 78 and 98 us).
+// The solver's products follow one another as its state does, and the gap's
+// as its gradients do.
+template <typename F>
+static int order_parts(Game* g, MvParams& P0, MvParams& P1, hipStream_t s, F&& enqueue) {
+  if (P0.part != 0 || part_rows(g, P0) + part_rows(g, P1) == 0) return enqueue();
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &st));
+  if (st != hipStreamCaptureStatusNone) {
+    for (MvParams* P : {&P0, &P1}) P->whole = part_rows(g, *P) > 0;
+    return enqueue();
+  }
+  std::lock_guard<std::mutex> lock(g->part_mu);
+  HIP_TRY(hipStreamWaitEvent(s, g->part_ev, 0));
+  const int rc = enqueue();
+  HIP_TRY(hipEventRecord(g->part_ev, s));
+  return rc;
 }
 
 template <typename IO>
@@ -3480,7 +3573,7 @@ static DParams mvd_params(Game* g, int d, const MvParams& like, int c) {
   const bool listed = like.active != nullptr;
   DParams P;
   P.items = g->dd[d].items.p;
-  P.chunks = (const int4*)(listed ? E.f64_act[c].p : E.f64[c].p);
+  P.chunks = (const int4*)(like.whole ? E.f64_whole[c].p : listed ? E.f64_act[c].p : E.f64[c].p);
   P.ctx = E.ctx.p;
   P.q = (const uint4*)E.q.p;
   P.rk = E.rk.p;
@@ -3488,9 +3581,9 @@ static DParams mvd_params(Game* g, int d, const MvParams& like, int c) {
   P.meta = E.meta.p;
   P.lam = g->lam.p;
   P.active = like.active;
-  P.part = g->dd[d].part.p;
+  P.part = g->dd[d].part[like.part].p;
   P.scale = like.scale;
-  P.nchunk = like.nblk > 0 ? (listed ? E.n_f64_act[c] : E.n_f64[c]) : 0;
+  P.nchunk = like.nblk > 0 ? (like.whole ? E.n_f64_whole[c] : listed ? E.n_f64_act[c] : E.n_f64[c]) : 0;
   return P;
 }
 
@@ -3536,12 +3629,12 @@ static int launch_mv(Game* g, MvParams P0, const float* in0, float* out0, MvPara
   if (g->hg.mv_kernel < 2 || g->hg.mv_kernel > 4) return fail(PMX_ESTATE, "no matvec schedule set");
   if (mc_lds_max(g) > (size_t)g->max_lds)
     return fail(PMX_EINVAL, "matvec workgroup needs more LDS than this device gives a workgroup");
-  return launch_mc<float>(g, P0, in0, out0, P1, in1, out1, s, tick);
+  return order_parts(g, P0, P1, s, [&]() { return launch_mc<float>(g, P0, in0, out0, P1, in1, out1, s, tick); });
 }
 static int launch_mv(Game* g, MvParams P0, const double* in0, double* out0, MvParams P1, const double* in1,
                      double* out1, hipStream_t s) {
   if (P0.nblk + P1.nblk == 0) return PMX_OK;
-  return launch_mvd(g, P0, in0, out0, P1, in1, out1, s);
+  return order_parts(g, P0, P1, s, [&]() { return launch_mvd(g, P0, in0, out0, P1, in1, out1, s); });
 }
 
 static MvParams empty_params(const MvParams& like) {
@@ -4216,6 +4309,7 @@ static int enqueue_iteration(Game* g, const float* const in[2], float* const out
   int rc;
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, -1.0);
   PA.active = PT.active = g->active.p;
+  PA.part = PT.part = 1;
   if ((rc = launch_mv(g, PA, in[1], g->grad[0].p, empty_params(PA), nullptr, nullptr, s, g->tdev.p))) return rc;
   if ((rc = rm_update(g, 0, out[0], s))) return rc;
   if ((rc = launch_mv(g, PT, out[0], g->grad[1].p, empty_params(PT), nullptr, nullptr, s))) return rc;
@@ -4373,6 +4467,7 @@ static int gap_launches(Game* g, const double* xsum, const double* ysum, const i
                         const GapBufs& B) {
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, 1.0);
   PA.active = PT.active = need_dev;
+  PA.part = PT.part = 2;
   const int rc = launch_mv(g, PA, ysum, B.gd[0], PT, xsum, B.gd[1], s);
   return rc ? rc : br_values(g, B.gd, B.br, s, need_dev);
 }

@@ -50,3 +50,90 @@ def test_padding_of_a_loaded_plan(kind, steps):
         for k in ("regret", "plan", "avg_sum"):
             assert np.array_equal(s[k][~pads[p]], t[k][~pads[p]]), (p, k)
     assert np.array_equal(clean.saddle_gap()[0], dirty.saddle_gap()[0])
+
+
+# products of one game on two streams, with other inputs each and nothing
+# between them that waits: rows over many board contexts go through buffers of
+# the game's own.  FP32 on the grouped schedule (terms) and on both others
+# (partial rows), FP64 (partial rows); beside a solver that runs on a third
+# stream, and beside replays of captured products
+TURN = [("one_class", lambda: I.small_turn_river(3, deck_size=23, n_board=3, cards_per_hand=2, bet_fracs=(0.5,),
+                                                 max_raises=1, stack=12.0, zero_frac=0.2)),
+        ("two_classes", lambda: [I.small_turn_river(4, deck_size=14, n_board=3, cards_per_hand=2, stack=9.0),
+                                 I.small_turn_river(5, deck_size=30, n_board=4, cards_per_hand=2, stack=9.0)])]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("tune", [None, (2, 2), (3, 1)])
+@pytest.mark.parametrize("name,fn", TURN, ids=[c[0] for c in TURN])
+def test_products_on_several_streams(name, fn, tune, dtype):
+    g, n = _game(fn()), 12
+    if tune:
+        g.game_tune(*tune)
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    x, y = (torch.rand((n, g.elems[p]), generator=gen, device="cuda", dtype=dtype) for p in range(2))
+    prods = (g.matvec_A_f64, g.matvec_AT_f64) if dtype == torch.float64 else (g.matvec_A, g.matvec_AT)
+    ref = [torch.full_like(x, 7.0), torch.full_like(y, 7.0)]
+    for i in range(n):
+        prods[0](y[i], ref[0][i])
+        prods[1](x[i], ref[1][i])
+        torch.cuda.synchronize()
+    # captured products: the caller's streams again may replay them beside others
+    cap, graph = [torch.full_like(x[0], 7.0), torch.full_like(y[0], 7.0)], torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        prods[0](y[0], cap[0])
+        prods[1](x[0], cap[1])
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    out = [torch.full_like(x, 7.0), torch.full_like(y, 7.0)]
+    torch.cuda.synchronize()
+    for rounds in range(3):
+        for v in out + cap:
+            v.fill_(7.0)
+        torch.cuda.synchronize()
+        for i in range(n):
+            with torch.cuda.stream(streams[i % 2]):
+                prods[0](y[i], out[0][i])
+                prods[1](x[i], out[1][i])
+            if i % 4 == 1:
+                with torch.cuda.stream(streams[2]):
+                    g.solver_step(1)
+                with torch.cuda.stream(streams[3]):
+                    graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], ref[0]) and torch.equal(out[1], ref[1])
+        # a captured product sums a row without cutting it: rounding of the
+        # partial rows (FP32 on schedules 2 and 3), up to a sum's magnitude
+        for got, want in zip(cap, ref):
+            tol = 1e-13 if dtype == torch.float64 else 1e-6
+            assert ((got - want[0]).abs() <= tol * want[0].abs().max()).all()
+    # the solver's own products were not disturbed either
+    h = _game(fn())
+    if tune:
+        h.game_tune(*tune)
+    for _ in range(9):
+        h.solver_step(1)
+    torch.cuda.synchronize()
+    for p in range(2):
+        s, t = g.solver_get_state(p), h.solver_get_state(p)
+        assert all(np.array_equal(s[k], t[k]) for k in ("regret", "plan", "avg_sum"))
+
+
+# a batch of turn games with retired instances: the solver's lists of cut rows
+# without them give what the instances give alone
+@pytest.mark.parametrize("active", [[1, 0, 1, 0], [0, 0, 1, 0]])
+def test_cut_rows_of_active_instances(active):
+    descs = [I.small_turn_river(s, deck_size=20, n_board=3, cards_per_hand=2, stack=9.0) for s in range(4)]
+    g = _game(descs)
+    g.solver_step(6)
+    g.solver_set_active(active)
+    g.solver_step(40)
+    torch.cuda.synchronize()
+    for i, on in enumerate(active):
+        h = _game([descs[i]] * 4)   # the same schedules: a batch of copies
+        h.solver_step(46 if on else 6)
+        torch.cuda.synchronize()
+        for p in range(2):
+            s, t = g.solver_get_state(p), h.solver_get_state(p)
+            for k in ("regret", "plan", "avg_sum"):
+                assert np.array_equal(g.unpack(p, s[k])[i], h.unpack(p, t[k])[0]), (i, p, k)
+        h.close()
