@@ -475,7 +475,7 @@ int mlp_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, int32_t ld
  * BF16 rows X [M][64]: BF16 weights W1 [512][64], W2 [512][512], W3 [8][512],
  * FP32 biases, hidden activations rounded to BF16 as by mlp_gemm_bf16, FP32
  * accumulation.  work: device scratch of 512 * 512 BF16 values.  Inputs and
- * scratch 16-byte aligned. */
+ * scratch 16-byte aligned.  M = 0: nothing to do, whatever the pointers. */
 int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* W2,
                      const float* b2, const uint16_t* W3, const float* b3, float* Z, uint16_t* work,
                      void* stream);

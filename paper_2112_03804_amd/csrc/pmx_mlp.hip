@@ -974,12 +974,12 @@ static constexpr int64_t kNetLargeRows = 8192;
 
 int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* W2,
                      const float* b2, const uint16_t* W3, const float* b3, float* Z, uint16_t* work, void* stream) {
+  if (M == 0) return PMX_OK;   // buffers of no rows may have no address
   if (M < 0 || !X || !W1 || !b1 || !W2 || !b2 || !W3 || !b3 || !Z || !work)
     return mfail(PMX_EINVAL, "bad network arguments");
   const uintptr_t all = (uintptr_t)X | (uintptr_t)W1 | (uintptr_t)b1 | (uintptr_t)W2 | (uintptr_t)b2 | (uintptr_t)W3 |
                         (uintptr_t)work;
   if (all % 16) return mfail(PMX_EINVAL, "network buffers must be 16-byte aligned");
-  if (M == 0) return PMX_OK;
   hipStream_t s = (hipStream_t)stream;
   const NetArgs P{M, X, W1, W2, W3, b1, b2, b3, Z};
   auto lds = [](int rows) { return sizeof(uint16_t) * (size_t)rows * (NetPitch + NetIn + 8); };

@@ -157,7 +157,7 @@ class WarmMLP:
         or, for rows not aligned to 16 bytes, layer by layer in chunks."""
         torch = _torch()
         out = torch.empty((M, K), dtype=torch.float32, device="cuda")
-        if Xb.data_ptr() % 16 == 0:
+        if M > 0 and Xb.data_ptr() % 16 == 0:
             if "pack" not in self._ws_net:
                 self._ws_net["pack"] = torch.empty((WIDTH * WIDTH,), dtype=torch.bfloat16, device="cuda")
             p, pb, d = self.p, self.pb, pmx.dptr

@@ -16,6 +16,16 @@ def _game(d):
     return pmx.Game(d)
 
 
+def _net(seed):
+    _game(I.tiny_config()).close()
+    from paper_2112_03804_amd import warmstart
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    net = warmstart.WarmMLP(seed=seed)
+    for k in ("b1", "b2", "b3"):
+        net.p[k].copy_(0.2 * torch.randn(net.p[k].shape, generator=gen, device="cuda"))
+    return net, gen
+
+
 # entries past a row's hands are ignored on input and written as 0 on output:
 # a plan loaded with anything there leaves no trace in the averages
 @pytest.mark.parametrize("steps", [1, 3, 40])
@@ -137,3 +147,17 @@ def test_cut_rows_of_active_instances(active):
             for k in ("regret", "plan", "avg_sum"):
                 assert np.array_equal(g.unpack(p, s[k])[i], h.unpack(p, t[k])[0]), (i, p, k)
         h.close()
+
+
+# no rows: an empty result, as a loop over no chunks gives
+def test_inference_of_no_rows():
+    net, _ = _net(1)
+    from paper_2112_03804_amd import pmx, warmstart
+    X = torch.empty((0, warmstart.D_IN), dtype=torch.bfloat16, device="cuda")
+    out = net.logits(X, 0)
+    assert out.shape == (0, warmstart.K) and out.dtype == torch.float32
+    assert net.logits(torch.zeros((5, warmstart.D_IN), dtype=torch.bfloat16, device="cuda"), 0).shape[0] == 0
+    # through the ABI: nothing to do, whatever the row pointers are
+    d, p, pb = pmx.dptr, net.p, net.pb
+    assert pmx.lib().mlp_forward_bf16(0, None, d(pb["W1"]), d(p["b1"]), d(pb["W2"]), d(p["b2"]), d(pb["W3"]),
+                                      d(p["b3"]), None, None, pmx.stream_ptr()) == 0
