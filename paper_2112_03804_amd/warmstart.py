@@ -31,6 +31,11 @@ def _torch():
     return torch
 
 
+def _aligned(*tensors) -> bool:
+    """Whether the fused kernels' 16-byte loads and stores may be used."""
+    return all(t.data_ptr() % 16 == 0 for t in tensors)
+
+
 class WarmMLP:
     """Network parameters (FP32 master + BF16 copies) and Adam state on the GPU."""
 
@@ -108,10 +113,11 @@ class WarmMLP:
 
     def loss_and_grad(self, Xb, T, Wt, M: int):
         """Weighted masked cross-entropy of a batch and the parameter gradients
-        (left in self.g); returns the loss summed over rows.  Rows not
-        aligned to 16 bytes, and an empty batch, go layer by layer."""
+        (left in self.g); returns the loss summed over rows.  Rows, weights or
+        weight gradients not aligned to 16 bytes, and an empty batch, go layer
+        by layer."""
         L = pmx.lib()
-        if M > 0 and Xb.data_ptr() % 16 == 0:
+        if M > 0 and _aligned(Xb, *self.pb.values(), *(self.g[k] for k in self.pb)):
             torch, ws, d = _torch(), self._ws_net, pmx.dptr
             if ws.get("M", 0) < M:
                 need = L.mlp_loss_and_grad_work(M)
@@ -154,10 +160,11 @@ class WarmMLP:
 
     def logits(self, Xb, M: int, chunk: int = 1 << 20):
         """Logits for M rows (inference): one kernel for the whole network,
-        or, for rows not aligned to 16 bytes, layer by layer in chunks."""
+        or, for rows or parameters not aligned to 16 bytes, layer by layer in
+        chunks."""
         torch = _torch()
         out = torch.empty((M, K), dtype=torch.float32, device="cuda")
-        if M > 0 and Xb.data_ptr() % 16 == 0:
+        if M > 0 and _aligned(Xb, *self.pb.values(), self.p["b1"], self.p["b2"]):
             if "pack" not in self._ws_net:
                 self._ws_net["pack"] = torch.empty((WIDTH * WIDTH,), dtype=torch.bfloat16, device="cuda")
             p, pb, d = self.p, self.pb, pmx.dptr

@@ -161,3 +161,40 @@ def test_inference_of_no_rows():
     d, p, pb = pmx.dptr, net.p, net.pb
     assert pmx.lib().mlp_forward_bf16(0, None, d(pb["W1"]), d(p["b1"]), d(pb["W2"]), d(p["b2"]), d(pb["W3"]),
                                       d(p["b3"]), None, None, pmx.stream_ptr()) == 0
+
+
+# every parameter and gradient at an odd offset of one flat buffer, as
+# programs that flatten their parameters keep them
+@pytest.mark.parametrize("rows", [1, 77, 700])
+@pytest.mark.parametrize("which", ["p", "pb", "g"])
+def test_parameters_in_a_flat_buffer(which, rows):
+    net, gen = _net(rows)
+    from paper_2112_03804_amd import warmstart
+    X = torch.randn((rows, warmstart.D_IN), generator=gen, device="cuda").to(torch.bfloat16)
+    T = torch.rand((rows, warmstart.K), generator=gen, device="cuda")
+    T = (T / T.sum(dim=1, keepdim=True)).contiguous()
+    W = torch.rand((rows,), generator=gen, device="cuda")
+    ref = net.forward(X, rows).clone()
+    ref_loss = net.loss_and_grad(X, T, W, rows).clone()
+    ref_g = {k: v.clone() for k, v in net.g.items()}
+    d = getattr(net, which)
+    flat = torch.empty(sum(v.numel() for v in d.values()) + 1, dtype=next(iter(d.values())).dtype, device="cuda")
+    at = 1   # lengths are multiples of 8: every view starts one value past a 16-byte boundary
+    for k, v in d.items():
+        view = flat[at:at + v.numel()].view(v.shape)
+        view.copy_(v)
+        d[k] = view
+        at += v.numel()
+    assert all(v.data_ptr() % 16 for v in d.values())
+    got = net.logits(X, rows)
+    loss = net.loss_and_grad(X, T, W, rows)
+    # the kernels of either path round the same values to BF16 and differ by
+    # the order of FP32 sums, and by the rare value rounded the other way
+    assert ((got - ref).norm() <= 2e-3 * ref.norm())
+    assert ((loss - ref_loss).abs() <= 1e-4 * ref_loss.abs()).all()
+    for k in ref_g:
+        assert (net.g[k] - ref_g[k]).norm() <= 2e-3 * ref_g[k].norm(), k
+    before = {k: v.clone() for k, v in net.p.items()}
+    net.adam(lr=1e-3)
+    assert all(not torch.equal(before[k], net.p[k]) for k in before)
+    assert all(torch.equal(net.p[k].to(torch.bfloat16), net.pb[k]) for k in net.pb)
