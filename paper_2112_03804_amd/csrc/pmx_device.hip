@@ -2529,6 +2529,7 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
   int n_cut[kGrpClasses] = {}, n_cut_act[kGrpClasses] = {};
   DBuf<GRed> red;
   int n_red = 0, red_blocks = 0;
+  size_t n_term = 0;            // length of a term buffer
   double cut_us = 0;            // estimated time of the longest sequence when it is carried
   DBuf<double> part[2];
   // FP64 products: row chunks (DevDir::items) per class
@@ -2576,8 +2577,9 @@ struct Game {
   std::vector<int64_t> lam_off[2];   // per player: offset of each instance's lambdas
   // solver state
   DBuf<float> R[2], x[2], grad[2];
-  DBuf<float> ring[2];              // plans 1 .. avg_seg - 1 of a segment (k_avg)
+  DBuf<float> ring[2];              // plans 1 .. avg_seg - 1 of a segment (k_avg; ensure_ring)
   int avg_seg = 1;                  // iterations per segment at most
+  bool ring_ready = false;
   DBuf<AvgChunk> avg_chunk[2];
   int n_avg[2] = {0, 0};
   DBuf<double> xs[2], gd[2], sd[2], br_inst;
@@ -2893,9 +2895,8 @@ static int cut_sequences(Game* g, int d, std::vector<GGroup>& groups) {
       }
   E.n_red = (int)red.size();
   E.red_blocks = (max_stride + 255) / 256;
-  int rc = E.red.upload(red);
-  for (int k = 0; k < 2 && !rc; ++k) rc = E.part[k].alloc((size_t)elems);
-  return rc;
+  E.n_term = (size_t)elems;
+  return E.red.upload(red);
 }
 
 static int upload_grp(Game* g, int d) {
@@ -2972,8 +2973,7 @@ static int upload_dir(Game* g, int d) {
   if ((rc = E.red.upload(D.red))) return rc;
   E.nred = (int)D.red.size();
   if ((rc = E.part[0].alloc((size_t)D.part_elems)) ||
-      (rc = E.part[1].alloc(hg.mv_kernel == 4 ? 0 : (size_t)(D.part_elems + 1) / 2)) ||
-      (rc = E.part[2].alloc((size_t)D.part_elems)))
+      (rc = E.part[1].alloc(hg.mv_kernel == 4 ? 0 : (size_t)(D.part_elems + 1) / 2)))
     return rc;
   if ((rc = upload_grp(g, d))) return rc;   // also the contexts of the FP64 products
   g->dm[d].block = 0;
@@ -3079,7 +3079,21 @@ static int upload_rm(Game* g, int p) {
   return E.stage.alloc((size_t)std::max(T.n_slot, 1) * E.stage_stride);
 }
 
-static void fill_f32(float* p, int64_t n, float v, hipStream_t s);
+// Buffers that only make products faster, after everything a game needs: the
+// terms of cut sequences (without them they are carried) and the gap's partial
+// rows (without them its rows stay whole).
+static void alloc_terms(Game* g) {
+  for (int d = 0; d < 2; ++d) {
+    DevGrp& E = g->dg[d];
+    if (E.n_red && (E.part[0].alloc(E.n_term) || E.part[1].alloc(E.n_term))) {
+      for (auto& b : E.part) (void)b.alloc(0);
+      E.n_red = 0;
+    }
+    (void)g->dd[d].part[2].alloc((size_t)g->hg.dir[d].part_elems);
+  }
+  (void)hipGetLastError();   // of an allocation that did not fit
+  g_err.clear();
+}
 
 static int upload_game(Game* g) {
   HostGame& hg = g->hg;
@@ -3126,14 +3140,7 @@ static int upload_game(Game* g) {
         (rc = g->xs[p].alloc(n)) || (rc = g->gd[p].alloc(n)) || (rc = g->sd[p].alloc(n)))
       return rc;
   }
-  // segments of the running averages: 32 iterations while the plans are small
-  // (one launch per solver graph or check), else 8 (28 bytes per element, and
-  // the sums cost 6 bytes per element and iteration instead of 20)
-  g->avg_seg = hg.elems[0] + hg.elems[1] <= (1 << 18) ? 32 : 8;
   for (int p = 0; p < 2; ++p) {
-    const size_t n = (size_t)hg.elems[p];
-    if ((rc = g->ring[p].alloc(n * (g->avg_seg - 1)))) return rc;
-    fill_f32(g->ring[p].p, (int64_t)(n * (g->avg_seg - 1)), 0.f, nullptr);   // padding stays 0
     std::vector<AvgChunk> ch;
     for (size_t i = 0; i < hg.inst.size(); ++i) {
       const int64_t b = hg.inst[i].vec_off[p], e = b + (int64_t)hg.inst[i].sf.n_seq[p] * hg.inst[i].stride[p];
@@ -3197,6 +3204,7 @@ static int upload_game(Game* g) {
   std::vector<double> pots;
   for (auto& b : hg.inst) pots.push_back(2.0 * b.inst.contrib);
   if ((rc = g->pot_inst.upload(pots))) return rc;
+  alloc_terms(g);
   return PMX_OK;
 }
 
@@ -3976,6 +3984,7 @@ int game_tune(Game* g, int32_t kernel, int32_t rows_per_chunk) {
     build_matvec_plan(g->hg, d, g->hg.rows_per_block);
     if ((rc = upload_dir(g, d))) return rc;
   }
+  alloc_terms(g);
   return PMX_OK;
 }
 
@@ -4317,6 +4326,35 @@ static int enqueue_iteration(Game* g, const float* const in[2], float* const out
   return PMX_OK;
 }
 
+// The plans of a segment of the running averages, taken by the first
+// solver_step (games made for products and gaps only don't hold them):
+// segments of 32 iterations while the plans are small (one k_avg launch per
+// solver graph or check), else of 8 (28 bytes per element, and the sums cost 6
+// bytes per element and iteration instead of 20), or shorter ones where memory
+// does not last.  None are taken while the stream is captured.
+static int ensure_ring(Game* g, hipStream_t s) {
+  if (g->ring_ready) return PMX_OK;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  HIP_TRY(hipStreamIsCapturing(s, &st));
+  if (st != hipStreamCaptureStatusNone) return PMX_OK;
+  // another thread's capture does not concern these allocations
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+  const int64_t* const n = g->hg.elems;
+  int seg = n[0] + n[1] <= (1 << 18) ? 32 : 8;
+  while (seg > 1 && (g->ring[0].alloc((size_t)n[0] * (seg - 1)) || g->ring[1].alloc((size_t)n[1] * (seg - 1)))) {
+    for (auto& r : g->ring) (void)r.alloc(0);
+    seg /= 2;
+  }
+  (void)hipGetLastError();   // of an allocation that did not fit
+  g_err.clear();
+  HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode));
+  for (int p = 0; p < 2; ++p) fill_f32(g->ring[p].p, n[p] * (seg - 1), 0.f, s);   // padding stays 0
+  g->avg_seg = seg;
+  g->ring_ready = true;
+  return PMX_OK;
+}
+
 // A segment of m <= avg_seg iterations: iteration i writes the plans to buffer
 // i, the last one back to the plans' own buffer, whose old content (the
 // segment's first plan) k_avg has taken by then with the others.  Between
@@ -4385,6 +4423,7 @@ int solver_step(Game* g, int32_t n_iters, void* stream) {
   if (rc) return rc;
   if (n_iters < 0) return fail(PMX_EINVAL, "n_iters must be >= 0");
   hipStream_t s = (hipStream_t)stream;
+  if (n_iters > 0 && (rc = ensure_ring(g, s))) return rc;
   int left = n_iters;
   if (g->use_graph && left >= kGraphIters) {
     if ((rc = capture_graph(g))) return rc;
@@ -4468,6 +4507,7 @@ static int gap_launches(Game* g, const double* xsum, const double* ysum, const i
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, 1.0);
   PA.active = PT.active = need_dev;
   PA.part = PT.part = 2;
+  for (MvParams* P : {&PA, &PT}) P->whole = g->dd[P->dir].nred > 0 && !g->dd[P->dir].part[2].p;
   const int rc = launch_mv(g, PA, ysum, B.gd[0], PT, xsum, B.gd[1], s);
   return rc ? rc : br_values(g, B.gd, B.br, s, need_dev);
 }

@@ -198,3 +198,52 @@ def test_parameters_in_a_flat_buffer(which, rows):
     net.adam(lr=1e-3)
     assert all(not torch.equal(before[k], net.p[k]) for k in before)
     assert all(torch.equal(net.p[k].to(torch.bfloat16), net.pb[k]) for k in net.pb)
+
+
+# the plans that the averages take together (28 bytes per element in segments
+# of eight iterations) are allocated by the first solver step, as many as fit:
+# a game that only just fits still solves, to the same bits
+def test_solver_memory():
+    descs = I.batched_configs(160, seed=2)
+    g = _game(descs)
+    free = lambda: torch.cuda.mem_get_info()[0]
+    torch.cuda.synchronize()
+    f0 = free()
+    h = _game(descs)
+    torch.cuda.synchronize()
+    made = f0 - free()
+    seg = 28 * sum(h.elems)
+    assert seg > 200 << 20
+    x, y = (torch.rand(n, device="cuda") for n in h.elems)
+    Ay, ATx = torch.empty_like(x), torch.empty_like(y)
+    f1 = free()
+    h.matvec_pair(y, x, Ay, ATx)
+    torch.cuda.synchronize()
+    assert f1 - free() < seg // 4
+    h.solver_step(40)
+    torch.cuda.synchronize()
+    assert f1 - free() > seg - (16 << 20)
+    ref = [h.solver_get_state(p) for p in range(2)]
+    h.close()
+    g.close()
+    torch.cuda.empty_cache()
+    # room for a game and less than half of its segments
+    room, hog = made + int(0.45 * seg), []
+    for _ in range(4):   # memory given back may be counted late
+        if free() > room + (8 << 20):
+            hog.append(torch.empty(free() - room, dtype=torch.uint8, device="cuda"))
+            torch.cuda.synchronize()
+    print("left", free() >> 20, "MB, game", made >> 20, "MB, segments", seg >> 20, "MB", flush=True)
+    assert room - seg // 8 < free() < room + seg // 8
+    g = _game(descs)
+    before = free()
+    g.solver_step(3)
+    g.solver_step(37)
+    torch.cuda.synchronize()
+    assert before - free() < seg // 2
+    for p in range(2):
+        st = g.solver_get_state(p)
+        assert all(np.array_equal(st[k], ref[p][k]) for k in ("regret", "plan", "avg_sum"))
+    g.close()
+    del hog
+    torch.cuda.empty_cache()
