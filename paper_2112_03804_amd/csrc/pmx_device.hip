@@ -43,6 +43,7 @@
 #include <memory>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "pmx_internal.hpp"
@@ -1350,6 +1351,8 @@ struct RmParams {
   int32_t max_rows, max_ext;    // LDS layout of the launch
   int32_t dcfr;
   float alpha, beta;
+  double* xs;                   // AVG: running averages, and their weights' power
+  int32_t gamma;
 };
 // Block of a workgroup: the hardware deals workgroups to the eight XCDs in
 // turn, so that neighbouring hands of one piece (blocks are listed piece by
@@ -1545,9 +1548,10 @@ __device__ inline void rm_merge(float* __restrict__ rsm, int grpv, int col, bool
 // MODE 0: bottom-up and top-down of a piece with no external parent (pulls
 // from deeper pieces first); 1: bottom-up of a deep piece (root values to the
 // stage buffer); 2: top-down of a deep piece (parent weights from x).  The
-// previous plan is not read: k_avg takes the plans into the running average.
-// DC: discounted CFR regrets (else RM+).
-template <int MODE, bool DC>
+// previous plan is not read: k_avg takes the plans into the running average;
+// AVG (segments of one iteration, without a k_avg launch): the pass that
+// overwrites the plan does.  DC: discounted CFR regrets (else RM+).
+template <int MODE, bool DC, bool AVG>
 __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict__ g, float* __restrict__ R,
                                                   float* __restrict__ x, float* __restrict__ stage,
                                                   const double* __restrict__ tdev) {
@@ -1582,6 +1586,9 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
   // loads at in-bounds hands (clamped) of the wavefront's rows, all issued
   // before the first is waited for (the rows past the piece's end are not
   // loaded: a uniform exit, no wait)
+  constexpr bool AV = AVG && MODE != 1;
+  float c[AV ? RMR : 1];                    // the old plan and its running average
+  double d[AV ? RMR : 1];
   {
     float a[RMR], b[RMR];
     const int64_t cbase = T.vec_base + (act ? h : T.n_hands - 1);
@@ -1592,6 +1599,10 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
       const int64_t idx = cbase + (int64_t)row_id(r) * stride;
       if (MODE != 2) a[k] = g[idx];
       b[k] = R[idx];
+      if (AV) {
+        c[k] = x[idx];
+        d[k] = P.xs[idx];
+      }
     }
     if (MODE == 2 && wv == 0 && T.n_ext > 0) {
       // parent weights of the external parents, all loads in flight at once
@@ -1660,6 +1671,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
   }
   __syncthreads();
   if (act) {
+    const double w = AV ? avg_weight(P.gamma, *tdev) : 0.0;
     // all LDS reads first, then the stores
     float a[RMR], b[RMR];
 #pragma unroll
@@ -1675,6 +1687,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmp(RmParams P, float* __restrict_
         const int64_t idx = base + (int64_t)row_id(r) * stride;
         if (MODE != 2) R[idx] = b[k];
         if (MODE != 1) x[idx] = a[k];
+        if (AV) P.xs[idx] = fma(w, (double)c[k], d[k]);
       }
     }
   }
@@ -1885,7 +1898,7 @@ __device__ inline void rmq_walk_down(int infv, int i0, int i1, float* L, int q, 
   }
 }
 
-template <int MODE, bool DC, int ROWS = kTaskRowsMax>
+template <int MODE, bool DC, int ROWS, bool AVG>
 __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict__ g, float* __restrict__ R,
                                                   float* __restrict__ x, float* __restrict__ stage,
                                                   const double* __restrict__ tdev) {
@@ -1928,6 +1941,9 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   const int extv = (MODE != 0 && lane < T.n_ext)
                        ? (MODE == 1 ? P.ext_slot[T.ext_off + lane] : P.ext_seq[T.ext_off + lane]) : 0;
   RmStep K;
+  constexpr bool AV = AVG && MODE != 1;
+  float c[AV ? RQK : 1];
+  double d[AV ? RQK : 1];
   {
     float a[RQK], b[RQK];
 #pragma unroll
@@ -1935,6 +1951,10 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
       const int64_t idx = T.vec_base + hc + (int64_t)rid[k] * stride;
       if (MODE != 2) a[k] = g[idx];
       b[k] = R[idx];
+      if (AV) {
+        c[k] = x[idx];
+        d[k] = P.xs[idx];
+      }
     }
     float xe[kTaskExtMax];
     if (MODE == 2 && wv == 0 && T.n_ext > 0) {
@@ -1999,6 +2019,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
   }
   __syncthreads();
   if (act) {
+    const double w = AV ? avg_weight(P.gamma, *tdev) : 0.0;
     float a[RQK], b[RQK];
 #pragma unroll
     for (int k = 0; k < RQK; ++k) {
@@ -2013,6 +2034,7 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
         const int64_t idx = T.vec_base + h + (int64_t)rid[k] * stride;
         if (MODE != 2) R[idx] = b[k];
         if (MODE != 1) x[idx] = a[k];
+        if (AV) P.xs[idx] = fma(w, (double)c[k], d[k]);
       }
     }
   }
@@ -2030,6 +2052,10 @@ __global__ __launch_bounds__(64 * RMW) void k_rmq(RmParams P, float* __restrict_
 // Batch of 512 (36.6 M elements): 401 us per segment of 8, 4.4 TB/s, while the
 // updates' kernel times fell from 580 to 382 us per iteration.  Turn + river
 // game: 427 us, and from 459 to 310 us.
+// A segment of one iteration (solver_step(1)) would move the same 20 bytes that
+// the updates did, with one more launch: there the updates take the averages
+// (us per iteration, k_avg and they: one-card game 17.8 and 15.9, river 30.1 and
+// 28.0, many-size river 40.1 and 41.1, batch of 512 636 and 594).
 // ---------------------------------------------------------------------------
 struct AvgChunk {
   int64_t off;                  // element offset, a multiple of four
@@ -3681,13 +3707,16 @@ static RmParams rm_params(Game* g, int p, int depth, int first_block) {
   P.dcfr = g->dcfr;
   P.alpha = (float)g->alpha;
   P.beta = (float)g->beta;
+  P.xs = g->xs[p].p;
+  P.gamma = g->gamma;
   return P;
 }
 
 // One player's regret update, the new plan to x: bottom-up passes of the deep pieces (deepest
 // first), the pieces without external parents, then the top-down passes of
-// the deep pieces (shallowest first).
-static int rm_update(Game* g, int p, float* x, hipStream_t s) {
+// the deep pieces (shallowest first).  avg: x is also the old plan, which goes
+// into the running average.
+static int rm_update(Game* g, int p, float* x, bool avg, hipStream_t s) {
   DevRm& E = g->drm[p];
   float* gr = g->grad[p].p;
   const double* td = g->tdev.p;
@@ -3709,29 +3738,17 @@ static int rm_update(Game* g, int p, float* x, hipStream_t s) {
       hipLaunchKernelGGL(kern, dim3(quad ? 4 * nb : nb), dim3(64 * RMW), lds, s, P, gr, g->R[p].p, x,
                          E.stage.p, td);
     };
-    if (whole) {
-      // one piece per treeplex: the fused pass only
-      if (P.dcfr) go(k_rmq<0, true, kTaskRowsWhole>);
-      else go(k_rmq<0, false, kTaskRowsWhole>);
-    } else if (quad) {
-      if (P.dcfr) {
-        if (mode == 0) go(k_rmq<0, true>);
-        else if (mode == 1) go(k_rmq<1, true>);
-        else go(k_rmq<2, true>);
-      } else {
-        if (mode == 0) go(k_rmq<0, false>);
-        else if (mode == 1) go(k_rmq<1, false>);
-        else go(k_rmq<2, false>);
-      }
-    } else if (P.dcfr) {
-      if (mode == 0) go(k_rmp<0, true>);
-      else if (mode == 1) go(k_rmp<1, true>);
-      else go(k_rmp<2, true>);
-    } else {
-      if (mode == 0) go(k_rmp<0, false>);
-      else if (mode == 1) go(k_rmp<1, false>);
-      else go(k_rmp<2, false>);
-    }
+    auto form = [&](auto dc, auto av) {
+      constexpr bool DC = decltype(dc)::value, AV = decltype(av)::value;
+      if (whole) go(k_rmq<0, DC, kTaskRowsWhole, AV>);   // one piece per treeplex: the fused pass only
+      else if (mode == 0) quad ? go(k_rmq<0, DC, kTaskRowsMax, AV>) : go(k_rmp<0, DC, AV>);
+      else if (mode == 1) quad ? go(k_rmq<1, DC, kTaskRowsMax, false>) : go(k_rmp<1, DC, false>);
+      else quad ? go(k_rmq<2, DC, kTaskRowsMax, AV>) : go(k_rmp<2, DC, AV>);
+    };
+    using Y = std::true_type;
+    using N = std::false_type;
+    if (P.dcfr) avg ? form(Y(), Y()) : form(Y(), N());
+    else avg ? form(N(), Y()) : form(N(), N());
   };
   auto launch = [&](int mode, int d) { launch_range(mode, d, E.blk_off[d], E.blk_off[d + 1], s); };
   if (D == 0) return PMX_OK;
@@ -4313,16 +4330,17 @@ int solver_set_active(Game* g, const int32_t* active_host, void* stream) {
 // advances the device iteration index t, read by the updates for their
 // discounts, so a captured sequence of iterations replays correctly) and
 // Player 1's update, then g2 = -A^T x_{t+1} and Player 2's update.  The plans
-// y_t, x_t are read from `in` and the new ones written to `out`.
-static int enqueue_iteration(Game* g, const float* const in[2], float* const out[2], hipStream_t s) {
+// y_t, x_t are read from `in` and the new ones written to `out` (avg: the same
+// buffers, and the updates take the averages).
+static int enqueue_iteration(Game* g, const float* const in[2], float* const out[2], bool avg, hipStream_t s) {
   int rc;
   MvParams PA = mv_params(g, 0, 1.0), PT = mv_params(g, 1, -1.0);
   PA.active = PT.active = g->active.p;
   PA.part = PT.part = 1;
   if ((rc = launch_mv(g, PA, in[1], g->grad[0].p, empty_params(PA), nullptr, nullptr, s, g->tdev.p))) return rc;
-  if ((rc = rm_update(g, 0, out[0], s))) return rc;
+  if ((rc = rm_update(g, 0, out[0], avg, s))) return rc;
   if ((rc = launch_mv(g, PT, out[0], g->grad[1].p, empty_params(PT), nullptr, nullptr, s))) return rc;
-  if ((rc = rm_update(g, 1, out[1], s))) return rc;
+  if ((rc = rm_update(g, 1, out[1], avg, s))) return rc;
   return PMX_OK;
 }
 
@@ -4362,7 +4380,7 @@ static int ensure_ring(Game* g, hipStream_t s) {
 static int enqueue_segment(Game* g, int m, hipStream_t s) {
   auto buf = [&](int p, int i) { return i == 0 ? g->x[p].p : g->ring[p].p + (size_t)(i - 1) * g->hg.elems[p]; };
   for (int i = 1; i <= m; ++i) {
-    if (i == m && g->n_avg[0] + g->n_avg[1] > 0) {
+    if (i == m && m > 1 && g->n_avg[0] + g->n_avg[1] > 0) {
       AvgSide S[2];
       for (int p = 0; p < 2; ++p) S[p] = {g->x[p].p, g->ring[p].p, g->hg.elems[p], g->xs[p].p};
       const dim3 grid(g->n_avg[0] + g->n_avg[1]);
@@ -4375,7 +4393,7 @@ static int enqueue_segment(Game* g, int m, hipStream_t s) {
     }
     const float* in[2] = {buf(0, i - 1), buf(1, i - 1)};
     float* out[2] = {buf(0, i == m ? 0 : i), buf(1, i == m ? 0 : i)};
-    const int rc = enqueue_iteration(g, in, out, s);
+    const int rc = enqueue_iteration(g, in, out, m == 1, s);
     if (rc) return rc;
   }
   HIP_TRY(hipGetLastError());

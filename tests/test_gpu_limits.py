@@ -247,3 +247,23 @@ def test_solver_memory():
     g.close()
     del hog
     torch.cuda.empty_cache()
+
+
+# one iteration is two products and two updates: the averages take no launch of
+# their own then (programs that step one iteration at a time)
+@pytest.mark.parametrize("steps,launches", [(1, 4), (5, 21)])
+def test_launches_of_a_step(steps, launches):
+    import ctypes
+    g = _game(I.tiny_config())
+    g.solver_step(1)
+    torch.cuda.synchronize()
+    from paper_2112_03804_amd import pmx
+    L, graph, n = pmx.lib(), ctypes.c_void_p(), ctypes.c_size_t()
+    stream = torch.cuda.Stream()
+    assert L.hipStreamBeginCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.c_int(2)) == 0
+    g.solver_step(steps, stream=stream.cuda_stream)
+    assert L.hipStreamEndCapture(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(graph)) == 0
+    assert L.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
+    assert L.hipGraphDestroy(graph) == 0
+    assert n.value == launches
+    g.close()
