@@ -396,7 +396,16 @@ void k_net(NetArgs P, const uint16_t* __restrict__ W2p) {
 constexpr int NetRows = 32;                      // rows per workgroup of k_net_rows
 constexpr int NetBias = 2 * NetW + NetOut;       // bias gradients: b1, b2, b3
 constexpr int NetGrads = NetW * NetW + NetW * NetIn + 16 * NetW;   // W2, W1, W3 (padded to 16 outputs)
-constexpr int NetMaxSplit = 16;
+// Ranges that the weight gradients' sums over rows are cut into: of eight row
+// blocks while that fills the chip, up to 16; of 32 (1,024 rows) from 16 such
+// on, up to 64 of any length, so that FP32 sums are no longer than the
+// layer-by-layer products' (MFMA steps and partial sums in a row: 48 and 48 at
+// 16,384 rows, 50 and 64 at 32,768, 52 and 96 at 65,536).  More ranges cost
+// partial sums: 32,768 rows 156 us with 64, 151 us with 16.
+__host__ __device__ constexpr int64_t net_splits(int64_t nb) {
+  const int64_t s = nb / 8 < 16 ? nb / 8 : nb / 32 < 16 ? 16 : nb / 32;
+  return s < 1 ? 1 : s > 64 ? 64 : s;
+}
 
 struct NetTrain {
   int64_t M, nb;                                 // rows; blocks of 32 rows
@@ -748,10 +757,15 @@ __global__ __launch_bounds__(256) void k_net_grads(const float* __restrict__ par
   if ((int)blockIdx.x < NetGradBlocks) {
     const int i = (int)blockIdx.x * 1024 + 4 * tid;
     float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    // 16 ranges in order, then the next 16
+    for (int z0 = 0; z0 < splits; z0 += 16) {
+      float4 u = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll 8
-    for (int z = 0; z < splits; ++z) {
-      const float4 p = *(const float4*)(part + (int64_t)z * NetGrads + i);
-      v.x += p.x, v.y += p.y, v.z += p.z, v.w += p.w;
+      for (int z = z0; z < min(splits, z0 + 16); ++z) {
+        const float4 p = *(const float4*)(part + (int64_t)z * NetGrads + i);
+        u.x += p.x, u.y += p.y, u.z += p.z, u.w += p.w;
+      }
+      v.x += u.x, v.y += u.y, v.z += u.z, v.w += u.w;
     }
     float* dst = i < NetW * NetW ? O.W2 + i
                : i < NetW * NetW + NetW * NetIn ? O.W1 + (i - NetW * NetW) : O.W3 + (i - NetW * NetW - NetW * NetIn);
@@ -1003,7 +1017,7 @@ static int64_t net_train_layout(int64_t M, int64_t off[11]) {
   const int64_t frag = nb * 512 * (int64_t)sizeof(uint16_t);   // one feature tile
   const int64_t bytes[10] = {2 * NetW * NetW, 2 * NetW * NetW, frag * (NetIn / 16), frag * (NetW / 16),
                              frag * (NetW / 16), frag * (NetW / 16), frag * (NetW / 16), frag,
-                             (int64_t)sizeof(float) * NetMaxSplit * NetGrads,
+                             (int64_t)sizeof(float) * net_splits(nb) * NetGrads,
                              (int64_t)sizeof(float) * nb * NetBias};
   off[0] = 0;
   for (int i = 0; i < 10; ++i) off[i + 1] = off[i] + (bytes[i] + 255) / 256 * 256;
@@ -1056,8 +1070,7 @@ int mlp_loss_and_grad_bf16(int64_t M, const uint16_t* X, const float* target, co
   const size_t lds = sizeof(uint16_t) * (NetRows * (2 * NetPitch + NetIn + 8 + 16) + NetOut * NetPitch) +
                      sizeof(float) * NetRows * (2 * (NetOut + 1) + 1);
   hipLaunchKernelGGL(k_net_rows, dim3((unsigned)P.nb), dim3(64 * NetWaves), lds, s, P);
-  // about eight row blocks per range, as many ranges as give the chip work
-  const int splits0 = (int)std::max<int64_t>(1, std::min<int64_t>(NetMaxSplit, P.nb / 8));
+  const int64_t splits0 = net_splits(P.nb);
   const int per = (int)((P.nb + splits0 - 1) / splits0), splits = (int)((P.nb + per - 1) / per);
   const NetWgrad Q{P.Xf, P.H1f, P.H2f, P.D1f, P.D2f, P.D3f, part, (int)P.nb, per, splits};
   hipLaunchKernelGGL(k_net_wgrad, dim3(8 * ((splits + 7) / 8) * NetWgradTiles), dim3(256), 0, s, Q);

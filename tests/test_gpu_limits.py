@@ -267,3 +267,30 @@ def test_launches_of_a_step(steps, launches):
     assert L.hipGraphDestroy(graph) == 0
     assert n.value == launches
     g.close()
+
+
+# weight gradients of long batches: sums over rows are cut into ranges, so that
+# one row of large activations hides the others of its own range at most (a
+# single FP32 sum would lose them all).  Row 0's second hidden activation is
+# 2^30, the others' 1; the output gradients are 1/8; every product is exact,
+# and 32 rows' 1s are less than half a unit (128) of 2^30's sum
+@pytest.mark.parametrize("rows,rows_of_a_range", [(8192, 512), (32768, 1024), (65536, 1024), (262144, 4096)])
+def test_sums_of_long_batches(rows, rows_of_a_range):
+    net, _ = _net(3)
+    from paper_2112_03804_amd import warmstart
+    for k in net.p:
+        net.p[k].zero_()
+    for k in net.pb:
+        net.pb[k].zero_()
+    net.pb["W1"][5, 2] = 1.0
+    net.pb["W2"][9, 5] = 1.0
+    X = torch.zeros((rows, warmstart.D_IN), dtype=torch.bfloat16, device="cuda")
+    X[:, 2] = 1.0
+    X[0, 2] = 2.0 ** 30
+    T = torch.zeros((rows, warmstart.K), device="cuda")
+    T[:, 0] = 1.0
+    net.loss_and_grad(X, T, None, rows)
+    # up to 20 partial sums more, each rounded to 128
+    want = 0.125 * (2.0 ** 30 + rows - 1)
+    assert abs(float(net.g["W3"][1, 9]) - want) <= 0.125 * (rows_of_a_range + 20 * 64)
+    assert abs(float(net.g["b3"][1]) - 0.125 * rows) <= 1e-5 * rows
