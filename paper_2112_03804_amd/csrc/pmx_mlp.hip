@@ -605,10 +605,11 @@ __global__ __launch_bounds__(64 * NetWaves) __attribute__((amdgpu_waves_per_eu(2
     float v = 0.f;
     for (int r = 0; r < R; ++r) v += dz[r * (NetOut + 1) + tid];
     P.bias[rb * NetBias + 2 * NetW + tid] = v;
-  } else if (tid == 64) {
-    float v = 0.f;
-    for (int r = 0; r < R; ++r) v += ls[r];
-    P.loss[rb] = v;
+  } else if (w == 1) {
+    float v = ls[lane & (R - 1)];
+#pragma unroll
+    for (int m = R / 2; m > 0; m >>= 1) v += __shfl_xor(v, m, 64);
+    if (lane == 0) P.loss[rb] = v;
   } else if (w == 2) {   // the output gradients' row fragment
     s16x8 o;
 #pragma unroll
@@ -792,9 +793,10 @@ __global__ __launch_bounds__(256) void k_net_grads(const float* __restrict__ par
   }
   const int i = (b - NetBiasBlocks) * 256 + tid;   // losses per 256 rows
   if (i < n_loss) {
-    float v = 0.f;
-    for (int k = 8 * i; k < min(nb, 8 * i + 8); ++k) v += loss[k];
-    O.loss[i] = v;
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = 8 * i + k < nb ? loss[8 * i + k] : 0.f;
+    O.loss[i] = ((v[0] + v[4]) + (v[2] + v[6])) + ((v[1] + v[5]) + (v[3] + v[7]));
   }
 }
 

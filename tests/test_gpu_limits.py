@@ -289,8 +289,11 @@ def test_sums_of_long_batches(rows, rows_of_a_range):
     X[0, 2] = 2.0 ** 30
     T = torch.zeros((rows, warmstart.K), device="cuda")
     T[:, 0] = 1.0
-    net.loss_and_grad(X, T, None, rows)
+    loss = net.loss_and_grad(X, T, None, rows)
     # up to 20 partial sums more, each rounded to 128
     want = 0.125 * (2.0 ** 30 + rows - 1)
     assert abs(float(net.g["W3"][1, 9]) - want) <= 0.125 * (rows_of_a_range + 20 * 64)
     assert abs(float(net.g["b3"][1]) - 0.125 * rows) <= 1e-5 * rows
+    # the loss of 256 rows is a sum in a tree of depth 8
+    assert loss.shape == (rows // 256,)
+    assert ((loss.double() - 256 * np.log(8.0)).abs() <= 256 * np.log(8.0) * 2.0 ** -24 * (8 + 8)).all()
