@@ -982,11 +982,12 @@ int mlp_gemm_bf16(int32_t M, int32_t N, int32_t K, const uint16_t* A, int32_t ld
   return PMX_OK;
 }
 
-// Rows from which the 128-row tiles are used: 32-row tiles read the second
-// layer's weights four times as often but give a small call four times the
-// workgroups and need no packed weights (8,191 rows: 20.0 us, 8,192: 22.5 us;
-// beyond 256 workgroups they would run in rounds).
-static constexpr int64_t kNetLargeRows = 8192;
+// Rows up to which the 32-row tiles are used, one workgroup per CU: they read
+// the second layer's weights four times as often as 128-row tiles but give a
+// small call four times the workgroups and need no packed weights (8,192 rows:
+// 20.1 us, 21.4 us with 128-row tiles; beyond 256 workgroups they would run in
+// rounds).
+static constexpr int64_t kNetSmallRows = 32 * 256;
 
 int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const float* b1, const uint16_t* W2,
                      const float* b2, const uint16_t* W3, const float* b3, float* Z, uint16_t* work, void* stream) {
@@ -999,7 +1000,7 @@ int mlp_forward_bf16(int64_t M, const uint16_t* X, const uint16_t* W1, const flo
   hipStream_t s = (hipStream_t)stream;
   const NetArgs P{M, X, W1, W2, W3, b1, b2, b3, Z};
   auto lds = [](int rows) { return sizeof(uint16_t) * (size_t)rows * (NetPitch + NetIn + 8); };
-  if (M >= kNetLargeRows) {
+  if (M > kNetSmallRows) {
     hipLaunchKernelGGL(k_net_pack, dim3(NetW * NetW / 8 / 256), dim3(256), 0, s, W2, work);
     const int64_t tiles = (M + 127) / 128;
     hipLaunchKernelGGL((k_net<8, true>), dim3((unsigned)std::min<int64_t>(tiles, 256)), dim3(64 * NetWaves), lds(128),
