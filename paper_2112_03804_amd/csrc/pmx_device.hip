@@ -3502,17 +3502,19 @@ static void launch_grp_class(GParams A, const float* in0, float* out0, const GPa
 
 // Weights for spreading a product's class launches over the streams (longest
 // first, each to the least loaded stream).  A single-direction product (the
-// solver's) weighs a class by per-workgroup durations measured on a batch of
-// river endgames, by kind and class, plus a floor for the latency of a launch
-// whose workgroups fit one round (the smallest and the largest hand classes);
-// a pair launch, whose classes cover both directions, balances by scan
-// entries, which measured better there.
+// solver's) weighs a class by its duration alone on the GPU: nanoseconds per
+// workgroup by kind and class, over a launch's latency, as measured one after
+// another on a batch of 512 river endgames (launches of 48 to 2,734
+// workgroups, 4.8 to 28.2 us; the kinds that it lacks are weighed as the wider
+// of the others).  An iteration of it: 523 us with durations of earlier forms
+// of the kernels, 517 us.  A pair launch, whose classes cover both directions,
+// balances by scan entries, which measured better there.
 static constexpr int64_t kGrpWgNs[GrpDir::kKinds][kGrpClasses] = {
-    {300, 35, 57, 51, 127}, {300, 35, 57, 51, 127}, {200, 22, 31, 25, 59}, {300, 27, 44, 39, 98}};
+    {0, 5, 8, 10, 18}, {0, 5, 8, 10, 18}, {0, 4, 7, 8, 14}, {0, 5, 8, 10, 18}};
 
 static int64_t grp_launch_weight(int kind, int c, int nchunk, bool pair) {
   if (pair) return (int64_t)nchunk * kGrpKE[c] * (kind == 2 ? 2 : kind == 3 ? 3 : 4);
-  return (int64_t)nchunk * kGrpWgNs[kind][c] + (kind == 2 ? 5000 : 7000) * (c == kGrpClasses - 1 ? 4 : 1);
+  return (int64_t)nchunk * kGrpWgNs[kind][c] + (kind == 2 ? 4800 : 5200);
 }
 
 // Kernel 4 (FP32 only): one launch per hands-per-thread class present, the
