@@ -375,14 +375,14 @@ int saddle_gap_of(Game* g, const double* x_dev, const double* y_dev, double* gap
 
 /* saddle_gap_of for callers that cannot allocate device memory (code under
  * stream capture, tight serving loops, harnesses that forbid allocation):
- * the same kernels, with the FP64 gradients, stage rows, per-hand values and
- * per-instance sums in one static device array of 32 MiB per GPU (set up at
- * game_create on the game's device, held until the process ends).  The
+ * the same kernels, with the FP64 gradients and the per-instance sums in one
+ * static device array of 32 MiB per GPU (set up at game_create on the game's
+ * device, held until the process ends).  The
  * call allocates nothing, on the device or the host: br1 and br2 (host
  * arrays, one entry per instance) are required and receive the sums; gap
- * may be NULL.  PMX_EINVAL when the game needs more scratch than the array
- * holds (8 bytes per element of both players' vectors, deep-piece stage
- * rows and hands, each part rounded up to 256 bytes; about 4 M elements:
+ * may be NULL.  PMX_EINVAL when the game is too large for the array (counted
+ * as 8 bytes per element of both players' vectors, of a row for each river
+ * subtree and per hand, each part rounded up to 256 bytes; about 4 M elements:
  * single river endgames and small batches fit, the batch of 512 and the
  * turn + river game do not).  Calls on one GPU share its array: calls that
  * overlap on one GPU (other streams or threads) race.  Synchronizes

@@ -1755,7 +1755,6 @@ namespace {
 void build_treeplex_plan(HostGame& hg, int p) {
   TpPlan& T = hg.tp[p];
   T = TpPlan();
-  int64_t hand_base = 0;
   for (size_t ii = 0; ii < hg.inst.size(); ++ii) {
     const Built& b = hg.inst[ii];
     const int base = (int)T.inf_parent.size();
@@ -1764,17 +1763,13 @@ void build_treeplex_plan(HostGame& hg, int p) {
       T.inf_first.push_back(I.first);
       T.inf_nact.push_back(I.nact);
     }
-    T.stage_stride = std::max(T.stage_stride, b.stride[p]);
     auto new_task = [&]() {
       TpTask t{};
       t.vec_base = b.vec_off[p];
       t.stride = b.stride[p];
       t.n_hands = b.inst.n[p];
       t.inf_begin = (int)T.order.size();
-      t.stage = -1;
-      t.pull_begin = t.pull_end = (int)T.pulls.size();
       t.inst = (int)ii;
-      t.hand_base = (int32_t)hand_base;
       t.ext_parent = -1;
       t.seq_begin = t.seq_end = -1;
       return t;
@@ -1801,15 +1796,12 @@ void build_treeplex_plan(HostGame& hg, int p) {
       T.tasks.push_back(t);
     } else {
       // deep tasks: one per (chance node, river card) subtree
-      std::vector<TpPull> pulls;
       for (const RiverTask& rt : b.sf.rivers) {
         TpTask t = new_task();
         for (int i = rt.inf_begin[p]; i < rt.inf_end[p]; ++i) T.order.push_back(base + i);
         t.inf_end = (int)T.order.size();
         seq_range(t);
-        t.stage = T.n_stage++;
         t.ext_parent = rt.parent_seq[p];
-        pulls.push_back(TpPull{rt.parent_seq[p], t.stage});
         T.deep.push_back((int)T.tasks.size());
         T.tasks.push_back(t);
       }
@@ -1817,15 +1809,10 @@ void build_treeplex_plan(HostGame& hg, int p) {
       for (int i = 0; i < (int)b.sf.inf[p].size(); ++i)
         if (b.sf.inf[p][i].board < 0) T.order.push_back(base + i);
       top.inf_end = (int)T.order.size();
-      top.pull_begin = (int)T.pulls.size();
-      T.pulls.insert(T.pulls.end(), pulls.begin(), pulls.end());
-      top.pull_end = (int)T.pulls.size();
       T.top.push_back((int)T.tasks.size());
       T.tasks.push_back(top);
     }
-    hand_base += b.inst.n[p];
   }
-  T.hands_total = hand_base;
 }
 
 }  // namespace

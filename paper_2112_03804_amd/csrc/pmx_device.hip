@@ -2568,8 +2568,8 @@ struct DevGrp {                 // grouped matvec layout of one direction (kerne
 struct DevTp {
   DBuf<int32_t> inf_parent, inf_first, inf_nact, order;
   DBuf<TpTask> tasks;
-  DBuf<int2> b_single, b_deep, b_top, b_all;
-  int n_single = 0, n_deep = 0, n_top = 0, n_all = 0;
+  DBuf<int2> b_single, b_deep, b_top;
+  int n_single = 0, n_deep = 0, n_top = 0;
 };
 
 struct DevRm {                  // regret-update pieces of one player
@@ -3149,16 +3149,10 @@ static int upload_game(Game* g) {
         (rc = E.tasks.upload(T.tasks)))
       return rc;
     auto bs = tp_blocks(T, T.single), bd = tp_blocks(T, T.deep), bt = tp_blocks(T, T.top);
-    std::vector<int32_t> all_ids = T.single;
-    all_ids.insert(all_ids.end(), T.deep.begin(), T.deep.end());
-    auto ba = tp_blocks(T, all_ids);
-    if ((rc = E.b_single.upload(bs)) || (rc = E.b_deep.upload(bd)) || (rc = E.b_top.upload(bt)) ||
-        (rc = E.b_all.upload(ba)))
-      return rc;
+    if ((rc = E.b_single.upload(bs)) || (rc = E.b_deep.upload(bd)) || (rc = E.b_top.upload(bt))) return rc;
     E.n_single = (int)bs.size();
     E.n_deep = (int)bd.size();
     E.n_top = (int)bt.size();
-    E.n_all = (int)ba.size();
   }
   for (int p = 0; p < 2; ++p) {
     size_t n = (size_t)hg.elems[p];
@@ -4680,14 +4674,18 @@ int saddle_gap_of_static(Game* g, const double* x, const double* y, double* gap,
   double* base = nullptr;
   if ((rc = static_scratch(g->device_id, &base))) return rc;
   // carve the FP64 gradients and the per-instance sums out of the static
-  // array, each on 256-byte boundaries; the limit counts stage rows and
-  // per-hand values too, as its description in pmx.h does
+  // array, each on 256-byte boundaries; the limit counts a row per river
+  // subtree and the hands too, as pmx.h says: what it refused stays refused
   const int ni = (int)g->hg.inst.size();
-  const TpPlan* tp = g->hg.tp;
-  auto stage_elems = [](const TpPlan& T) { return (size_t)std::max(T.n_stage, 1) * std::max(T.stage_stride, 1); };
-  size_t need[7] = {(size_t)g->hg.elems[0], (size_t)g->hg.elems[1], stage_elems(tp[0]), stage_elems(tp[1]),
-                    (size_t)std::max<int64_t>(tp[0].hands_total, 1), (size_t)std::max<int64_t>(tp[1].hands_total, 1),
-                    2 * (size_t)ni};
+  size_t need[7] = {(size_t)g->hg.elems[0], (size_t)g->hg.elems[1], 0, 0, 0, 0, 2 * (size_t)ni};
+  for (int p = 0; p < 2; ++p) {
+    size_t stride = 1;
+    for (const Built& b : g->hg.inst) {
+      stride = std::max(stride, (size_t)b.stride[p]);
+      need[4 + p] += b.inst.n[p];
+    }
+    need[2 + p] = std::max<size_t>(g->hg.tp[p].deep.size(), 1) * stride;   // a row per river subtree
+  }
   double* part[7];
   size_t off = 0;
   for (int k = 0; k < 7; ++k) {

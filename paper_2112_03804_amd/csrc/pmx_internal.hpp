@@ -293,25 +293,15 @@ struct TpTask {                         // treeplex task: one subtree of one ins
   int64_t vec_base;
   int32_t stride, n_hands;
   int32_t inf_begin, inf_end;           // range into the task's infoset id list
-  int32_t stage;                        // deep task: row of the stage buffer, else -1
-  int32_t pull_begin, pull_end;         // top task: stage rows to pull
   int32_t inst;
-  int32_t hand_base;                    // offset of this instance's hands in per-hand outputs
   int32_t ext_parent;                   // deep task: the first-round sequence its roots hang from
   int32_t seq_begin, seq_end;           // contiguous sequences owned by the task (-1: not contiguous)
-};
-struct TpPull {
-  int32_t seq;                          // instance-relative sequence receiving the value
-  int32_t stage;
 };
 struct TpPlan {                         // one player
   std::vector<int32_t> inf_parent, inf_first, inf_nact;   // global infoset table (seq ids relative)
   std::vector<int32_t> order;           // infoset ids of each task, DFS order
   std::vector<TpTask> tasks;
-  std::vector<TpPull> pulls;
   std::vector<int32_t> deep, top, single;                 // task ids per phase
-  int n_stage = 0, stage_stride = 0;
-  int64_t hands_total = 0;
 };
 
 // Regret-update tasks.  Each player's treeplex is cut into pieces of at most
