@@ -297,3 +297,61 @@ def test_sums_of_long_batches(rows, rows_of_a_range):
     # the loss of 256 rows is a sum in a tree of depth 8
     assert loss.shape == (rows // 256,)
     assert ((loss.double() - 256 * np.log(8.0)).abs() <= 256 * np.log(8.0) * 2.0 ** -24 * (8 + 8)).all()
+
+
+# rows with non-finite values: the logits of the others are the same bits as
+# without them, and where the layer-by-layer path gives a non-finite logit, so
+# does the fused one (a warm start falls back row by row on these).  ReLU takes
+# a NaN to 0 on either path, so that weights of both signs leave finite logits,
+# and non-negative ones infinities in the rows of +inf and 3e38
+@pytest.mark.parametrize("positive", [False, True])
+@pytest.mark.parametrize("rows", [40, 300, 8192, 8500])
+def test_non_finite_rows(rows, positive):
+    net, gen = _net(rows)
+    from paper_2112_03804_amd import warmstart
+    if positive:
+        for v in net.pb.values():
+            v.abs_()
+    X = torch.randn((rows, warmstart.D_IN), generator=gen, device="cuda").to(torch.bfloat16)
+    T = torch.full((rows, warmstart.K), 1.0 / warmstart.K, device="cuda")
+    bad = torch.zeros(rows, dtype=torch.bool, device="cuda")
+    clean, clean_loss = net.logits(X, rows), net.loss_and_grad(X, T, None, rows).clone()
+    for k, v in ((3, float("nan")), (17, float("inf")), (31, -float("inf")), (rows - 1, 3e38)):
+        X[k] = v
+        bad[k] = True
+    got, ref = net.logits(X, rows), net.forward(X, rows)[:rows]
+    assert torch.equal(got[~bad], clean[~bad])
+    assert torch.equal(torch.isfinite(got), torch.isfinite(ref))
+    if positive:
+        assert not torch.isfinite(got[[17, rows - 1]]).any()
+    loss = net.loss_and_grad(X, T, None, rows)
+    hit = torch.zeros(((rows + 255) // 256) * 256, dtype=torch.bool, device="cuda")
+    hit[:rows] = bad & ~torch.isfinite(ref).all(dim=1)
+    hit = hit.view(-1, 256).any(dim=1)
+    assert torch.equal(~torch.isfinite(loss), hit)
+    clear = torch.ones_like(hit)
+    clear[[0, (rows - 1) // 256]] = False
+    assert torch.equal(loss[clear], clean_loss[clear])
+
+
+# a first step that the caller captures: nothing is allocated then, and replays
+# are iterations like any other
+@pytest.mark.parametrize("steps", [1, 3, 9])
+@pytest.mark.parametrize("fn", [I.tiny_config, lambda: I.batched_configs(3, seed=8, n_lo=40, n_hi=300)], ids=["tiny", "batch"])
+def test_captured_first_step(fn, steps):
+    g, h = _game(fn()), _game(fn())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        g.solver_step(steps)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        g.solver_step(2)
+        h.solver_step(steps)
+        h.solver_step(2)
+        torch.cuda.synchronize()
+        for p in range(2):
+            s, t = g.solver_get_state(p), h.solver_get_state(p)
+            assert all(np.array_equal(s[k], t[k]) for k in ("regret", "plan", "avg_sum"))
+    g.close()
+    h.close()
