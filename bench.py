@@ -35,9 +35,9 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E, published
 # known size (profiles/matvec_pair_traffic_counters.md).  They describe the
 # kernel sources whose code (comments and whitespace removed) has the SHA-1
 # recorded here and are reported as null for any other version of that code.
-TRAFFIC = {"sources_sha1": "4a459901936f2722d033e79fc67a953f6c05a9c2",
-           "river": {"4:1": 1422373, "3:1": 1635390},
-           "batch": {"4:1": 351534482, "4:2": 351211196}}
+TRAFFIC = {"sources_sha1": "af46ed7aaf91dd17e5f4ba1f880bbdcfc3989653",
+           "river": {"4:1": 1427454, "3:1": 1636234},
+           "batch": {"4:1": 351531482, "4:2": 351210996}}
 TRAFFIC_SOURCES = ("paper_2112_03804_amd/csrc/pmx_device.hip", "paper_2112_03804_amd/csrc/host_build.cpp")
 # the schedules of the counter probe (the autotuner's usual choices; traffic
 # is reported for these only) and the batch schedule of the trace probe
@@ -570,16 +570,15 @@ def pmc_probe(args):
 def trace_probe(args):
     """Launches for a kernel trace of the solver iteration: the batch, the turn
     + river game, the river endgame and the river with Libratus' sizes, each
-    at the schedule the bench's autotuner picks there (``--trace-game``
-    selects one), a few graph-captured iterations after a warm-up, then one
-    FP64 gap."""
+    at the default schedule (``--trace-game`` selects one), a few
+    graph-captured iterations after a warm-up, then one FP64 gap."""
     import torch
     from paper_2112_03804_amd import instances as I
     from paper_2112_03804_amd import pmx
     games = (("batch", lambda: pmx.Game(I.batched_configs(args.batch)), PROBE_BATCH_SCHEDULE, 64),
-             ("turn_river", lambda: pmx.Game(I.config(2)), (3, 8), 32),
-             ("river", lambda: pmx.Game(I.config(1)), (3, 1), 64),
-             ("libratus_river", lambda: pmx.Game(I.libratus_river(stack=1000.0)), (3, 1), 64))
+             ("turn_river", lambda: pmx.Game(I.config(2)), (4, 1), 32),
+             ("river", lambda: pmx.Game(I.config(1)), (4, 1), 64),
+             ("libratus_river", lambda: pmx.Game(I.libratus_river(stack=1000.0)), (4, 1), 64))
     for name, make, sched, iters in games:
         if args.trace_game and name != args.trace_game:
             continue

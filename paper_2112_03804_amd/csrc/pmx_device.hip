@@ -3500,9 +3500,9 @@ static void launch_grp_class(GParams A, const float* in0, float* out0, const GPa
 // workgroup by kind and class, over a launch's latency, as measured one after
 // another on a batch of 512 river endgames (launches of 48 to 2,734
 // workgroups, 4.8 to 28.2 us; the kinds that it lacks are weighed as the wider
-// of the others).  An iteration of it: 523 us with durations of earlier forms
-// of the kernels, 517 us.  A pair launch, whose classes cover both directions,
-// balances by scan entries, which measured better there.
+// of the others).  32 iterations and a gap of it: 16.75 ms with durations of
+// earlier forms of the kernels, 16.54 ms.  A pair launch, whose classes cover
+// both directions, balances by scan entries, which measured better there.
 static constexpr int64_t kGrpWgNs[GrpDir::kKinds][kGrpClasses] = {
     {0, 5, 8, 10, 18}, {0, 5, 8, 10, 18}, {0, 4, 7, 8, 14}, {0, 5, 8, 10, 18}};
 

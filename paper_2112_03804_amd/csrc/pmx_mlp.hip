@@ -223,7 +223,7 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs P, int splits) {
 //
 // Eight wavefronts, each 64 features of a hidden layer for every row of the
 // tile; the second layer's weights stream from L2, the next k step in
-// flight during the current one's MFMAs.  A tile of 128 rows (133 KB of LDS)
+// flight during the current one's MFMAs.  A tile of 128 rows (152 KB of LDS)
 // asks 31 bytes per cycle and CU of L2 at the MFMA rate, a quarter of what 32
 // rows would.  PACKED: those weights in fragment order, 1 KB contiguous per
 // load; as stored, a k step would use half of each 128-byte line and find
@@ -231,7 +231,7 @@ __global__ __launch_bounds__(256) void k_gemm_reduce(GemmArgs P, int splits) {
 // inputs in flight during the second layer.
 //
 // 1.5 M rows: 6.12 ms layer by layer with the activations through HBM in FP32
-// and BF16 (148 TFLOP/s), 0.78 ms here (1,157 TFLOP/s; an 8192^3 library
+// and BF16 (148 TFLOP/s), 0.75 ms here (1,210 TFLOP/s; an 8192^3 library
 // product reaches 1,190).  Up to 8,192 rows: 20 us, the latency of one tile.
 // ---------------------------------------------------------------------------
 constexpr int NetIn = 64, NetW = 512, NetOut = 8;
@@ -389,9 +389,10 @@ void k_net(NetArgs P, const uint16_t* __restrict__ W2p) {
 // Layer by layer through HBM it was 16 launches, 300 us at 8,192 rows, of
 // which column sums took 113 us (one thread per column adding 128 partials)
 // and the GEMMs, at 64 x 64 tiles with 2-byte transposes through LDS, 160 us.
-// Now 52 us with Adam's: k_net_rows 27 (every CU reads the second layer's
-// weights twice, 512 KB in 6.3 us each time), k_net_wgrad 18 (its fragments'
-// loads, 512 KB per workgroup), k_net_grads 5, Adam 4, packing 2.4.
+// Now 52 us with Adam's; in a kernel trace, where they add up to 56:
+// k_net_rows 27 (every CU reads the second layer's weights twice, 512 KB in
+// 6.3 us each time), k_net_wgrad 18 (its fragments' loads, 512 KB per
+// workgroup), k_net_grads 5, Adam 4, packing 2.4.
 // ---------------------------------------------------------------------------
 constexpr int NetRows = 32;                      // rows per workgroup of k_net_rows
 constexpr int NetBias = 2 * NetW + NetOut;       // bias gradients: b1, b2, b3
