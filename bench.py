@@ -35,9 +35,9 @@ HBM_PEAK_GBS = 8000.0      # MI355X HBM3E, published
 # known size (profiles/matvec_pair_traffic_counters.md).  They describe the
 # kernel sources whose code (comments and whitespace removed) has the SHA-1
 # recorded here and are reported as null for any other version of that code.
-TRAFFIC = {"sources_sha1": "af46ed7aaf91dd17e5f4ba1f880bbdcfc3989653",
-           "river": {"4:1": 1427454, "3:1": 1636234},
-           "batch": {"4:1": 351531482, "4:2": 351210996}}
+TRAFFIC = {"sources_sha1": "73b92b308adc3d572d9ff8aaa669620437716429",
+           "river": {"4:1": 1427479, "3:1": 1631114},
+           "batch": {"4:1": 351536288, "4:2": 351215015}}
 TRAFFIC_SOURCES = ("paper_2112_03804_amd/csrc/pmx_device.hip", "paper_2112_03804_amd/csrc/host_build.cpp")
 # the schedules of the counter probe (the autotuner's usual choices; traffic
 # is reported for these only) and the batch schedule of the trace probe

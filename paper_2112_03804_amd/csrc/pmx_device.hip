@@ -3262,11 +3262,11 @@ static McParams mc_params(Game* g, int d, const MvParams& like, int c) {
   return P;
 }
 
-template <int BLOCK, int KH, typename IO>
+template <int BLOCK, int KH>
 static constexpr size_t mc_lds() {
   constexpr int KE = BLOCK == 512 ? 4 * KH : 4 * KH + 4;
   constexpr int SK = KE + (KE % 8 == 0 ? 4 : 0);
-  return sizeof(double) * (2 * kMcSegMax + 3 * (BLOCK / 64)) + 2 * sizeof(IO) * (size_t)BLOCK * SK;
+  return sizeof(double) * (2 * kMcSegMax + 3 * (BLOCK / 64)) + 2 * sizeof(float) * (size_t)BLOCK * SK;
 }
 
 // LDS bytes of the largest class a launch of the chunk-aligned kernel needs.
@@ -3276,21 +3276,20 @@ static size_t mc_lds_max(Game* g) {
     if (!g->dm[0].count[c] && !g->dm[1].count[c]) continue;
     size_t b = 0;
     if (g->dm[0].block == 512)
-      b = c == 0 ? mc_lds<512, 1, float>() : c == 1 ? mc_lds<512, 2, float>() : mc_lds<512, 3, float>();
+      b = c == 0 ? mc_lds<512, 1>() : c == 1 ? mc_lds<512, 2>() : mc_lds<512, 3>();
     else
-      b = c == 0 ? mc_lds<256, 1, float>() : c == 1 ? mc_lds<256, 2, float>() : c == 2 ? mc_lds<256, 3, float>()
-        : c == 3 ? mc_lds<256, 4, float>() : mc_lds<256, 5, float>();
+      b = c == 0 ? mc_lds<256, 1>() : c == 1 ? mc_lds<256, 2>() : c == 2 ? mc_lds<256, 3>()
+        : c == 3 ? mc_lds<256, 4>() : mc_lds<256, 5>();
     m = std::max(m, b);
   }
   return m;
 }
 
-template <int BLOCK, int KH, typename IO>
-static void launch_mc_class(const McParams& A, const IO* in0, IO* out0, const McParams& B, const IO* in1,
-                            IO* out1, hipStream_t s, double* tick) {
-  const size_t lds = mc_lds<BLOCK, KH, IO>();
-  hipLaunchKernelGGL((k_mvc<BLOCK, KH, IO>), dim3(A.nchunk + B.nchunk), dim3(BLOCK), lds, s, A, in0, out0, B,
-                     in1, out1, tick);
+template <int BLOCK, int KH>
+static void launch_mc_class(const McParams& A, const float* in0, float* out0, const McParams& B, const float* in1,
+                            float* out1, hipStream_t s, double* tick) {
+  hipLaunchKernelGGL((k_mvc<BLOCK, KH, float>), dim3(A.nchunk + B.nchunk), dim3(BLOCK), (mc_lds<BLOCK, KH>()), s, A,
+                     in0, out0, B, in1, out1, tick);
 }
 
 // Kernels 2 and 3: one launch per hands-per-thread class present.
@@ -3394,9 +3393,8 @@ static int order_parts(Game* g, MvParams& P0, MvParams& P1, hipStream_t s, F&& e
   return rc;
 }
 
-template <typename IO>
-static int launch_mc(Game* g, const MvParams& P0, const IO* in0, IO* out0, const MvParams& P1, const IO* in1,
-                     IO* out1, hipStream_t s, double* tick) {
+static int launch_mc(Game* g, const MvParams& P0, const float* in0, float* out0, const MvParams& P1, const float* in1,
+                     float* out1, hipStream_t s, double* tick) {
   const int block = g->dm[0].block;
   if (block == 0 || g->dm[1].block != block) return fail(PMX_ESTATE, "matvec layout not built");
   int cls[kMcClasses], n = 0;
@@ -3415,17 +3413,17 @@ static int launch_mc(Game* g, const MvParams& P0, const IO* in0, IO* out0, const
     double* tk = first ? tick : nullptr;
     if (block == 512) {
       switch (c) {
-        case 0: launch_mc_class<512, 1, IO>(A, in0, out0, B, in1, out1, st, tk); break;
-        case 1: launch_mc_class<512, 2, IO>(A, in0, out0, B, in1, out1, st, tk); break;
-        default: launch_mc_class<512, 3, IO>(A, in0, out0, B, in1, out1, st, tk); break;
+        case 0: launch_mc_class<512, 1>(A, in0, out0, B, in1, out1, st, tk); break;
+        case 1: launch_mc_class<512, 2>(A, in0, out0, B, in1, out1, st, tk); break;
+        default: launch_mc_class<512, 3>(A, in0, out0, B, in1, out1, st, tk); break;
       }
     } else {
       switch (c) {
-        case 0: launch_mc_class<256, 1, IO>(A, in0, out0, B, in1, out1, st, tk); break;
-        case 1: launch_mc_class<256, 2, IO>(A, in0, out0, B, in1, out1, st, tk); break;
-        case 2: launch_mc_class<256, 3, IO>(A, in0, out0, B, in1, out1, st, tk); break;
-        case 3: launch_mc_class<256, 4, IO>(A, in0, out0, B, in1, out1, st, tk); break;
-        default: launch_mc_class<256, 5, IO>(A, in0, out0, B, in1, out1, st, tk); break;
+        case 0: launch_mc_class<256, 1>(A, in0, out0, B, in1, out1, st, tk); break;
+        case 1: launch_mc_class<256, 2>(A, in0, out0, B, in1, out1, st, tk); break;
+        case 2: launch_mc_class<256, 3>(A, in0, out0, B, in1, out1, st, tk); break;
+        case 3: launch_mc_class<256, 4>(A, in0, out0, B, in1, out1, st, tk); break;
+        default: launch_mc_class<256, 5>(A, in0, out0, B, in1, out1, st, tk); break;
       }
     }
     return PMX_OK;
@@ -3659,7 +3657,7 @@ static int launch_mv(Game* g, MvParams P0, const float* in0, float* out0, MvPara
   if (g->hg.mv_kernel < 2 || g->hg.mv_kernel > 4) return fail(PMX_ESTATE, "no matvec schedule set");
   if (mc_lds_max(g) > (size_t)g->max_lds)
     return fail(PMX_EINVAL, "matvec workgroup needs more LDS than this device gives a workgroup");
-  return order_parts(g, P0, P1, s, [&]() { return launch_mc<float>(g, P0, in0, out0, P1, in1, out1, s, tick); });
+  return order_parts(g, P0, P1, s, [&]() { return launch_mc(g, P0, in0, out0, P1, in1, out1, s, tick); });
 }
 static int launch_mv(Game* g, MvParams P0, const double* in0, double* out0, MvParams P1, const double* in1,
                      double* out1, hipStream_t s) {
