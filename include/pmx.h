@@ -310,7 +310,8 @@ int tb_matrix(const Game* g, int32_t which, TbMatrix* out);
  * products for Ahat, U and V (one wavefront per row) and M's unit triangular
  * solve by pointer jumping along its chains (ceil(log2 depth) rounds).  Same
  * vectors as matvec_A_f64 / matvec_AT_f64.  PMX_ESTATE before tb_build.
- * Asynchronous. */
+ * The solve's vectors are the game's: calls that overlap (other streams or
+ * threads) race.  Asynchronous. */
 int matvec_A_tb(Game* g, const double* y_dev, double* out_dev, void* stream);
 int matvec_AT_tb(Game* g, const double* x_dev, double* out_dev, void* stream);
 
